@@ -137,13 +137,19 @@ typedef struct {
     int32_t flags;        /* OT_TUNE_* bits                                           */
 } ot_tuning;
 
-/* Sort the points by host leaf before the persistent pass: locate, then
- * 8-bit radix passes (all stable but the first) over the host ids down to groups of at most 64
- * consecutive ids (two passes up to 4 M leaves, three above) that carry
- * positions and forces into plan-owned buffers; the pass then visits the
- * points in that order and writes each result at its point's input row.
- * Neighbouring threads then share stencil nodes in cache and in the
- * workgroup's spreading table.  Needs the same ops for every instance. */
+/* Sort the points before the persistent pass, with radix passes (8 bits at
+ * most, all stable but the first) that carry positions and forces into
+ * plan-owned buffers; the pass then visits the points in that order and
+ * writes each result at its point's input row.  Runs of at least 64 points
+ * per block (a cube of 8^3 cells at the root table's level, or the leaves
+ * below one split root cell) are sorted by block, and each block with enough
+ * points is worked on as a dense grid of its stencil nodes in LDS; block,
+ * tile and grid then shape the pass over the other blocks' points only.
+ * Otherwise the points are sorted by host leaf, down to groups of at most 64
+ * consecutive ids (two passes up to 4 M leaves, three above), so that
+ * neighbouring threads share stencil nodes in cache and in the workgroup's
+ * spreading table.  Results are the same bit for bit (FIXED).  Needs the
+ * same ops for every instance. */
 #define OT_TUNE_SORT_POINTS 1
 
 /* Host-major pass for sorted plans whose instances interpolate or spread
@@ -158,7 +164,7 @@ typedef struct {
 
 /* Replay the plan's kernels through a captured HIP graph: one graph launch
  * per run instead of the plan's kernel launches (4 without point sorting,
- * 12 with it up to about 33 M points and 4 M leaves, more above), which
+ * 12 to 15 with it up to about 33 M points, more above), which
  * saves host time per run.  Off by default: on this GPU the graph launch
  * made a run about 7 us longer on 11 k points and no faster on 10^7. */
 #define OT_TUNE_GRAPH 4

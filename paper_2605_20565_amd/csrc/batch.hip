@@ -28,6 +28,9 @@ template <typename T, int MODE>
 const void *kbatch_fn(bool grad, bool small);
 template <typename T, int MODE>
 const void *hm_fn(int ops);
+template <typename T, int MODE>
+const void *block_fn(int ops, bool root);
+int block_threads(bool root);
 constexpr int kHmWindow = 256;   // points per window of the host-major pass (kHmThreads)
 
 namespace {
@@ -151,7 +154,8 @@ extern "C" int ot_batch_plan_create(const ot_tree *tree, const int64_t *offsets,
     p->grad_plan = (ops_union & kOpGrad) != 0;
     if (sort_points && p->n_points > 0) {
         const int64_t n = p->n_points;
-        point_sort_key_bits(tree->n_leaves, p->sort_shift, p->sort_bits);
+        p->use_blocks = !(tuning->flags & OT_TUNE_HOST_MAJOR) && (ops_all & ~kOpLocate) && blk_rule(tree, n);
+        p->sort_key = p->use_blocks ? point_sort_by_block(tree->view.nblk) : point_sort_by_host(tree->n_leaves);
         const size_t rec = ((ops_all & (kOpSpread | kOpGrad)) ? 6 : 3) * (size_t)n * (dtype == OT_F32 ? 4 : 8);
         hipError_t e = hipSuccess;
         for (int i = 0; i < 2 && e == hipSuccess; ++i) {
@@ -159,6 +163,7 @@ extern "C" int ot_batch_plan_create(const ot_tree *tree, const int64_t *offsets,
             if (e == hipSuccess) e = hipMalloc(&p->srec[i], rec);
         }
         if (e == hipSuccess) e = hipMalloc(&p->sws, (size_t)point_sort_ws_bytes(n));
+        if (e == hipSuccess && p->use_blocks) e = hipMalloc(&p->blk_mem, (size_t)blk_bytes(tree, n));
 
         if (e != hipSuccess) {
             (void)hipGetLastError();
@@ -199,7 +204,7 @@ extern "C" int ot_batch_plan_create(const ot_tree *tree, const int64_t *offsets,
     (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kfn, block, 0);
     if (per_cu <= 0) per_cu = 1;
     int grid = tuning && tuning->grid ? tuning->grid : std::max(1, cus) * per_cu;
-    if (p->n_tiles > 0 && grid > p->n_tiles) grid = (int)p->n_tiles;
+    if (p->n_tiles > 0 && grid > p->n_tiles && !p->use_blocks) grid = (int)p->n_tiles;
     p->grid = std::max(1, grid);
     if (p->use_hm) {
         const int hops = ops_all & (kOpInterp | kOpSpread);
@@ -220,6 +225,19 @@ extern "C" int ot_batch_plan_create(const ot_tree *tree, const int64_t *offsets,
         (void)hipGetLastError();
         ot_batch_plan_destroy(p);
         return fail(OT_ERR_OOM, "ot_batch_plan_create: device allocation failed");
+    }
+    if (p->use_blocks) {
+        blk_layout(tree, p->n_points, p->blk_mem, p->counter, &p->blk);
+        const int bops = ops_all & ~kOpLocate;
+        for (int root = 0; root < 2; ++root) {
+            const void *bfn = dtype == OT_F32 ? (mode == OT_SPREAD_FIXED ? block_fn<float, kModeFixed>(bops, root)
+                                                                         : block_fn<float, kModeAtomic>(bops, root))
+                                              : (mode == OT_SPREAD_FIXED ? block_fn<double, kModeFixed>(bops, root)
+                                                                         : block_fn<double, kModeAtomic>(bops, root));
+            int per = 0;
+            (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, bfn, block_threads(root), 0);
+            (root ? p->blk.root_grid : p->blk.sub_grid) = std::max(1, cus) * std::max(1, per);
+        }
     }
     if (!starts.empty()) {
         hipError_t e = hipMemcpy(p->tile_start, starts.data(), starts.size() * 8, hipMemcpyHostToDevice);
@@ -356,7 +374,7 @@ extern "C" int ot_batch_plan_destroy(ot_batch_plan *p)
     drop_graph(p);
     if (p->ev[0]) (void)hipEventDestroy(p->ev[0]);
     if (p->ev[1]) (void)hipEventDestroy(p->ev[1]);
-    for (void *q : {(void *)p->skv[0], (void *)p->skv[1], p->srec[0], p->srec[1], p->sws, p->fxws, (void *)p->fb_list})
+    for (void *q : {(void *)p->skv[0], (void *)p->skv[1], p->srec[0], p->srec[1], p->sws, p->fxws, (void *)p->fb_list, p->blk_mem})
         if (q) (void)hipFree(q);
     if (p->tile_start) (void)hipFree(p->tile_start);
     if (p->tile_info) (void)hipFree(p->tile_info);

@@ -10,6 +10,7 @@
 #include <vector>
 
 #include "batch_plan.h"
+#include "block_pass.h"
 #include "hm_pass.h"
 #include "ot_common.h"
 #include "point_sort.h"
@@ -19,18 +20,20 @@
 namespace ot {
 
 
-// Tiles handed over by the host-major pass: window indices and their count
-// (device), the window size, the number of points and the common ops.
+// Tiles handed over by the host-major pass (window indices) or the block pass
+// (ranges) and their count (device), the window size, the number of points and
+// the common ops.
 struct FbTiles {
     const uint32_t *list;
     const unsigned *count;
     int64_t pts, n;
     uint32_t ops;
+    const uint2 *ranges;   // instead of list: (first point, count) of each tile
 };
 
 // GRAD: the plan's ops are gradient passes (8, 10, 12), else forward (1..7).
 // S: slots of the workgroup's spreading table.  fb.list != null: the tiles
-// are the windows the host-major pass handed over, not the plan's table.
+// are the windows another pass handed over, not the plan's table.
 template <typename T, int MODE, bool PER, bool GRAD, int S>
 __global__ __launch_bounds__(512) void k_batch(TreeView tv, const int64_t *__restrict__ tile_start,
                                                const uint32_t *__restrict__ tile_info, int64_t n_tiles,
@@ -41,7 +44,7 @@ __global__ __launch_bounds__(512) void k_batch(TreeView tv, const int64_t *__res
                                                unsigned long long *__restrict__ facc, const FxState *__restrict__ fx,
                                                T *__restrict__ grad, FbTiles fb)
 {
-    if (fb.list) n_tiles = *fb.count;
+    if (fb.count) n_tiles = *fb.count;
     using Acc = typename AccType<T, MODE>::type;
     __shared__ uint32_t keys[S];
     __shared__ Acc vals[LdsSink<T, MODE, S>::kVals];
@@ -62,7 +65,11 @@ __global__ __launch_bounds__(512) void k_batch(TreeView tv, const int64_t *__res
         if (tile >= n_tiles) break;   // same value in every thread of the workgroup
         int64_t start, end;
         uint32_t info;
-        if (fb.list) {
+        if (fb.ranges) {   // sorted by block: the words hold no hosts
+            start = fb.ranges[tile].x;
+            end = start + fb.ranges[tile].y;
+            info = fb.ops << 24;
+        } else if (fb.list) {
             start = (int64_t)fb.list[tile] * fb.pts;
             end = start + fb.pts < fb.n ? start + fb.pts : fb.n;
             info = fb.ops << 24;
@@ -74,7 +81,7 @@ __global__ __launch_bounds__(512) void k_batch(TreeView tv, const int64_t *__res
         if constexpr (!GRAD) {
             switch (info >> 24) {
 #define OT_CASE(OPSV) \
-    case OPSV: track_range<T, OPSV, PER>(tv, start, end, kv, rs, pos, field, force, ids, vel, sink); break;
+    case OPSV: track_range<T, OPSV, PER>(tv, start, end, kv, rs, pos, field, force, ids, vel, sink, nullptr, nullptr, fb.ranges == nullptr); break;
                 OT_CASE(1) OT_CASE(2) OT_CASE(3) OT_CASE(4) OT_CASE(5) OT_CASE(6) OT_CASE(7)
 #undef OT_CASE
             default: break;
@@ -82,7 +89,7 @@ __global__ __launch_bounds__(512) void k_batch(TreeView tv, const int64_t *__res
         } else {
             switch (info >> 24) {
 #define OT_CASE(OPSV) \
-    case OPSV: track_range<T, OPSV, PER>(tv, start, end, kv, rs, pos, field, force, ids, vel, sink, grad); break;
+    case OPSV: track_range<T, OPSV, PER>(tv, start, end, kv, rs, pos, field, force, ids, vel, sink, grad, nullptr, fb.ranges == nullptr); break;
                 OT_CASE(kOpGrad) OT_CASE(kOpGrad | kOpInterp) OT_CASE(kOpGrad | kOpSpread)
 #undef OT_CASE
             default: break;
@@ -93,6 +100,13 @@ __global__ __launch_bounds__(512) void k_batch(TreeView tv, const int64_t *__res
     }
 }
 
+// Instantiated in block_inst.hip: the block pass over sorted points.
+template <typename T, int MODE>
+int enqueue_blocks(const ot_tree *t, BlkWork &w, int ops, const uint64_t *kv, const T *rec, const T *field, T *vel,
+                   T *fout, const FxWs &ws, T *grad, hipStream_t s);
+
+constexpr int kCounters = 8;
+
 template <typename T, int MODE>
 int enqueue(ot_batch_plan *p, const void *field, const void *force, const void *pos, int32_t *ids, void *vel,
             void *fout, void *grad, hipStream_t s)
@@ -100,14 +114,14 @@ int enqueue(ot_batch_plan *p, const void *field, const void *force, const void *
     const ot_tree *t = p->tree;
     const int64_t n = p->n_points;
     // counter[0]: the pass's tile queue, [1]: the per-point pass over handed-over
-    // windows, [2]: how many windows were handed over
+    // windows, [2]: how many windows were handed over, [3..7]: the block pass's
     int rc;
     const bool spread = (p->ops_union & kOpSpread) != 0;
     const FxWs ws = fx_ws(p->fxws);
     if (spread) {
-        if ((rc = spread_begin(t, ws, p->dtype, p->mode, 0, fout, s, p->counter, 3))) return rc;
+        if ((rc = spread_begin(t, ws, p->dtype, p->mode, 0, fout, s, p->counter, kCounters))) return rc;
     } else {
-        hipLaunchKernelGGL(k_fill<unsigned>, dim3(1), dim3(64), 0, s, p->counter, (int64_t)3, 0u);
+        hipLaunchKernelGGL(k_fill<unsigned>, dim3(1), dim3(64), 0, s, p->counter, (int64_t)kCounters, 0u);
     }
     const uint64_t *kv = nullptr;
     int rs = 3;
@@ -123,7 +137,7 @@ int enqueue(ot_batch_plan *p, const void *field, const void *force, const void *
         unsigned long long *maxbits = ((p->ops_all & kOpSpread) && p->mode == OT_SPREAD_FIXED)
                                           ? &ws.fx->maxbits
                                           : nullptr;
-        point_sort<T>(t->view, n, t->n_leaves, p->sort_shift, p->sort_bits, (const T *)pos,
+        point_sort<T>(t->view, n, p->sort_key, (const T *)pos,
                       carry_force ? (const T *)force : nullptr, (p->ops_all & kOpLocate) ? ids : nullptr, b, maxbits,
                       s, r);
         kv = r.kv;
@@ -153,7 +167,7 @@ int enqueue(ot_batch_plan *p, const void *field, const void *force, const void *
 #undef OT_KHM
         OT_HIP(hipGetLastError());
         // windows the host-major pass handed over, per point
-        const FbTiles fb{p->fb_list, p->counter + 2, (int64_t)kHmThreads, n, (uint32_t)sops};
+        const FbTiles fb{p->fb_list, p->counter + 2, (int64_t)kHmThreads, n, (uint32_t)sops, nullptr};
         constexpr int kS = SinkSlots<T, MODE>::value;
         if (t->view.periodic)
             hipLaunchKernelGGL((k_batch<T, MODE, true, false, kS>), dim3(p->grid), dim3(kHmThreads), 0, s, t->view,
@@ -169,13 +183,25 @@ int enqueue(ot_batch_plan *p, const void *field, const void *force, const void *
         OT_HIP(hipGetLastError());
         return OT_OK;
     }
+    const int bops = p->ops_all & ~kOpLocate;
+    FbTiles fb{};
+    unsigned *queue = p->counter;
+    int block = p->block;
+    if (p->use_blocks && n > 0) {
+        // dense blocks first, then the ranges of points in sparse ones
+        if ((rc = enqueue_blocks<T, MODE>(t, p->blk, bops, kv, kpos, (const T *)field, (T *)vel, (T *)fout, ws,
+                                          (T *)grad, s)))
+            return rc;
+        fb = FbTiles{nullptr, p->counter + kBlkRanges, 0, n, (uint32_t)bops, p->blk.ranges};
+        block = kBlkWindow;
+    }
 #define OT_KBATCH_S(PERV, GRADV, SV)                                                                               \
-    hipLaunchKernelGGL((k_batch<T, MODE, PERV, GRADV, SV>), dim3(p->grid), dim3(p->block), 0, s, t->view,            \
-                       p->tile_start, p->tile_info, p->n_tiles, p->counter, kv, rs, kpos, (const T *)field, kforce,  \
-                       kids, (T *)vel, (T *)fout, ws.acc, ws.fx, (T *)grad, FbTiles{})
+    hipLaunchKernelGGL((k_batch<T, MODE, PERV, GRADV, SV>), dim3(p->grid), dim3(block), 0, s, t->view,               \
+                       p->tile_start, p->tile_info, p->n_tiles, queue, kv, rs, kpos, (const T *)field, kforce,       \
+                       kids, (T *)vel, (T *)fout, ws.acc, ws.fx, (T *)grad, fb)
 #define OT_KBATCH(PERV, GRADV)                                                                                     \
     do {                                                                                                           \
-        if (p->small_table) OT_KBATCH_S(PERV, GRADV, kSmallSlots);                                                \
+        if (p->small_table && !p->use_blocks) OT_KBATCH_S(PERV, GRADV, kSmallSlots);                                                \
         else OT_KBATCH_S(PERV, GRADV, (SinkSlots<T, MODE>::value));                                                \
     } while (0)
     if (p->grad_plan) {

@@ -7,6 +7,24 @@
 #include <stdint.h>
 
 #include "ot_common.h"
+#include "point_sort.h"
+
+namespace ot {
+struct BlkTile;
+// Device memory of a run's block pass (block_pass.h): work words (counts and
+// queues), tiles of root cubes and of sub-tables, and the per-point pass's
+// ranges (first sorted point, count).
+struct BlkWork {
+    int64_t n;               // points
+    unsigned *words;
+    BlkTile *root_tiles, *sub_tiles;
+    uint2 *ranges;
+    int root_grid, sub_grid; // persistent workgroups
+};
+int64_t blk_bytes(const ot_tree *t, int64_t n);       // device bytes besides the words
+void blk_layout(const ot_tree *t, int64_t n, void *mem, unsigned *words, BlkWork *w);
+bool blk_rule(const ot_tree *t, int64_t n);           // whether sorted points take the block pass
+}  // namespace ot
 
 struct ot_batch_plan {
     const ot_tree *tree;
@@ -27,7 +45,7 @@ struct ot_batch_plan {
     hipEvent_t ev[2];
     // point sorting (OT_TUNE_SORT_POINTS)
     bool sort_points;
-    int sort_bits, sort_shift;
+    ot::PointSortKey sort_key;
     int ops_all;              // the common ops of every instance
     bool grad_plan;           // instances carry OT_OP_GRAD_POS
     bool small_table;         // tiles of at most kSmallTile points: the small spreading table
@@ -35,6 +53,9 @@ struct ot_batch_plan {
     void *srec[2];            // position (+ force) records in sorted order
     void *sws;                // counting workspace
     void *fxws;               // fixed-point spreading workspace (FIXED plans that spread)
+    bool use_blocks;          // block pass
+    ot::BlkWork blk;
+    void *blk_mem;
     // host-major pass (sorted forward plans with OT_TUNE_HOST_MAJOR)
     bool use_hm;
     int hm_grid;

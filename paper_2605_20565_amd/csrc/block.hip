@@ -1,0 +1,136 @@
+// Host side of the block pass (block_pass.h): its device memory and the rule
+// that chooses it.
+#include "batch_plan.h"
+#include "block_pass.h"
+
+namespace ot {
+
+namespace {
+int64_t align256(int64_t b) { return (b + 255) & ~int64_t(255); }
+// a dense block of c points gets ceil(c / kBlkTilePts) tiles; a run of sparse
+// blocks ends at a dense block or at the end of a workgroup's keys
+int64_t max_tiles(int64_t n) { return n / kBlkDense + n / kBlkTilePts + 1; }
+int64_t max_ranges(const ot_tree *t, int64_t n)
+{
+    return n / kBlkWindow + n / kBlkDense + (int64_t)t->view.nblk / 64 + 4;
+}
+
+// The blocks among the sorted words, and the passes' work: tiles of the blocks
+// with enough points (root cubes and sub-tables apart), and ranges of at most
+// kBlkWindow points for the per-point pass (sparser blocks next to each other
+// in the order, and points without a host).  A workgroup takes kBlkKeys - 1
+// consecutive keys; eight lanes find a key's first point, probing eight places
+// of the remaining range at once, so a search is ~log_9 n dependent loads.
+constexpr int kBlkKeys = 128;
+__global__ __launch_bounds__(kBlkKeys * 8) void k_block_bounds(const uint64_t *__restrict__ kv, int64_t n, uint32_t nblk,
+                                                               uint32_t blk1, unsigned *__restrict__ words,
+                                                               BlkTile *__restrict__ root_tiles,
+                                                               BlkTile *__restrict__ sub_tiles,
+                                                               uint2 *__restrict__ ranges)
+{
+    __shared__ uint32_t st[kBlkKeys];
+    __shared__ uint64_t sparse[kBlkKeys / 64];
+    __shared__ unsigned cnt[3], base[3];   // root tiles, sub-table tiles, ranges
+    const int grp = threadIdx.x >> 3, sub = threadIdx.x & 7, seg = (threadIdx.x & 63) & ~7;
+    const uint32_t key = blockIdx.x * (uint32_t)(kBlkKeys - 1) + (uint32_t)grp;
+    if (threadIdx.x < 3) cnt[threadIdx.x] = 0u;
+    // keys run up to nblk (no host); nblk + 1 starts at n
+    int64_t lo = key > nblk ? n : 0, hi = n;
+    while (__any(lo < hi)) {
+        const int64_t p = lo + (hi - lo) * (sub + 1) / 9;
+        const bool less = lo < hi && (uint32_t)(kv[p] >> 32) < key;
+        const unsigned m = (unsigned)(__ballot(less) >> seg) & 255u;
+        if (lo < hi) {
+            const int c = __popc(m);
+            const int64_t l = lo, len = hi - lo;
+            if (c > 0) lo = l + len * c / 9 + 1;
+            if (c < 8) hi = l + len * (c + 1) / 9;
+        }
+    }
+    if (sub == 0) st[grp] = (uint32_t)lo;
+    __syncthreads();
+    // one thread per key from here on
+    const int g = (int)threadIdx.x;
+    const uint32_t k = blockIdx.x * (uint32_t)(kBlkKeys - 1) + (uint32_t)g;
+    const bool mine = g < kBlkKeys - 1 && k <= nblk;
+    const uint32_t s = mine ? st[g] : 0u, c = mine ? st[g + 1] - s : 0u;
+    const int which = k < blk1 ? 0 : 1;
+    const bool dense = mine && k < nblk && c >= (uint32_t)kBlkDense;
+    if (g < kBlkKeys) {
+        const uint64_t b = __ballot(mine && !dense);
+        if ((g & 63) == 0) sparse[g >> 6] = b;
+    }
+    __syncthreads();
+    uint32_t nt = 0, nr = 0, at = 0, rs = 0, re = 0;
+    if (dense) {
+        nt = (c + kBlkTilePts - 1) / kBlkTilePts;
+        at = atomicAdd(&cnt[which], nt);
+    } else if (mine && (g == 0 || !((sparse[(g - 1) >> 6] >> ((g - 1) & 63)) & 1ull))) {
+        // the first of consecutive sparse keys takes the points of all of them
+        int e = g;   // the run's last key
+        const uint64_t z0 = ~sparse[0], z1 = ~sparse[1];
+        const uint64_t f0 = g < 64 ? z0 >> g : 0ull;
+        if (f0) e = g + __ffsll((unsigned long long)f0) - 1;
+        else {
+            const int h = g < 64 ? 0 : g - 64;
+            const uint64_t f1 = z1 >> h;
+            e = f1 ? 64 + h + __ffsll((unsigned long long)f1) - 1 : kBlkKeys;
+        }
+        rs = s;
+        re = st[min(e, kBlkKeys - 1)];
+        nr = (re - rs + kBlkWindow - 1) / kBlkWindow;
+        if (nr) at = atomicAdd(&cnt[2], nr);
+    }
+    __syncthreads();
+    if (threadIdx.x < 3)
+        base[threadIdx.x] = cnt[threadIdx.x] ? atomicAdd(&words[kBlkRootTiles + threadIdx.x], cnt[threadIdx.x]) : 0u;
+    __syncthreads();
+    if (nt) {
+        BlkTile *out = (which ? sub_tiles : root_tiles) + base[which] + at;
+        for (uint32_t i = 0; i < nt; ++i) {
+            const uint32_t b = (uint32_t)((uint64_t)c * i / nt), e = (uint32_t)((uint64_t)c * (i + 1) / nt);
+            out[i] = BlkTile{(int64_t)s + b, e - b, k};
+        }
+    }
+    for (uint32_t i = 0; i < nr; ++i)
+        ranges[base[2] + at + i] = make_uint2(rs + i * kBlkWindow, min((uint32_t)kBlkWindow, re - rs - i * kBlkWindow));
+}
+
+}  // namespace
+
+void enqueue_bounds(const ot_tree *t, BlkWork &w, const uint64_t *kv, hipStream_t s)
+{
+    const TreeView &tv = t->view;
+    const unsigned nb = (unsigned)((tv.nblk + kBlkKeys - 1) / (kBlkKeys - 1));   // keys 0 .. nblk
+    hipLaunchKernelGGL(k_block_bounds, dim3(nb), dim3(kBlkKeys * 8), 0, s, kv, w.n, (uint32_t)tv.nblk,
+                       (uint32_t)tv.blk1, w.words, w.root_tiles, w.sub_tiles, w.ranges);
+}
+
+int block_threads(bool root) { return root ? BlkThreads<float, true>::value : BlkThreads<float, false>::value; }
+
+int64_t blk_bytes(const ot_tree *t, int64_t n)
+{
+    return 2 * align256((int64_t)sizeof(BlkTile) * max_tiles(n)) + align256(8 * max_ranges(t, n));
+}
+
+void blk_layout(const ot_tree *t, int64_t n, void *mem, unsigned *words, BlkWork *w)
+{
+    char *p = (char *)mem;
+    w->n = n;
+    w->words = words;
+    w->root_tiles = (BlkTile *)p;
+    p += align256((int64_t)sizeof(BlkTile) * max_tiles(n));
+    w->sub_tiles = (BlkTile *)p;
+    p += align256((int64_t)sizeof(BlkTile) * max_tiles(n));
+    w->ranges = (uint2 *)p;
+}
+
+// Root cubes need a root of at least 8^3 cells.  Fewer than 64 points per
+// block on average leave most blocks to the per-point pass, which then does
+// better on points sorted by groups of 64 leaves.
+bool blk_rule(const ot_tree *t, int64_t n)
+{
+    return t->view.lev[0] >= kBlkBits && n >= 64 * (int64_t)t->view.nblk && n < (int64_t(1) << 31);
+}
+
+}  // namespace ot

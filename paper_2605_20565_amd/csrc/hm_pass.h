@@ -102,9 +102,8 @@ __device__ __forceinline__ uint32_t hm_exscan(uint32_t v, uint32_t *sh_w, uint32
 // sum of m of them, taken modulo 2^64, is m bits(1.5 2^52) + sum q exactly.
 __device__ __forceinline__ unsigned long long fx_bits(double w, double fs)
 {
-    return (unsigned long long)__double_as_longlong(fma(w, fs, 6755399441055744.0));
+    return (unsigned long long)__double_as_longlong(fma(w, fs, kFxMagic));
 }
-constexpr unsigned long long kFxMagicBits = 0x4338000000000000ull;   // bits of 1.5 * 2^52
 
 // One node's sums of a run (cnt contributions per component) to its table
 // slot, or to device memory when the node's leaf has no slot.

@@ -52,7 +52,15 @@ struct TreeView {
     // cell m when all 8 are leaves of level lev[0] (then child c's leaf is
     // entry + c), kSplit otherwise.
     const uint32_t *summary;
+    // Block keys (block_of): every 8^3 cube of root cells, then every
+    // sub-table of table level 1, 2, ... is one block.  blk1: number of root
+    // cubes (the key of the first level-1 sub-table); blk_base[t]: key of
+    // level t's first sub-table (device memory, like pool_off); nblk: all
+    // blocks.  Only trees with lev[0] >= kBlkBits have root cubes.
+    int32_t blk1, nblk;
+    const int64_t *blk_base;
 };
+constexpr int kBlkBits = 3;
 
 // Spread the low 10 bits of v so that bit b lands on bit 3b.
 __host__ __device__ __forceinline__ uint32_t part1by2(uint32_t v)
@@ -124,8 +132,10 @@ __device__ __forceinline__ int64_t step1_index(const TreeView &tv, uint32_t e, u
 // the root).  The level of each table step is computed and its pool offset
 // read from device memory: a lane-dependent index into the by-value tree
 // view would put a copy of the struct in per-lane scratch memory.
+// BLK: also the block key of the sub-table that holds the leaf.
+template <bool BLK = false>
 __device__ __forceinline__ uint32_t descend_from_level2(const TreeView &tv, uint32_t e, uint32_t ix, uint32_t iy,
-                                                        uint32_t iz)
+                                                        uint32_t iz, uint32_t *key = nullptr)
 {
     int lv = min(tv.lev[0] + 3, tv.L);
     for (int t = 2; t < tv.nlev && (e & kSplit); ++t) {
@@ -134,6 +144,7 @@ __device__ __forceinline__ uint32_t descend_from_level2(const TreeView &tv, uint
         const uint32_t m = (1u << d) - 1u;
         const uint32_t sub = interleave3((ix >> s) & m, (iy >> s) & m, (iz >> s) & m);
         const int64_t po = ((const __attribute__((address_space(1))) int64_t *)tv.pool_off)[t];
+        if (BLK) *key = (uint32_t)((const __attribute__((address_space(1))) int64_t *)tv.blk_base)[t] + (e & ~kSplit);
         e = ld_table(tv, po + (int64_t)(e & ~kSplit) * (int64_t(1) << (3 * d)) + sub);
         lv = nl;
     }

@@ -10,7 +10,7 @@
 // LSD passes, see point_sort_key_bits).
 //
 // A pass takes tiles of 2048 points: the keys are staged in LDS with
-// coalesced loads, ranked by the digit (stably, with eight 1-bit splits,
+// coalesced loads, ranked by the digit (stably, with one 1-bit split per digit bit,
 // except in the first pass, whose order no later pass relies on: there each
 // key takes the next slot of its digit from an LDS counter), and every
 // digit's run is written contiguously; the records, read once in
@@ -128,11 +128,11 @@ __device__ __forceinline__ void block_max_to(unsigned long long v, unsigned long
 // A thread's kItems points go through the descent together: all positions,
 // then all root-table loads, then the deeper levels, so that the table loads
 // (the pass's latency) are in flight at once rather than one after another.
-template <typename T>
+template <typename T, bool BLK>
 __global__ __launch_bounds__(kThreads) void k_point_keys(TreeView tv, int64_t n, const T *__restrict__ pos,
                                                          int32_t *__restrict__ ids, uint64_t *__restrict__ kv,
-                                                         uint32_t none, int shift, uint32_t *__restrict__ counts,
-                                                         int nblocks)
+                                                         uint32_t none, int shift, uint32_t dmask,
+                                                         uint32_t *__restrict__ counts, int nblocks)
 {
     __shared__ uint32_t hist[kBuckets];
     for (int i = threadIdx.x; i < kBuckets; i += kThreads) hist[i] = 0;
@@ -174,28 +174,32 @@ __global__ __launch_bounds__(kThreads) void k_point_keys(TreeView tv, int64_t n,
     uint32_t e1[kItems];
 #pragma unroll
     for (int j = 0; j < kItems; ++j) e1[j] = ld_table(tv, step1_index(tv, e[j], I[j][0], I[j][1], I[j][2]));
+    uint32_t key[kItems];
 #pragma unroll
     for (int j = 0; j < kItems; ++j) {
+        if (BLK) key[j] = (e[j] & kSplit) ? (uint32_t)tv.blk1 + (e[j] & ~kSplit) : root[j] >> (3 * kBlkBits);
         if (e[j] & kSplit) e[j] = e1[j];
-        if (e[j] & kSplit) e[j] = descend_from_level2(tv, e[j], I[j][0], I[j][1], I[j][2]);
+        if (e[j] & kSplit) e[j] = descend_from_level2<BLK>(tv, e[j], I[j][0], I[j][1], I[j][2], &key[j]);
+        if (!BLK) key[j] = e[j];
+        else if (!ok[j]) key[j] = none;
     }
 #pragma unroll
     for (int j = 0; j < kItems; ++j) {
         const int64_t k = base + j * kThreads + threadIdx.x;
         if (k < n) {
-            // the host's whole leaf entry (level << 26 | id): the tracking pass
-            // takes it from here instead of searching again
+            // by host: the whole leaf entry (level << 26 | id), which the
+            // tracking pass takes from here instead of searching again
             if (ids) ids[k] = ok[j] ? (int32_t)(e[j] & kIdMask) : -1;
-            kv[k] = ((uint64_t)e[j] << 32) | (uint32_t)k;
-            atomicAdd(&hist[((e[j] & kIdMask) >> shift) & (kBuckets - 1)], 1u);
+            kv[k] = ((uint64_t)key[j] << 32) | (uint32_t)k;
+            atomicAdd(&hist[((key[j] & kIdMask) >> shift) & dmask], 1u);
         }
     }
     __syncthreads();
-    for (int d = threadIdx.x; d < kBuckets; d += kThreads) counts[(int64_t)d * nblocks + tile] = hist[d];
+    for (int d = threadIdx.x; d <= (int)dmask; d += kThreads) counts[(int64_t)d * nblocks + tile] = hist[d];
 }
 
 __global__ __launch_bounds__(kThreads) void k_point_hist(const uint64_t *__restrict__ kv, int64_t n, int shift,
-                                                         uint32_t *__restrict__ counts, int nblocks)
+                                                         uint32_t dmask, uint32_t *__restrict__ counts, int nblocks)
 {
     __shared__ uint32_t hist[kBuckets];
     for (int i = threadIdx.x; i < kBuckets; i += kThreads) hist[i] = 0;
@@ -211,9 +215,9 @@ __global__ __launch_bounds__(kThreads) void k_point_hist(const uint64_t *__restr
     }
 #pragma unroll
     for (int j = 0; j < kItems; ++j)
-        if (base + j * kThreads + threadIdx.x < n) atomicAdd(&hist[((hk[j] & kIdMask) >> shift) & (kBuckets - 1)], 1u);
+        if (base + j * kThreads + threadIdx.x < n) atomicAdd(&hist[((hk[j] & kIdMask) >> shift) & dmask], 1u);
     __syncthreads();
-    for (int d = threadIdx.x; d < kBuckets; d += kThreads) counts[(int64_t)d * nblocks + tile] = hist[d];
+    for (int d = threadIdx.x; d <= (int)dmask; d += kThreads) counts[(int64_t)d * nblocks + tile] = hist[d];
 }
 
 // One counting pass over tiles of kTile points, stable except the first
@@ -224,7 +228,7 @@ template <typename T, int R>
 __global__ __launch_bounds__(kThreads) void k_point_scatter(
     const uint64_t *__restrict__ kin, const T *__restrict__ rin, const T *__restrict__ pos,
     const T *__restrict__ force, uint64_t *__restrict__ kout, T *__restrict__ rout, int64_t n, int shift,
-    const uint32_t *__restrict__ offs, const uint32_t *__restrict__ offs_hi, int nblocks,
+    int pbits, const uint32_t *__restrict__ offs, const uint32_t *__restrict__ offs_hi, int nblocks,
     unsigned long long *__restrict__ maxbits, int first)
 {
     __shared__ uint32_t sk[kPadded];
@@ -235,6 +239,7 @@ __global__ __launch_bounds__(kThreads) void k_point_scatter(
     __shared__ uint32_t dcur[kBuckets];
     __shared__ unsigned long long sh_max[kThreads / 64];
 
+    const uint32_t dmask = (1u << pbits) - 1u;
     const int tile = xcd_tile(nblocks);
     const int64_t base = (int64_t)tile * kTile;
     const int64_t rem = n - base;
@@ -292,7 +297,7 @@ __global__ __launch_bounds__(kThreads) void k_point_scatter(
     for (int j = 0; j < kItems; ++j) {
         const int li = j * kThreads + threadIdx.x;
         const uint32_t key = kk[j];
-        if (li < valid) atomicAdd(&dcount[((key & kIdMask) >> shift) & (kBuckets - 1)], 1u);
+        if (li < valid) atomicAdd(&dcount[((key & kIdMask) >> shift) & dmask], 1u);
         sk[pad(li)] = key;
         si[pad(li)] = (uint16_t)li;
     }
@@ -312,7 +317,7 @@ __global__ __launch_bounds__(kThreads) void k_point_scatter(
         for (int j = 0; j < kItems; ++j) {
             const int li = j * kThreads + threadIdx.x;
             if (li < valid) {
-                const uint32_t d = ((kk[j] & kIdMask) >> shift) & (kBuckets - 1);
+                const uint32_t d = ((kk[j] & kIdMask) >> shift) & dmask;
                 const uint32_t p = dstart[d] + atomicAdd(&dcur[d], 1u);
                 sk[pad((int)p)] = kk[j];
                 si[pad((int)p)] = (uint16_t)li;
@@ -320,7 +325,7 @@ __global__ __launch_bounds__(kThreads) void k_point_scatter(
         }
         __syncthreads();
     } else {
-        // stable: eight one-bit splits, each a block-wide scan of the zeros
+        // stable: one-bit splits, each a block-wide scan of the zeros
         uint32_t k[kItems];
         uint32_t x[kItems];
         const int t0 = threadIdx.x * kItems;
@@ -330,7 +335,7 @@ __global__ __launch_bounds__(kThreads) void k_point_scatter(
             x[j] = si[pad(t0 + j)];
         }
         __syncthreads();
-        for (int b = 0; b < kBits; ++b) {
+        for (int b = 0; b < pbits; ++b) {
             uint32_t zeros = 0;
 #pragma unroll
             for (int j = 0; j < kItems; ++j) zeros += 1u - (((k[j] & kIdMask) >> (shift + b)) & 1u);
@@ -346,7 +351,7 @@ __global__ __launch_bounds__(kThreads) void k_point_scatter(
                 si[pad((int)p)] = (uint16_t)x[j];
             }
             __syncthreads();
-            if (b + 1 < kBits) {
+            if (b + 1 < pbits) {
 #pragma unroll
                 for (int j = 0; j < kItems; ++j) {
                     k[j] = sk[pad(t0 + j)];
@@ -382,7 +387,7 @@ __global__ __launch_bounds__(kThreads) void k_point_scatter(
     for (int j = 0; j < kItems; ++j) {
         const int i = j * kThreads + threadIdx.x;
         const uint32_t key = sk[pad(i)];
-        const uint32_t d = ((key & kIdMask) >> shift) & (kBuckets - 1);
+        const uint32_t d = ((key & kIdMask) >> shift) & dmask;
         const int64_t oi = (int64_t)d * nblocks + tile;
         const int64_t o = (int64_t)offs[oi] + (offs_hi ? (int64_t)offs_hi[oi / kScanBlock] : 0);
         dstv[j] = i < valid ? o + (i - (int)dstart[d]) : -1;
@@ -435,27 +440,35 @@ __global__ __launch_bounds__(kThreads) void k_point_scatter(
 }
 
 template <typename T, int R>
-void sort_passes(const TreeView &tv, int64_t n, int64_t n_leaves, int shift, int bits, const T *pos, const T *force,
-                 int32_t *ids, PointSortBufs<T> &b, unsigned long long *maxbits, hipStream_t s,
-                 PointSortResult<T> &out)
+void sort_passes(const TreeView &tv, int64_t n, const PointSortKey &key, const T *pos, const T *force, int32_t *ids,
+                 PointSortBufs<T> &b, unsigned long long *maxbits, hipStream_t s, PointSortResult<T> &out)
 {
     const int nb = (int)((n + kTile - 1) / kTile);
-    const int64_t nc = (int64_t)kBuckets * nb;
+    // the passes share the key bits evenly: fewer digits make longer runs
+    const int passes = (key.bits + kBits - 1) / kBits;
+    const int pbits = (key.bits + passes - 1) / passes;
+    const uint32_t dmask = (1u << pbits) - 1u;
+    const int64_t nc = (int64_t)(dmask + 1) * nb;
     uint32_t *counts = (uint32_t *)b.ws, *offs = counts + nc, *tmp = offs + nc;
-    hipLaunchKernelGGL(k_point_keys<T>, dim3(nb), dim3(kThreads), 0, s, tv, n, pos, ids, b.kv[0],
-                       (uint32_t)n_leaves, shift, counts, nb);
+    if (key.blocks)
+        hipLaunchKernelGGL((k_point_keys<T, true>), dim3(nb), dim3(kThreads), 0, s, tv, n, pos, ids, b.kv[0], key.none,
+                           key.shift, dmask, counts, nb);
+    else
+        hipLaunchKernelGGL((k_point_keys<T, false>), dim3(nb), dim3(kThreads), 0, s, tv, n, pos, ids, b.kv[0], key.none,
+                           key.shift, dmask, counts, nb);
     const uint64_t *kin = b.kv[0];
     const T *rin = nullptr;
     int cur = 0;
-    for (int sh = 0; sh < bits; sh += kBits) {
+    for (int p = 0; p < passes; ++p) {
         const int o = cur ^ 1;   // write buffer: 1, 0, 1, ...
-        if (sh > 0) hipLaunchKernelGGL(k_point_hist, dim3(nb), dim3(kThreads), 0, s, kin, n, shift + sh, counts, nb);
+        const int sh = key.shift + p * pbits;
+        if (p > 0) hipLaunchKernelGGL(k_point_hist, dim3(nb), dim3(kThreads), 0, s, kin, n, sh, dmask, counts, nb);
         // the digit offsets: each 2048-count block's own scan, plus the
         // blocks' scanned sums, which the scatter adds (one launch less)
         const uint32_t *offs_hi = exclusive_scan_split(counts, offs, nc, tmp, s);
         hipLaunchKernelGGL((k_point_scatter<T, R>), dim3(nb), dim3(kThreads), 0, s, kin, rin, pos, force, b.kv[o],
-                           b.rec[o], n, shift + sh, (const uint32_t *)offs, offs_hi, nb,
-                           sh == 0 ? maxbits : (unsigned long long *)nullptr, sh == 0 ? 1 : 0);
+                           b.rec[o], n, sh, pbits, (const uint32_t *)offs, offs_hi, nb,
+                           p == 0 ? maxbits : (unsigned long long *)nullptr, p == 0 ? 1 : 0);
         kin = b.kv[o];
         rin = b.rec[o];
         cur = o;
@@ -474,18 +487,18 @@ int64_t point_sort_ws_bytes(int64_t n)
 }
 
 template <typename T>
-void point_sort(const TreeView &tv, int64_t n, int64_t n_leaves, int shift, int bits, const T *pos, const T *force,
-                int32_t *ids, PointSortBufs<T> &b, unsigned long long *maxbits, hipStream_t s,
-                PointSortResult<T> &out)
+void point_sort(const TreeView &tv, int64_t n, const PointSortKey &key, const T *pos, const T *force, int32_t *ids,
+                PointSortBufs<T> &b, unsigned long long *maxbits, hipStream_t s, PointSortResult<T> &out)
 {
-    if (force) sort_passes<T, 6>(tv, n, n_leaves, shift, bits, pos, force, ids, b, maxbits, s, out);
-    else sort_passes<T, 3>(tv, n, n_leaves, shift, bits, pos, nullptr, ids, b, nullptr, s, out);
+    if (force) sort_passes<T, 6>(tv, n, key, pos, force, ids, b, maxbits, s, out);
+    else sort_passes<T, 3>(tv, n, key, pos, nullptr, ids, b, nullptr, s, out);
     out.stride = force ? 6 : 3;
 }
 
-template void point_sort<float>(const TreeView &, int64_t, int64_t, int, int, const float *, const float *, int32_t *,
-                                PointSortBufs<float> &, unsigned long long *, hipStream_t, PointSortResult<float> &);
-template void point_sort<double>(const TreeView &, int64_t, int64_t, int, int, const double *, const double *,
+template void point_sort<float>(const TreeView &, int64_t, const PointSortKey &, const float *, const float *,
+                                int32_t *, PointSortBufs<float> &, unsigned long long *, hipStream_t,
+                                PointSortResult<float> &);
+template void point_sort<double>(const TreeView &, int64_t, const PointSortKey &, const double *, const double *,
                                  int32_t *, PointSortBufs<double> &, unsigned long long *, hipStream_t,
                                  PointSortResult<double> &);
 

@@ -103,10 +103,11 @@ struct AccType<T, kModeFixed> { using type = unsigned long long; };
 // integer (ties to even), held in two's complement in the low mantissa bits.
 // For FP32 inputs the product is exact, so q is exactly rint of the exact
 // value w F 2^s.  fs = (double)F * 2^s is exact and formed once per point.
+constexpr double kFxMagic = 6755399441055744.0;                          // 1.5 * 2^52
+constexpr unsigned long long kFxMagicBits = 0x4338000000000000ull;   // its bits
 __device__ __forceinline__ unsigned long long fx_round_fma(double w, double fs)
 {
-    const double magic = 6755399441055744.0;   // 1.5 * 2^52
-    return (unsigned long long)(__double_as_longlong(fma(w, fs, magic)) - __double_as_longlong(magic));
+    return (unsigned long long)__double_as_longlong(fma(w, fs, kFxMagic)) - kFxMagicBits;
 }
 
 template <typename T, int MODE>
@@ -307,8 +308,9 @@ __device__ __forceinline__ bool host_from_id(const TreeView &tv, int32_t h, uint
 // force[rs k + 0..2] (rs = 3 for the caller's arrays, the record stride for
 // sorted records).  For sorted points, word is the point's sort word (the
 // host's leaf entry << 32 | input index): the host comes from the word,
-// found by the sort's key pass on the same position, and the per-point
-// outputs go to the input index.  Otherwise the host is hid[k] when the
+// found by the sort's key pass on the same position (word_host; else the
+// word holds no host and the descent finds it), and the per-point outputs go
+// to the input index.  Otherwise the host is hid[k] when the
 // caller gives host ids (Algorithm 1's host_cell_id; -1 or an id out of
 // range: no host), else the table descent finds it.  With kOpGrad, force[k]
 // is also the vector the gradient contracts the field with, and the
@@ -318,14 +320,15 @@ __device__ __forceinline__ void track_point_at(const TreeView &tv, int64_t k, bo
                                                const T (&X)[3], int rs, const T *__restrict__ field,
                                                const T *__restrict__ force, int32_t *__restrict__ ids,
                                                T *__restrict__ vel, Sink &sink, T *__restrict__ grad,
-                                               const int32_t *__restrict__ hid, const T *Fpre = nullptr)
+                                               const int32_t *__restrict__ hid, const T *Fpre = nullptr,
+                                               bool word_host = true)
 {
     const int64_t kd = sorted ? (int64_t)(uint32_t)word : k;
     const int64_t kp = (int64_t)rs * k;
     uint32_t I[3];
     bool ok = point_cell<T>(tv, X[0], X[1], X[2], I);
     uint32_t e = 0u;
-    if (sorted) e = (uint32_t)(word >> 32);
+    if (sorted && word_host) e = (uint32_t)(word >> 32);
     else if (hid) ok = host_from_id(tv, hid[k], e) && ok;
     else if (ok) e = descend(tv, I[0], I[1], I[2]);
     if (!ok) e = 0u;
@@ -591,7 +594,8 @@ __device__ __forceinline__ void track_range(const TreeView &tv, int64_t start, i
                                             const uint64_t *__restrict__ kv, int rs, const T *__restrict__ pos,
                                             const T *__restrict__ field, const T *__restrict__ force,
                                             int32_t *__restrict__ ids, T *__restrict__ vel, Sink &sink,
-                                            T *__restrict__ grad = nullptr, const int32_t *__restrict__ hid = nullptr)
+                                            T *__restrict__ grad = nullptr, const int32_t *__restrict__ hid = nullptr,
+                                            bool word_host = true)
 {
     if (!kv) {
         for (int64_t k = start + threadIdx.x; k < end; k += blockDim.x)
@@ -629,7 +633,7 @@ __device__ __forceinline__ void track_range(const TreeView &tv, int64_t start, i
             Fn[2] = force[(int64_t)rs * kc + 2];
         }
         track_point_at<T, OPS, PER, Sink>(tv, k, true, w, X, rs, field, force, ids, vel, sink, grad, nullptr,
-                                          kF ? F : nullptr);
+                                          kF ? F : nullptr, word_host);
         if (!more) break;
         k = kn;
         w = wn;

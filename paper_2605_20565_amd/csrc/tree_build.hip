@@ -514,14 +514,27 @@ extern "C" int ot_build_tree(const uint64_t *keys, const uint8_t *levels, int64_
     // summary one level up (an eighth of the root: most lookups of points in
     // random order then hit a table small enough for one XCD's L2)
     const int64_t off_at = (entries + 1) & ~int64_t(1);
-    const int64_t sum_at = off_at + 2 * kMaxTabLevels;
+    // (both pool offsets and block-key bases, int64 each)
+    const int64_t sum_at = off_at + 4 * kMaxTabLevels;
     const int64_t sum_cells = tv.lev[0] >= 1 ? (int64_t(1) << (3 * (tv.lev[0] - 1))) : 0;
     DevBuf table, flags, ids, stmp;
     if ((rc = dalloc(table, (sum_at + sum_cells) * 4)) || (rc = dalloc(flags, n * 4)) || (rc = dalloc(ids, n * 4)) ||
         (rc = dalloc(stmp, scan_tmp_words(n) * 4)))
         return rc;
     hipLaunchKernelGGL(k_fill_u32, dim3(2048), dim3(256), 0, s, (uint32_t *)table.p, entries, 0xFFFFFFFFu);
-    OT_HIP(hipMemcpyAsync((uint32_t *)table.p + off_at, tv.off, sizeof(tv.off), hipMemcpyHostToDevice, s));
+    // block keys: the root cubes, then the sub-tables level by level
+    int64_t heads[2 * kMaxTabLevels] = {0};
+    std::memcpy(heads, tv.off, sizeof(tv.off));
+    int64_t *bb = heads + kMaxTabLevels;
+    bb[1] = tv.lev[0] >= kBlkBits ? int64_t(1) << (3 * (tv.lev[0] - kBlkBits)) : 0;
+    tv.blk1 = (int32_t)bb[1];
+    int64_t blocks = bb[1];
+    for (int t = 1; t < tv.nlev; ++t) {
+        bb[t] = blocks;
+        blocks += (int64_t)hcnt[t - 1];
+    }
+    tv.nblk = (int32_t)blocks;   // at most 8^5 + n_leaves / 8
+    OT_HIP(hipMemcpyAsync((uint32_t *)table.p + off_at, heads, sizeof(heads), hipMemcpyHostToDevice, s));
     for (int t = 0; t < tv.nlev; ++t) {
         if (t + 1 < tv.nlev) {
             hipLaunchKernelGGL(k_split_flags, dim3(nblk(n)), dim3(256), 0, s, ks, (const uint8_t *)lvs.p, n, L,
@@ -559,6 +572,7 @@ extern "C" int ot_build_tree(const uint64_t *keys, const uint8_t *levels, int64_
     tr->table_entries = entries;
     tv.table = tr->table;
     tv.pool_off = (const int64_t *)(tr->table + off_at);
+    tv.blk_base = tv.pool_off + kMaxTabLevels;
     tv.summary = sum_cells ? tr->table + sum_at : nullptr;
     tv.levels = tr->levels;
     tv.nleaf = (int32_t)n;
