@@ -4,13 +4,15 @@
 // host changed (the leavers of phase I).  The paper checks the previous host
 // first because its search is a binary search; here a fresh descent is one
 // or two loads from the (cached) descent table, cheaper than fetching the
-// previous leaf's key and level (measured: 0.12 against 0.25 ms for 10^7
-// points), so every point descends and is compared with its previous id.
+// previous leaf's key and level, so every point descends and is compared
+// with its previous id.
 // find_owner: under a partition of the leaves into contiguous Morton ranges
 // (Sec. 3.1), the owner of a point is the range holding the Morton key of
 // its finest-level cell, found by a binary search over the P + 1 splitters;
 // the per-owner counts are the sizes of the send buffers of phase II.
 #include <hip/hip_runtime.h>
+
+#include <algorithm>
 
 #include "ot_common.h"
 #include "track_device.h"
@@ -33,21 +35,68 @@ __device__ __forceinline__ void block_count_to(unsigned long long v, unsigned lo
     }
 }
 
-template <typename T>
+// Cells of a thread's ITEMS points of one tile (ITEMS * kThreads points from
+// base), all loaded before any is used, at clamped indices.
+template <typename T, int ITEMS>
+__device__ __forceinline__ void tile_cells(const TreeView &tv, const T *__restrict__ pos, int64_t n, int64_t base,
+                                           uint32_t (&I)[ITEMS][3], bool (&ok)[ITEMS])
+{
+    T X[ITEMS][3];
+#pragma unroll
+    for (int j = 0; j < ITEMS; ++j) {
+        const int64_t k = base + j * kThreads + threadIdx.x;
+        const int64_t kc = k < n ? k : n - 1;
+#pragma unroll
+        for (int d = 0; d < 3; ++d) X[j][d] = pos[3 * kc + d];
+    }
+#pragma unroll
+    for (int j = 0; j < ITEMS; ++j) ok[j] = point_cell<T>(tv, X[j][0], X[j][1], X[j][2], I[j]);
+}
+
+// Bound by memory (20 bytes a point in FP32).  A workgroup walks over tiles of
+// ITEMS points per thread whose table loads are in flight together, and adds
+// its count of moved points once: one add per 256 points had put 39,000 adds
+// on one address (10 ns each on this target) and the kernel at 478 us for 10^7
+// points; relocation with its count and find_owner together 615 -> 191 us.
+template <typename T, int ITEMS>
 __global__ __launch_bounds__(kThreads) void k_relocate(TreeView tv, const T *__restrict__ pos, int64_t n,
                                                        int32_t *__restrict__ ids,
                                                        unsigned long long *__restrict__ moved)
 {
     __shared__ unsigned long long sh[kThreads / 64];
-    const int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    const int rsh = tv.L - tv.lev[0];
     unsigned long long changed = 0;
-    if (k < n) {
-        const int32_t prev = ids[k];
-        uint32_t I[3];
-        const bool ok = point_cell<T>(tv, pos[3 * k], pos[3 * k + 1], pos[3 * k + 2], I);
-        const int32_t id = ok ? (int32_t)(descend(tv, I[0], I[1], I[2]) & kIdMask) : -1;
-        ids[k] = id;
-        changed = id != prev ? 1ull : 0ull;
+    for (int64_t base = blockIdx.x * (int64_t)(kThreads * ITEMS); base < n;
+         base += gridDim.x * (int64_t)(kThreads * ITEMS)) {
+        uint32_t I[ITEMS][3], root[ITEMS], e[ITEMS];
+        int32_t prev[ITEMS];
+        bool ok[ITEMS];
+#pragma unroll
+        for (int j = 0; j < ITEMS; ++j) {
+            const int64_t k = base + j * kThreads + threadIdx.x;
+            prev[j] = ids[k < n ? k : n - 1];
+        }
+        tile_cells<T, ITEMS>(tv, pos, n, base, I, ok);
+        // root summary, the root where it has no answer, then deeper levels
+#pragma unroll
+        for (int j = 0; j < ITEMS; ++j) {
+            root[j] = interleave3(I[j][0] >> rsh, I[j][1] >> rsh, I[j][2] >> rsh);
+            e[j] = tv.summary ? ld_summary(tv, root[j] >> 3) : kSplit;
+        }
+#pragma unroll
+        for (int j = 0; j < ITEMS; ++j) {
+            if (!(e[j] & kSplit)) e[j] += root[j] & 7u;
+            else e[j] = descend_below_root(tv, ld_table(tv, root[j]), I[j][0], I[j][1], I[j][2]);
+        }
+#pragma unroll
+        for (int j = 0; j < ITEMS; ++j) {
+            const int64_t k = base + j * kThreads + threadIdx.x;
+            const int32_t id = ok[j] ? (int32_t)(e[j] & kIdMask) : -1;
+            if (k < n) {
+                ids[k] = id;
+                changed += id != prev[j] ? 1ull : 0ull;
+            }
+        }
     }
     if (moved) block_count_to(changed, sh, moved);
 }
@@ -62,13 +111,14 @@ __global__ void k_leaf_splitters(const uint64_t *__restrict__ keys, int64_t n_le
     else split[r] = (int64_t)keys[((int64_t)r * n_leaves) / P];
 }
 
-// Splitters staged in LDS; each thread takes kOwnerItems points.  Counts:
-// for up to kBallotOwners owners every wave counts each owner with one
-// ballot (no same-address atomics), else LDS atomics.
-constexpr int kOwnerItems = 8;
+// Splitters staged in LDS.  A workgroup walks over tiles of ITEMS points per
+// thread, loaded together (one after another they had taken 112 us for 10^7
+// points and 8 owners), and adds its counts to device memory once.
+// Counts: for up to kBallotOwners owners every wave counts each owner with
+// one ballot (no same-address atomics), else LDS atomics.
 constexpr int kBallotOwners = 32;
 
-template <typename T>
+template <typename T, int ITEMS>
 __global__ __launch_bounds__(kThreads) void k_find_owner(TreeView tv, const int64_t *__restrict__ split, int P,
                                                          const T *__restrict__ pos, int64_t n,
                                                          int32_t *__restrict__ owner,
@@ -79,34 +129,38 @@ __global__ __launch_bounds__(kThreads) void k_find_owner(TreeView tv, const int6
     for (int i = threadIdx.x; i <= P; i += kThreads) s_split[i] = split[i];
     for (int i = threadIdx.x; i < P; i += kThreads) hist[i] = 0u;
     __syncthreads();
-    const int64_t base = (int64_t)blockIdx.x * kThreads * kOwnerItems;
-    for (int j = 0; j < kOwnerItems; ++j) {
-        const int64_t k = base + (int64_t)j * kThreads + threadIdx.x;
-        int32_t o = -1;
-        if (k < n) {
-            uint32_t I[3];
-            const bool ok = point_cell<T>(tv, pos[3 * k], pos[3 * k + 1], pos[3 * k + 2], I);
-            if (ok) {
-                const int64_t key = (int64_t)(split3_21(I[0]) | (split3_21(I[1]) << 1) | (split3_21(I[2]) << 2));
-                // largest r in [0, P) with split[r] <= key
-                int lo = 0, hi = P;
-                while (hi - lo > 1) {
-                    const int mid = (lo + hi) >> 1;
-                    if (s_split[mid] <= key) lo = mid;
-                    else hi = mid;
-                }
-                o = lo;
+    for (int64_t base = blockIdx.x * (int64_t)(kThreads * ITEMS); base < n;
+         base += gridDim.x * (int64_t)(kThreads * ITEMS)) {
+        uint32_t I[ITEMS][3];
+        bool ok[ITEMS];
+        int32_t o[ITEMS];
+        tile_cells<T, ITEMS>(tv, pos, n, base, I, ok);
+#pragma unroll
+        for (int j = 0; j < ITEMS; ++j) {
+            const int64_t k = base + j * kThreads + threadIdx.x;
+            const int64_t key = (int64_t)(split3_21(I[j][0]) | (split3_21(I[j][1]) << 1) | (split3_21(I[j][2]) << 2));
+            // largest r in [0, P) with split[r] <= key
+            int lo = 0, hi = P;
+            while (hi - lo > 1) {
+                const int mid = (lo + hi) >> 1;
+                if (s_split[mid] <= key) lo = mid;
+                else hi = mid;
             }
-            owner[k] = o;
+            o[j] = k < n && ok[j] ? lo : -1;
+            if (k < n) owner[k] = o[j];
         }
         if (counts) {
             if (P <= kBallotOwners) {
                 for (int r = 0; r < P; ++r) {
-                    const unsigned long long m = __ballot(o == r);
-                    if ((threadIdx.x & 63) == 0 && m) atomicAdd(&hist[r], (unsigned)__popcll(m));
+                    unsigned c = 0u;
+#pragma unroll
+                    for (int j = 0; j < ITEMS; ++j) c += (unsigned)__popcll(__ballot(o[j] == r));
+                    if ((threadIdx.x & 63) == 0 && c) atomicAdd(&hist[r], c);
                 }
-            } else if (o >= 0) {
-                atomicAdd(&hist[o], 1u);
+            } else {
+#pragma unroll
+                for (int j = 0; j < ITEMS; ++j)
+                    if (o[j] >= 0) atomicAdd(&hist[o[j]], 1u);
             }
         }
     }
@@ -115,6 +169,22 @@ __global__ __launch_bounds__(kThreads) void k_find_owner(TreeView tv, const int6
         for (int i = threadIdx.x; i < P; i += kThreads)
             if (hist[i]) atomicAdd(&counts[i], (unsigned long long)hist[i]);
     }
+}
+
+// Launch of the two kernels above: kWide points per thread once that still
+// gives every CU a workgroup, and at most kWalkers workgroups, so that the
+// shared counters see few adds.
+constexpr int kWide = 4;
+constexpr int kWalkers = 1024;
+struct Walk {
+    bool wide;
+    unsigned grid;
+};
+Walk walk(int64_t n)
+{
+    const bool wide = n >= (int64_t)kThreads * kWide * 256;
+    const int64_t per = (int64_t)kThreads * (wide ? kWide : 1);
+    return {wide, (unsigned)std::min<int64_t>((n + per - 1) / per, kWalkers)};
 }
 
 }  // namespace
@@ -133,11 +203,16 @@ extern "C" int ot_relocate(const ot_tree *t, const void *pos, int32_t dtype, int
     unsigned long long *mv = (unsigned long long *)moved;
     if (mv) hipLaunchKernelGGL(k_fill<unsigned long long>, dim3(1), dim3(64), 0, s, mv, (int64_t)1, 0ull);
     if (n > 0) {
-        const dim3 g((unsigned)((n + kThreads - 1) / kThreads)), b(kThreads);
-        if (dtype == OT_F32)
-            hipLaunchKernelGGL(k_relocate<float>, g, b, 0, s, t->view, (const float *)pos, n, ids, mv);
-        else
-            hipLaunchKernelGGL(k_relocate<double>, g, b, 0, s, t->view, (const double *)pos, n, ids, mv);
+        const Walk w = walk(n);
+        if (dtype == OT_F32) {
+            const float *x = (const float *)pos;
+            if (w.wide) hipLaunchKernelGGL((k_relocate<float, kWide>), dim3(w.grid), dim3(kThreads), 0, s, t->view, x, n, ids, mv);
+            else hipLaunchKernelGGL((k_relocate<float, 1>), dim3(w.grid), dim3(kThreads), 0, s, t->view, x, n, ids, mv);
+        } else {
+            const double *x = (const double *)pos;
+            if (w.wide) hipLaunchKernelGGL((k_relocate<double, kWide>), dim3(w.grid), dim3(kThreads), 0, s, t->view, x, n, ids, mv);
+            else hipLaunchKernelGGL((k_relocate<double, 1>), dim3(w.grid), dim3(kThreads), 0, s, t->view, x, n, ids, mv);
+        }
     }
     OT_HIP(hipGetLastError());
     return OT_OK;
@@ -168,14 +243,18 @@ extern "C" int ot_find_owner(const int64_t *splitters, int32_t P, int32_t l_max,
     tv.L = l_max;
     tv.periodic = periodic ? 1 : 0;
     if (n > 0) {
-        const int64_t per_block = (int64_t)kThreads * kOwnerItems;
-        const dim3 g((unsigned)((n + per_block - 1) / per_block)), b(kThreads);
-        if (dtype == OT_F32)
-            hipLaunchKernelGGL(k_find_owner<float>, g, b, 0, s, tv, splitters, (int)P, (const float *)pos, n, owner,
-                               cnt);
-        else
-            hipLaunchKernelGGL(k_find_owner<double>, g, b, 0, s, tv, splitters, (int)P, (const double *)pos, n,
-                               owner, cnt);
+        const Walk w = walk(n);
+#define OT_OWNER(TT, ITEMS)                                                                                        \
+    hipLaunchKernelGGL((k_find_owner<TT, ITEMS>), dim3(w.grid), dim3(kThreads), 0, s, tv, splitters, (int)P,        \
+                       (const TT *)pos, n, owner, cnt)
+        if (dtype == OT_F32) {
+            if (w.wide) OT_OWNER(float, kWide);
+            else OT_OWNER(float, 1);
+        } else {
+            if (w.wide) OT_OWNER(double, kWide);
+            else OT_OWNER(double, 1);
+        }
+#undef OT_OWNER
     }
     OT_HIP(hipGetLastError());
     return OT_OK;

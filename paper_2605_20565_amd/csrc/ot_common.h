@@ -183,8 +183,8 @@ __device__ __forceinline__ uint32_t descend(const TreeView &tv, uint32_t ix, uin
     return descend_below_root(tv, e, ix, iy, iz);
 }
 
-// Integer coordinates at level L: floor(x 2^L) in FP64, wrapped (periodic)
-// or range-checked.  False when the point has no host cell.  Branch-free:
+// Integer coordinates at level L: floor(x 2^L), exact, wrapped (periodic) or
+// range-checked.  False when the point has no host cell.  Branch-free:
 // the periodic wrap is the floor-mod f - floor(f 2^-L) 2^L, exact in FP64
 // for |f| < 2^52, so no 64-bit integer conversion is needed, and the axes'
 // checks combine without short-circuits (which had compiled to a branch and
@@ -202,6 +202,30 @@ __device__ __forceinline__ bool point_cell(const TreeView &tv, T x, T y, T z, ui
         double f = floor(fin ? v[d] : 0.0);
         if (tv.periodic) f -= floor(f * inv) * sc;          // floor-mod into [0, 2^L)
         const bool in = fin & (f >= 0.0) & (f < sc);
+        ok = ok & in;
+        I[d] = in ? (uint32_t)f : 0u;
+    }
+    return ok;
+}
+
+// FP32 positions: the same cells in FP32 arithmetic.  Scaling by powers of two
+// is exact (an overflow to infinity has no host, as in FP64), so are floor and
+// the floor-mod, whose result is below 2^L <= 2^21 and a multiple of the
+// operand's last place.  Half the instructions of the FP64 form, which
+// converts first.
+template <>
+__device__ __forceinline__ bool point_cell<float>(const TreeView &tv, float x, float y, float z, uint32_t I[3])
+{
+    const float sc = (float)(1 << tv.L);
+    const float inv = 1.0f / sc;
+    const float v[3] = {x * sc, y * sc, z * sc};
+    bool ok = true;
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        const bool fin = fabsf(v[d]) < 4503599627370496.0f;   // 2^52; false for NaN
+        float f = floorf(fin ? v[d] : 0.0f);
+        if (tv.periodic) f -= floorf(f * inv) * sc;
+        const bool in = fin & (f >= 0.0f) & (f < sc);
         ok = ok & in;
         I[d] = in ? (uint32_t)f : 0u;
     }
