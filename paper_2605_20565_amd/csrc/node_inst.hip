@@ -1,0 +1,40 @@
+// One (precision, spreading mode) instantiation of the node-parallel pass; the
+// build compiles this file once per pair (OT_INST_T, OT_INST_MODE).
+#include "node_pass.h"
+
+#ifndef OT_INST_T
+#error "OT_INST_T and OT_INST_MODE select the instantiation"
+#endif
+
+namespace ot {
+
+template <typename T, int MODE>
+int dispatch_nodes(int ops, const ot_tree *t, hipStream_t s, int64_t n, const void *pos, const void *field,
+                   const void *force, int32_t *ids, void *vel, void *fout, void *grad, const FxWs &ws,
+                   const int32_t *hid)
+{
+    const dim3 g((unsigned)((n + kNodePts - 1) / kNodePts)), b(kNodeThreads);
+#define OT_NODES(OPSV, PERV)                                                                                       \
+    hipLaunchKernelGGL((k_nodes<T, OPSV, MODE, PERV>), g, b, 0, s, t->view, n, (const T *)pos, (const T *)field,    \
+                       (const T *)force, ids, (T *)vel, (T *)fout, ws.acc, ws.fx, (T *)grad, hid)
+#define OT_CASE(OPSV)                                                                                              \
+    case OPSV:                                                                                                     \
+        if (t->view.periodic) OT_NODES(OPSV, true);                                                                \
+        else OT_NODES(OPSV, false);                                                                                \
+        break;
+    switch (ops) {
+        OT_CASE(2) OT_CASE(3) OT_CASE(4) OT_CASE(5) OT_CASE(6) OT_CASE(7)
+        OT_CASE(kOpGrad) OT_CASE(kOpGrad | kOpInterp) OT_CASE(kOpGrad | kOpSpread)
+    default: return fail(OT_ERR_INVALID, "ops must be a non-empty combination of OT_OP_* bits");
+    }
+#undef OT_CASE
+#undef OT_NODES
+    return OT_OK;
+}
+
+template int dispatch_nodes<OT_INST_T, OT_INST_MODE>(int ops, const ot_tree *t, hipStream_t s, int64_t n,
+                                                    const void *pos, const void *field, const void *force,
+                                                    int32_t *ids, void *vel, void *fout, void *grad, const FxWs &ws,
+                                                    const int32_t *hid);
+
+}  // namespace ot

@@ -21,7 +21,25 @@ int dispatch_ops(int ops, const ot_tree *t, dim3 g, dim3 b, int64_t tile, hipStr
                  const void *field, const void *force, int32_t *ids, void *vel, void *fout, void *grad,
                  const FxWs &ws, const int32_t *hid);
 
+// Launch of the node-parallel pass; instantiated in node_inst.hip (node_pass.h).
+template <typename T, int MODE>
+int dispatch_nodes(int ops, const ot_tree *t, hipStream_t s, int64_t n, const void *pos, const void *field,
+                   const void *force, int32_t *ids, void *vel, void *fout, void *grad, const FxWs &ws,
+                   const int32_t *hid);
+
 constexpr int kMaxPointsPerThread = 4;
+
+// Point sets up to these sizes take the node-parallel pass (node_pass.h).
+// Measured, FP32, random points on 38 k leaves, kernel alone, per-point pass
+// against this one.  Interpolation: 1 k points 6.6 -> 4.5 us, 10 k 7.1 -> 4.9,
+// 25 k 8.4 -> 5.0, 49 k 9.8 -> 7.4 (with the gradient 10.1 -> 11.1, and slower on
+// larger trees from 25 k).  Spreading: 1 k 37 -> 9.2 us, 10 k 49 -> 18, 49 k 174
+// -> 61; from 65,536 points the per-point pass takes tiles of 128 points with
+// the large table, and markers in order on few leaves are faster there (100 k:
+// 66 against 134 us a call).  A whole fused FP32 fixed-point call on 11 k points:
+// 53.5 -> 25.9 us (three launches instead of five).
+constexpr int64_t kNodesMaxSpread = 65535;
+constexpr int64_t kNodesMaxGather = 16384;
 
 // Prepare the spreading target before a pass: zero the output (atomic mode,
 // overwrite) or the fixed-point accumulators and compute the scale.
@@ -36,6 +54,60 @@ __global__ void k_zero2(unsigned long long *__restrict__ a, int64_t n, unsigned 
         a[i] = 0ull;
     if (b && blockIdx.x == 0)
         for (int64_t i = threadIdx.x; i < m; i += blockDim.x) b[i] = 0u;
+}
+
+// Small calls: zero n 64-bit words at a, and the max |F| of this workgroup's
+// share of the m force components into parts (workgroups 0 .. kFxParts - 1).
+template <typename T>
+__global__ __launch_bounds__(256) void k_zero_max(unsigned long long *__restrict__ a, int64_t n,
+                                                  const T *__restrict__ f, int64_t m,
+                                                  unsigned long long *__restrict__ parts)
+{
+    if ((int)blockIdx.x >= kFxParts) {
+        const int64_t step = (int64_t)(gridDim.x - kFxParts) * blockDim.x;
+        for (int64_t i = (blockIdx.x - kFxParts) * (int64_t)blockDim.x + threadIdx.x; i < n; i += step) a[i] = 0ull;
+        return;
+    }
+    __shared__ unsigned long long wmax[4];
+    unsigned long long best = 0ull;
+    constexpr int kU = 8;   // loads in flight per thread, at clamped indices
+    const int64_t step = (int64_t)kFxParts * 256;
+    for (int64_t i0 = blockIdx.x * (int64_t)256 + threadIdx.x; i0 < m; i0 += kU * step) {
+        T v[kU];
+#pragma unroll
+        for (int u = 0; u < kU; ++u) v[u] = f[i0 + u * step < m ? i0 + u * step : i0];
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            const unsigned long long b = isfinite(v[u]) ? abs_bits(v[u]) : 0ull;
+            best = std::max(best & 0x7FFFFFFFFFFFFFFFull, b) | (best & 0x8000000000000000ull) |
+                   (isfinite(v[u]) ? 0ull : 0x8000000000000000ull);
+        }
+    }
+    auto join = [](unsigned long long x, unsigned long long y) {
+        return std::max(x & 0x7FFFFFFFFFFFFFFFull, y & 0x7FFFFFFFFFFFFFFFull) | ((x | y) & 0x8000000000000000ull);
+    };
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) best = join(best, (unsigned long long)__shfl_xor(best, o, 64));
+    if ((threadIdx.x & 63) == 0) wmax[threadIdx.x >> 6] = best;
+    __syncthreads();
+    if (threadIdx.x == 0) parts[blockIdx.x] = join(join(wmax[0], wmax[1]), join(wmax[2], wmax[3]));
+}
+
+template <typename T>
+void nodes_begin(const ot_tree *t, const FxWs &ws, const void *force, int64_t n, hipStream_t s)
+{
+    const int64_t n3 = t->n_leaves * 3;
+    const unsigned gz = (unsigned)std::min<int64_t>((n3 + 255) / 256, 1024);
+    hipLaunchKernelGGL(k_zero_max<T>, dim3(kFxParts + gz), dim3(256), 0, s, ws.acc, n3, (const T *)force, 3 * n,
+                       ws.fx->parts);
+}
+
+template <typename T>
+void nodes_end(const ot_tree *t, const FxWs &ws, int accumulate, void *fout, int64_t n, hipStream_t s)
+{
+    const int64_t n3 = t->n_leaves * 3;
+    const unsigned gb = (unsigned)std::min<int64_t>((n3 + 255) / 256, 8192);
+    hipLaunchKernelGGL((k_fx_finalize<T, true>), dim3(gb), dim3(256), 0, s, ws.acc, (T *)fout, n3, ws.fx, accumulate, n);
 }
 
 }  // namespace
@@ -91,9 +163,11 @@ int spread_epilogue(const ot_tree *t, const FxWs &ws, int dtype, int mode, int a
     const int64_t n3 = t->n_leaves * 3;
     const unsigned gb = (unsigned)std::min<int64_t>((n3 + 255) / 256, 8192);
     if (dtype == OT_F32)
-        hipLaunchKernelGGL(k_fx_finalize<float>, dim3(gb), dim3(256), 0, s, ws.acc, (float *)fout, n3, ws.fx, accumulate);
+        hipLaunchKernelGGL((k_fx_finalize<float, false>), dim3(gb), dim3(256), 0, s, ws.acc, (float *)fout, n3, ws.fx,
+                           accumulate, (int64_t)0);
     else
-        hipLaunchKernelGGL(k_fx_finalize<double>, dim3(gb), dim3(256), 0, s, ws.acc, (double *)fout, n3, ws.fx, accumulate);
+        hipLaunchKernelGGL((k_fx_finalize<double, false>), dim3(gb), dim3(256), 0, s, ws.acc, (double *)fout, n3, ws.fx,
+                           accumulate, (int64_t)0);
     OT_HIP(hipGetLastError());
     return OT_OK;
 }
@@ -117,6 +191,24 @@ int check_common(const ot_tree *t, int dtype, int64_t n, const void *pos)
 }
 
 namespace {
+
+// A small call's pass: three launches with fixed-point spreading.
+template <typename T>
+int nodes_pass(const ot_tree *t, int ops, const void *field, const void *force, const void *pos, int dtype, int64_t n,
+               int mode, int accumulate, int32_t *ids, void *vel, void *fout, void *grad, const FxWs &ws,
+               const int32_t *hid, hipStream_t s)
+{
+    const bool spread = (ops & kOpSpread) != 0, fixed = spread && mode == OT_SPREAD_FIXED;
+    int rc = OT_OK;
+    if (fixed) nodes_begin<T>(t, ws, force, n, s);
+    else if (spread) rc = spread_begin(t, ws, dtype, mode, accumulate, fout, s);
+    if (!rc)
+        rc = fixed ? dispatch_nodes<T, kModeFixed>(ops, t, s, n, pos, field, force, ids, vel, fout, grad, ws, hid)
+                   : dispatch_nodes<T, kModeAtomic>(ops, t, s, n, pos, field, force, ids, vel, fout, grad, ws, hid);
+    if (!rc && fixed) nodes_end<T>(t, ws, accumulate, fout, n, s);
+    OT_HIP(hipGetLastError());
+    return rc;
+}
 
 // The pass's kernel alone, no clearing, scale or conversion around it.
 int launch_ops(const ot_tree *t, int ops, const void *field, const void *force, const void *pos, int dtype, int64_t n,
@@ -186,6 +278,14 @@ int run_pass(const ot_tree *t, int ops, const void *field, const void *force, co
         work = owned;
     }
     const FxWs ws = fx_ws(work);
+    if (n > 0 && (ops & ~kOpLocate) && n <= (spread ? kNodesMaxSpread : kNodesMaxGather)) {
+        rc = dtype == OT_F32 ? nodes_pass<float>(t, ops, field, force, pos, dtype, n, mode, accumulate, ids, vel, fout,
+                                                 grad, ws, hid, s)
+                             : nodes_pass<double>(t, ops, field, force, pos, dtype, n, mode, accumulate, ids, vel, fout,
+                                                  grad, ws, hid, s);
+        if (owned) (void)hipFreeAsync(owned, s);
+        return rc;
+    }
     if (spread) rc = spread_prologue(t, ws, dtype, mode, accumulate, force, n, fout, s);
     if (!rc) rc = launch_ops(t, ops, field, force, pos, dtype, n, mode, ids, vel, fout, grad, ws, hid, s);
     if (!rc && spread) rc = spread_epilogue(t, ws, dtype, mode, accumulate, fout, s);

@@ -23,7 +23,13 @@ struct FxState {
     unsigned long long nonfinite; // != 0: some force component is NaN or infinite
     double scale;                 // 2^s
     double inv;                   // 2^-s
+    // Small calls: max |F| bits of each workgroup of the clearing kernel (bit
+    // 63: it saw a non-finite component), which the later kernels reduce
+    // themselves (fx_scale); nothing to clear first and no atomics.
+    unsigned long long parts[28];
 };
+constexpr int kFxParts = 28;
+static_assert(sizeof(FxState) == kFxHeader, "the header of a spreading workspace");
 
 // A spreading workspace: header and n_leaves x 3 int64 accumulators.
 struct FxWs {
@@ -551,6 +557,23 @@ __device__ __forceinline__ int fx_shift(unsigned long long maxbits, int64_t n)
     return s;
 }
 
+// Scale, its inverse and the non-finite flag from a small call's parts.
+template <typename T>
+__device__ __forceinline__ void fx_scale(const FxState *fx, int64_t n, double &scale, double &inv, bool &poison)
+{
+    unsigned long long m = 0ull, any = 0ull;
+#pragma unroll
+    for (int i = 0; i < kFxParts; ++i) {
+        const unsigned long long v = fx->parts[i];
+        any |= v;
+        m = std::max(m, v & 0x7FFFFFFFFFFFFFFFull);
+    }
+    const int s = fx_shift<T>(m, n);
+    scale = ldexp(1.0, s);
+    inv = ldexp(1.0, -s);
+    poison = (any >> 63) != 0ull;
+}
+
 template <typename T>
 __global__ void k_fx_prepare(FxState *fx, int64_t n)
 {
@@ -562,12 +585,17 @@ __global__ void k_fx_prepare(FxState *fx, int64_t n)
 
 // Accumulators to field_out.  A non-finite force cannot be carried by the
 // integer sums, so when one was seen every output value becomes NaN.
-template <typename T>
+// PARTS: a small call of n points, whose scale comes from the parts.
+template <typename T, bool PARTS>
 __global__ void k_fx_finalize(const unsigned long long *__restrict__ acc, T *__restrict__ out, int64_t n3,
-                              const FxState *__restrict__ fx, int accumulate)
+                              const FxState *__restrict__ fx, int accumulate, int64_t n)
 {
-    const double inv = fx->inv;
-    const bool poison = fx->nonfinite != 0ull;
+    double inv = fx->inv;
+    bool poison = fx->nonfinite != 0ull;
+    if (PARTS) {
+        double scale;
+        fx_scale<T>(fx, n, scale, inv, poison);
+    }
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n3; i += (int64_t)gridDim.x * blockDim.x) {
         const T v = poison ? T(NAN) : (T)((double)(long long)acc[i] * inv);
         out[i] = accumulate ? out[i] + v : v;
