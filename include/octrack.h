@@ -43,7 +43,11 @@
  *   - A tree handle is read-only after ot_build_tree: every call that needs
  *     working memory takes it from the caller (a `work` argument), from its
  *     batch plan, or allocates it on the call's stream, so calls on one tree
- *     may run on several streams at once.
+ *     may run on several streams at once.  Larger calls on points without
+ *     given host ids sort the points first; that memory the tree keeps for
+ *     the next such call (at most four buffers and 1 GiB, for one call each
+ *     at a time, freed with the tree).  Where there is none to be had, and in
+ *     calls that are captured in a graph, the points are taken as they are.
  *   - Host ids (`ids` arguments marked "input"): the host leaf of every point
  *     as ot_locate returns it (Algorithm 1's host_cell_id, which Sec. 3.2
  *     makes the prerequisite of interpolation and spreading).  When given,
@@ -148,7 +152,9 @@ typedef struct {
  * Otherwise the points are sorted by host leaf, down to groups of at most 64
  * consecutive ids (two passes up to 4 M leaves, three above), so that
  * neighbouring threads share stencil nodes in cache and in the workgroup's
- * spreading table.  Results are the same bit for bit (FIXED).  Needs the
+ * spreading table.  Runs of few points (under 55,000 that spread, under
+ * 100,000 that do not) are not sorted at all unless OT_TUNE_HOST_MAJOR asks
+ * for it.  Results are the same bit for bit (FIXED).  Needs the
  * same ops for every instance. */
 #define OT_TUNE_SORT_POINTS 1
 
@@ -231,13 +237,13 @@ int ot_spread(const ot_tree *tree, const void *force, const void *pos, const int
  * (code under HIP graph capture, tight serving loops, harnesses that forbid
  * hipMalloc): ot_spread with its workspace taken from a static device array
  * of 256 + 24 * OT_NOALLOC_MAX_LEAVES bytes (about 24 MiB) that the library
- * holds on every device it runs on until the process ends.  The call
- * allocates nothing; the caller still passes inputs and outputs.  Every call
+ * holds on every device it runs on until the process ends.  The call does not
+ * sort the points and allocates nothing; the caller still passes inputs and outputs.  Every call
  * on one device shares that device's array: calls that overlap on one
  * device (several streams or threads) race and give wrong results.  The
  * array keeps the last call's contents; each call clears what it needs.
- * FIXED mode only uses the array (ATOMIC mode runs ot_spread, which
- * allocates nothing in that mode).  Errors: as ot_spread, and
+ * FIXED mode only uses the array (ATOMIC mode needs none).  Errors: as
+ * ot_spread, and
  * OT_ERR_CAPACITY for a tree with more than OT_NOALLOC_MAX_LEAVES leaves in
  * FIXED mode, OT_ERR_INVALID when the current device is not the tree's. */
 #define OT_NOALLOC_MAX_LEAVES 1048576

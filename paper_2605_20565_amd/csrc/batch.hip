@@ -28,16 +28,27 @@ template <typename T, int MODE>
 const void *kbatch_fn(bool grad, bool small);
 template <typename T, int MODE>
 const void *hm_fn(int ops);
-template <typename T, int MODE>
-const void *block_fn(int ops, bool root);
-int block_threads(bool root);
 constexpr int kHmWindow = 256;   // points per window of the host-major pass (kHmThreads)
+
+namespace {
+
+}  // namespace
+
+int plain_pass(const ot_tree *t, int ops, const void *field, const void *force, const void *pos, int dtype, int64_t n,
+               int mode, int32_t *ids, void *vel, void *fout, void *grad, void *work, hipStream_t s);   // track.hip
 
 namespace {
 
 int enqueue_any(ot_batch_plan *p, const void *field, const void *force, const void *pos, int32_t *ids, void *vel,
                 void *fout, void *grad, hipStream_t s)
 {
+    if (p->use_small) {
+        if (p->timing) OT_HIP(hipEventRecord(p->ev[0], s));
+        const int rc = plain_pass(p->tree, p->ops_all, field, force, pos, p->dtype, p->n_points, p->mode, ids, vel, fout,
+                                  grad, p->fxws, s);
+        if (!rc && p->timing) OT_HIP(hipEventRecord(p->ev[1], s));
+        return rc;
+    }
     if (p->dtype == OT_F32)
         return p->mode == OT_SPREAD_FIXED ? enqueue<float, kModeFixed>(p, field, force, pos, ids, vel, fout, grad, s)
                                           : enqueue<float, kModeAtomic>(p, field, force, pos, ids, vel, fout, grad, s);
@@ -50,6 +61,30 @@ bool valid_ops(int o)
     return (o >= 0 && o <= 7) || o == kOpGrad || o == (kOpGrad | kOpInterp) || o == (kOpGrad | kOpSpread);
 }
 
+// Launch shape of the per-point pass: 256 threads and up to 4 points per
+// thread, narrower and shorter tiles when there are too few points for two
+// workgroups per CU (measured: 256 x 512-1024 beats 512 x 2048 by 15-20% on
+// large sets, where two 56 KiB tables per CU leave 512-thread groups few waves).
+void default_shape(const ot_tree *tree, int64_t n_all, bool sorted, int given_block, int &block, int &tile)
+{
+    const int64_t want = 2 * (int64_t)tree->cus;
+    block = 256;
+    while (block > 64 && (n_all + block - 1) / block < want) block >>= 1;
+    if (given_block) block = given_block;
+    tile = (int)(block * std::max<int64_t>(1, std::min<int64_t>(4, n_all / ((int64_t)block * want))));
+    if (sorted && tree->n_leaves > 0) {
+        // sorted tiles: about 160 points per point-per-leaf of the run, the
+        // power of two nearest to it within [block, 4 block], so that a
+        // tile's stencil nodes fit the 2048-slot spreading table (autotuned
+        // on the workloads: 256 at ~1 point per leaf, 512 at ~4, 1024 at ~5
+        // with 26 per finest leaf)
+        const double target = 160.0 * (double)n_all / (double)tree->n_leaves;
+        int t = block;
+        while (t < 4 * block && (double)(2 * t) <= target * 1.41421356) t *= 2;
+        tile = std::min(tile, t);
+    }
+}
+
 void drop_graph(ot_batch_plan *p)
 {
     if (p->have_graph) {
@@ -60,6 +95,62 @@ void drop_graph(ot_batch_plan *p)
 }
 
 }  // namespace
+
+// A plain call as one run of a sorted plan in the tree's working memory.  handled = false (and nothing enqueued): the
+// caller takes the unsorted pass.
+int sorted_pass(const ot_tree *t, int ops, const void *field, const void *force, const void *pos, int dtype, int64_t n,
+                int mode, int accumulate, int32_t *ids, void *vel, void *fout, void *grad, void *work, hipStream_t s,
+                bool &handled)
+{
+    handled = false;
+    // a capture keeps the call free of allocations
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
+        (void)hipGetLastError();
+        return OT_OK;
+    }
+    ot_batch_plan p{};
+    p.tree = t;
+    p.dtype = dtype;
+    p.mode = mode;
+    p.accumulate = accumulate;
+    p.ops_union = p.ops_all = ops;
+    p.grad_plan = (ops & kOpGrad) != 0;
+    p.n_points = n;
+    p.sort_points = true;
+    p.fxws = work;
+    p.use_blocks = blk_rule(t, n, ops);
+    p.use_nodes = !p.use_blocks && node_rule(t, n, ops);
+    p.sort_key = p.use_blocks ? point_sort_by_block(t->view.nblk) : point_sort_by_host(t->n_leaves);
+    default_shape(t, n, true, 0, p.block, p.tile);
+    p.small_table = p.tile <= kSmallTile;
+    p.n_tiles = (n + p.tile - 1) / p.tile;
+    p.grid = t->cus * (p.small_table ? 8 : 2);
+    const int64_t rec = ((ops & (kOpSpread | kOpGrad)) ? 6 : 3) * n * (dtype == OT_F32 ? 4 : 8);
+    auto up = [](int64_t b) { return (b + 255) & ~int64_t(255); };
+    const int64_t total = 2 * up(8 * n) + 2 * up(rec) + up(point_sort_ws_bytes(n)) +
+                          (p.use_blocks ? up(blk_bytes(t, n)) : 0) + 256;
+    const Scratch m = scratch_take(t, (size_t)total, s);
+    if (!m.p) return OT_OK;
+    char *q = (char *)m.p;
+    auto take = [&](int64_t b) {
+        char *r = q;
+        q += up(b);
+        return (void *)r;
+    };
+    for (int i = 0; i < 2; ++i) {
+        p.skv[i] = (uint64_t *)take(8 * n);
+        p.srec[i] = take(rec);
+    }
+    p.sws = take(point_sort_ws_bytes(n));
+    p.counter = (unsigned *)take(64);
+    if (p.use_blocks) blk_layout(t, n, take(blk_bytes(t, n)), p.counter, &p.blk);
+    handled = true;
+    const int rc = enqueue_any(&p, field, force, pos, ids, vel, fout, grad, s);
+    scratch_give(t, m, s);
+    return rc;
+}
+
 }  // namespace ot
 
 using namespace ot;
@@ -79,27 +170,9 @@ extern "C" int ot_batch_plan_create(const ot_tree *tree, const int64_t *offsets,
     }
     if (kinds == 3) return fail(OT_ERR_INVALID, "gradient and forward-only ops cannot share a plan");
     const bool sort_points = tuning && (tuning->flags & OT_TUNE_SORT_POINTS);
-    // defaults: 256 threads and up to 4 points per thread, narrower and
-    // shorter tiles when there are too few points for two workgroups per CU
-    // (measured: 256 x 512-1024 beats 512 x 2048 by 15-20% on large sets,
-    // where two 56 KiB tables per CU leave 512-thread groups few waves)
-    const int64_t want = 2 * (int64_t)tree->cus;
     const int64_t n_all = offsets[n_inst] > 0 ? offsets[n_inst] : 0;
-    int block = 256;
-    while (block > 64 && (n_all + block - 1) / block < want) block >>= 1;
-    if (tuning && tuning->block) block = tuning->block;
-    int tile = (int)(block * std::max<int64_t>(1, std::min<int64_t>(4, n_all / ((int64_t)block * want))));
-    if (sort_points && tree->n_leaves > 0) {
-        // sorted tiles: about 160 points per point-per-leaf of the run, the
-        // power of two nearest to it within [block, 4 block], so that a
-        // tile's stencil nodes fit the 2048-slot spreading table (autotuned
-        // on the workloads: 256 at ~1 point per leaf, 512 at ~4, 1024 at ~5
-        // with 26 per finest leaf)
-        const double target = 160.0 * (double)n_all / (double)tree->n_leaves;
-        int t = block;
-        while (t < 4 * block && (double)(2 * t) <= target * 1.41421356) t *= 2;
-        tile = std::min(tile, t);
-    }
+    int block, tile;
+    default_shape(tree, n_all, sort_points, tuning ? tuning->block : 0, block, tile);
     if (tuning && tuning->tile) tile = tuning->tile;
     if (block < 64 || block > 512 || block % 64) return fail(OT_ERR_INVALID, "block must be a multiple of 64 in [64, 512]");
     if (tile < block || tile % block || tile > (int)kCountMask) return fail(OT_ERR_INVALID, "tile must be a multiple of block");
@@ -128,16 +201,6 @@ extern "C" int ot_batch_plan_create(const ot_tree *tree, const int64_t *offsets,
         }
     }
     if (ops_all < 0) ops_all = 0;
-    if (sort_points) {
-        // one run of tiles over the sorted points; ids were written by the sort-key pass
-        const int sops = ops_all & ~kOpLocate;
-        const int64_t n = offsets[n_inst];
-        if (sops)
-            for (int64_t a = 0; a < n; a += tile) {
-                starts.push_back(a);
-                infos.push_back((uint32_t)std::min<int64_t>(tile, n - a) | ((uint32_t)sops << 24));
-            }
-    }
     ot_batch_plan *p = new ot_batch_plan();
     p->tree = tree;
     p->dtype = dtype;
@@ -146,15 +209,18 @@ extern "C" int ot_batch_plan_create(const ot_tree *tree, const int64_t *offsets,
     p->tile = tile;
     p->ops_union = ops_union;
     p->n_points = offsets[n_inst];
-    p->n_tiles = (int64_t)starts.size();
+    // sorted: every `tile` sorted points; ids were written by the sort-key pass
+    p->n_tiles = sort_points ? ((ops_all & ~kOpLocate) ? (offsets[n_inst] + tile - 1) / tile : 0) : (int64_t)starts.size();
     p->have_graph = false;
     p->use_graph = tuning && (tuning->flags & OT_TUNE_GRAPH);
     p->sort_points = sort_points;
     p->ops_all = ops_all;
     p->grad_plan = (ops_union & kOpGrad) != 0;
-    if (sort_points && p->n_points > 0) {
+    p->use_small = sort_points && !(tuning->flags & OT_TUNE_HOST_MAJOR) && small_rule(p->n_points, ops_all);
+    if (sort_points && p->n_points > 0 && !p->use_small) {
         const int64_t n = p->n_points;
-        p->use_blocks = !(tuning->flags & OT_TUNE_HOST_MAJOR) && (ops_all & ~kOpLocate) && blk_rule(tree, n);
+        p->use_blocks = !(tuning->flags & OT_TUNE_HOST_MAJOR) && blk_rule(tree, n, ops_all);
+        p->use_nodes = !p->use_blocks && !(tuning->flags & OT_TUNE_HOST_MAJOR) && node_rule(tree, n, ops_all);
         p->sort_key = p->use_blocks ? point_sort_by_block(tree->view.nblk) : point_sort_by_host(tree->n_leaves);
         const size_t rec = ((ops_all & (kOpSpread | kOpGrad)) ? 6 : 3) * (size_t)n * (dtype == OT_F32 ? 4 : 8);
         hipError_t e = hipSuccess;
@@ -228,16 +294,6 @@ extern "C" int ot_batch_plan_create(const ot_tree *tree, const int64_t *offsets,
     }
     if (p->use_blocks) {
         blk_layout(tree, p->n_points, p->blk_mem, p->counter, &p->blk);
-        const int bops = ops_all & ~kOpLocate;
-        for (int root = 0; root < 2; ++root) {
-            const void *bfn = dtype == OT_F32 ? (mode == OT_SPREAD_FIXED ? block_fn<float, kModeFixed>(bops, root)
-                                                                         : block_fn<float, kModeAtomic>(bops, root))
-                                              : (mode == OT_SPREAD_FIXED ? block_fn<double, kModeFixed>(bops, root)
-                                                                         : block_fn<double, kModeAtomic>(bops, root));
-            int per = 0;
-            (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, bfn, block_threads(root), 0);
-            (root ? p->blk.root_grid : p->blk.sub_grid) = std::max(1, cus) * std::max(1, per);
-        }
     }
     if (!starts.empty()) {
         hipError_t e = hipMemcpy(p->tile_start, starts.data(), starts.size() * 8, hipMemcpyHostToDevice);

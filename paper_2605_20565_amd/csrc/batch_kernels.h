@@ -12,6 +12,7 @@
 #include "batch_plan.h"
 #include "block_pass.h"
 #include "hm_pass.h"
+#include "node_pass.h"
 #include "ot_common.h"
 #include "point_sort.h"
 #include "track_device.h"
@@ -20,15 +21,14 @@
 namespace ot {
 
 
-// Tiles handed over by the host-major pass (window indices) or the block pass
-// (ranges) and their count (device), the window size, the number of points and
-// the common ops.
+// Tiles of a sorted run: every `pts` sorted points, or those handed over by
+// the host-major pass (window indices in list, their count in device memory);
+// the number of points and the common ops.  pts = 0: the plan's tile table.
 struct FbTiles {
     const uint32_t *list;
     const unsigned *count;
     int64_t pts, n;
     uint32_t ops;
-    const uint2 *ranges;   // instead of list: (first point, count) of each tile
 };
 
 // GRAD: the plan's ops are gradient passes (8, 10, 12), else forward (1..7).
@@ -41,7 +41,7 @@ __global__ __launch_bounds__(512) void k_batch(TreeView tv, const int64_t *__res
                                                int rs, const T *__restrict__ pos,
                                                const T *__restrict__ field, const T *__restrict__ force,
                                                int32_t *__restrict__ ids, T *__restrict__ vel, T *__restrict__ fout,
-                                               unsigned long long *__restrict__ facc, const FxState *__restrict__ fx,
+                                               unsigned long long *__restrict__ facc, FxRef fx,
                                                T *__restrict__ grad, FbTiles fb)
 {
     if (fb.count) n_tiles = *fb.count;
@@ -50,7 +50,7 @@ __global__ __launch_bounds__(512) void k_batch(TreeView tv, const int64_t *__res
     __shared__ Acc vals[LdsSink<T, MODE, S>::kVals];
     __shared__ unsigned s_tile;
     // the fixed-point state exists only for plans that spread (fx null otherwise)
-    const double scale = (MODE == kModeFixed && fx) ? fx->scale : 0.0;
+    const double scale = (MODE == kModeFixed && fx.st) ? fx_scale<T>(fx) : 0.0;
     LdsSink<T, MODE, S> sink{keys, vals, fout, facc, scale};
     sink.clear();
     // The next tile is claimed before the flush, so the queue atomic's round
@@ -65,12 +65,8 @@ __global__ __launch_bounds__(512) void k_batch(TreeView tv, const int64_t *__res
         if (tile >= n_tiles) break;   // same value in every thread of the workgroup
         int64_t start, end;
         uint32_t info;
-        if (fb.ranges) {   // sorted by block: the words hold no hosts
-            start = fb.ranges[tile].x;
-            end = start + fb.ranges[tile].y;
-            info = fb.ops << 24;
-        } else if (fb.list) {
-            start = (int64_t)fb.list[tile] * fb.pts;
+        if (fb.pts) {
+            start = (fb.list ? (int64_t)fb.list[tile] : tile) * fb.pts;
             end = start + fb.pts < fb.n ? start + fb.pts : fb.n;
             info = fb.ops << 24;
         } else {
@@ -81,7 +77,7 @@ __global__ __launch_bounds__(512) void k_batch(TreeView tv, const int64_t *__res
         if constexpr (!GRAD) {
             switch (info >> 24) {
 #define OT_CASE(OPSV) \
-    case OPSV: track_range<T, OPSV, PER>(tv, start, end, kv, rs, pos, field, force, ids, vel, sink, nullptr, nullptr, fb.ranges == nullptr); break;
+    case OPSV: track_range<T, OPSV, PER>(tv, start, end, kv, rs, pos, field, force, ids, vel, sink); break;
                 OT_CASE(1) OT_CASE(2) OT_CASE(3) OT_CASE(4) OT_CASE(5) OT_CASE(6) OT_CASE(7)
 #undef OT_CASE
             default: break;
@@ -89,7 +85,7 @@ __global__ __launch_bounds__(512) void k_batch(TreeView tv, const int64_t *__res
         } else {
             switch (info >> 24) {
 #define OT_CASE(OPSV) \
-    case OPSV: track_range<T, OPSV, PER>(tv, start, end, kv, rs, pos, field, force, ids, vel, sink, grad, nullptr, fb.ranges == nullptr); break;
+    case OPSV: track_range<T, OPSV, PER>(tv, start, end, kv, rs, pos, field, force, ids, vel, sink, grad); break;
                 OT_CASE(kOpGrad) OT_CASE(kOpGrad | kOpInterp) OT_CASE(kOpGrad | kOpSpread)
 #undef OT_CASE
             default: break;
@@ -105,6 +101,11 @@ template <typename T, int MODE>
 int enqueue_blocks(const ot_tree *t, BlkWork &w, int ops, const uint64_t *kv, const T *rec, const T *field, T *vel,
                    T *fout, const FxWs &ws, T *grad, hipStream_t s);
 
+// Instantiated in node_inst.hip: the node-parallel pass over sorted ranges.
+template <typename T, int MODE>
+int enqueue_ranges(const ot_tree *t, int ops, const NodeRanges &nr, unsigned *queue, const uint64_t *kv, const T *rec,
+                   const T *field, T *vel, T *fout, const FxWs &ws, T *grad, hipStream_t s);
+
 constexpr int kCounters = 8;
 
 template <typename T, int MODE>
@@ -118,42 +119,52 @@ int enqueue(ot_batch_plan *p, const void *field, const void *force, const void *
     int rc;
     const bool spread = (p->ops_union & kOpSpread) != 0;
     const FxWs ws = fx_ws(p->fxws);
-    if (spread) {
-        if ((rc = spread_begin(t, ws, p->dtype, p->mode, 0, fout, s, p->counter, kCounters))) return rc;
-    } else {
-        hipLaunchKernelGGL(k_fill<unsigned>, dim3(1), dim3(64), 0, s, p->counter, (int64_t)kCounters, 0u);
-    }
+    const FxRef fx{ws.fx, n};
     const uint64_t *kv = nullptr;
     int rs = 3;
     int32_t *kids = ids;
     const T *kpos = (const T *)pos, *kforce = (const T *)force;
-    const void *scale_from = force;   // max |F| still to take (FIXED)
     if (p->sort_points && n > 0) {
-        // ids come from the key pass; positions and forces travel with the
-        // keys, and the first pass takes max |F| on the way
+        // ids come from the key pass, which also clears what the run adds to;
+        // positions and forces travel with the keys, and the first sort pass
+        // takes max |F| on the way
         const bool carry_force = (p->ops_all & (kOpSpread | kOpGrad)) != 0;
+        SortZero zero{nullptr, 0, p->counter, kCounters};
+        if (spread && p->mode == OT_SPREAD_FIXED) {
+            zero.p = (uint32_t *)ws.fx;
+            zero.words = (kFxHeader + t->n_leaves * 3 * 8) / 4;
+        } else if (spread && !p->accumulate) {
+            zero.p = (uint32_t *)fout;
+            zero.words = t->n_leaves * 3 * (int64_t)sizeof(T) / 4;
+        }
         PointSortBufs<T> b{{p->skv[0], p->skv[1]}, {(T *)p->srec[0], (T *)p->srec[1]}, p->sws};
         PointSortResult<T> r;
         unsigned long long *maxbits = ((p->ops_all & kOpSpread) && p->mode == OT_SPREAD_FIXED)
                                           ? &ws.fx->maxbits
                                           : nullptr;
-        point_sort<T>(t->view, n, p->sort_key, (const T *)pos,
-                      carry_force ? (const T *)force : nullptr, (p->ops_all & kOpLocate) ? ids : nullptr, b, maxbits,
-                      s, r);
+        point_sort<T>(t->view, n, p->sort_key, (const T *)pos, carry_force ? (const T *)force : nullptr,
+                      (p->ops_all & kOpLocate) ? ids : nullptr, b, zero, maxbits, s, r);
         kv = r.kv;
         rs = r.stride;
         kpos = r.rec;
         kforce = carry_force ? r.rec + 3 : nullptr;
         kids = nullptr;
-        if (maxbits) scale_from = nullptr;
+        if (!(p->ops_all & ~kOpLocate)) {
+            OT_HIP(hipGetLastError());
+            return OT_OK;
+        }
+    } else if (spread) {
+        if ((rc = spread_begin(t, ws, p->dtype, p->mode, p->accumulate, fout, s, p->counter, kCounters))) return rc;
+        if ((rc = spread_max(ws, p->dtype, p->mode, force, n, s))) return rc;
+    } else {
+        hipLaunchKernelGGL(k_fill<unsigned>, dim3(1), dim3(64), 0, s, p->counter, (int64_t)kCounters, 0u);
     }
-    if (spread && (rc = spread_scale(t, ws, p->dtype, p->mode, scale_from, n, s))) return rc;
     if (p->timing) OT_HIP(hipEventRecord(p->ev[0], s));
     if (p->use_hm && n > 0) {
         const int sops = p->ops_all & (kOpInterp | kOpSpread);
 #define OT_KHM(PERV, OPSV)                                                                                         \
     hipLaunchKernelGGL((k_hm<T, MODE, PERV, OPSV>), dim3(p->hm_grid), dim3(kHmThreads), 0, s, t->view, n, p->n_win,  \
-                       p->counter, kv, rs, kpos, (const T *)field, (T *)vel, (T *)fout, ws.acc, ws.fx, p->fb_list,  \
+                       p->counter, kv, rs, kpos, (const T *)field, (T *)vel, (T *)fout, ws.acc, fx, p->fb_list,  \
                        p->counter + 2)
         if (t->view.periodic) {
             if (sops == kOpInterp) OT_KHM(true, kOpInterp);
@@ -167,41 +178,45 @@ int enqueue(ot_batch_plan *p, const void *field, const void *force, const void *
 #undef OT_KHM
         OT_HIP(hipGetLastError());
         // windows the host-major pass handed over, per point
-        const FbTiles fb{p->fb_list, p->counter + 2, (int64_t)kHmThreads, n, (uint32_t)sops, nullptr};
+        const FbTiles fb{p->fb_list, p->counter + 2, (int64_t)kHmThreads, n, (uint32_t)sops};
         constexpr int kS = SinkSlots<T, MODE>::value;
         if (t->view.periodic)
             hipLaunchKernelGGL((k_batch<T, MODE, true, false, kS>), dim3(p->grid), dim3(kHmThreads), 0, s, t->view,
                                p->tile_start, p->tile_info, (int64_t)0, p->counter + 1, kv, rs, kpos, (const T *)field,
-                               kforce, (int32_t *)nullptr, (T *)vel, (T *)fout, ws.acc, ws.fx, (T *)nullptr, fb);
+                               kforce, (int32_t *)nullptr, (T *)vel, (T *)fout, ws.acc, fx, (T *)nullptr, fb);
         else
             hipLaunchKernelGGL((k_batch<T, MODE, false, false, kS>), dim3(p->grid), dim3(kHmThreads), 0, s, t->view,
                                p->tile_start, p->tile_info, (int64_t)0, p->counter + 1, kv, rs, kpos, (const T *)field,
-                               kforce, (int32_t *)nullptr, (T *)vel, (T *)fout, ws.acc, ws.fx, (T *)nullptr, fb);
+                               kforce, (int32_t *)nullptr, (T *)vel, (T *)fout, ws.acc, fx, (T *)nullptr, fb);
         OT_HIP(hipGetLastError());
         if (p->timing) OT_HIP(hipEventRecord(p->ev[1], s));
-        if (spread && (rc = spread_epilogue(t, ws, p->dtype, p->mode, 0, fout, s))) return rc;
+        if (spread && (rc = spread_epilogue(t, ws, p->dtype, p->mode, p->accumulate, fout, n, s))) return rc;
         OT_HIP(hipGetLastError());
         return OT_OK;
     }
     const int bops = p->ops_all & ~kOpLocate;
     FbTiles fb{};
-    unsigned *queue = p->counter;
-    int block = p->block;
-    if (p->use_blocks && n > 0) {
-        // dense blocks first, then the ranges of points in sparse ones
-        if ((rc = enqueue_blocks<T, MODE>(t, p->blk, bops, kv, kpos, (const T *)field, (T *)vel, (T *)fout, ws,
+    if (p->sort_points) fb = FbTiles{nullptr, nullptr, (int64_t)p->tile, n, (uint32_t)bops};
+    if (p->sort_points && n > 0 && (p->use_blocks || p->use_nodes)) {
+        // dense blocks first, then the ranges of points in sparse ones (or all points)
+        if (p->use_blocks && (rc = enqueue_blocks<T, MODE>(t, p->blk, bops, kv, kpos, (const T *)field, (T *)vel,
+                                                           (T *)fout, ws, (T *)grad, s)))
+            return rc;
+        const NodeRanges nr = p->use_blocks ? NodeRanges{p->blk.ranges, p->counter + kBlkRanges, n, kBlkWindow, false}
+                                            : NodeRanges{nullptr, nullptr, n, node_range_pts(t, n), true};
+        if ((rc = enqueue_ranges<T, MODE>(t, bops, nr, p->counter, kv, kpos, (const T *)field, (T *)vel, (T *)fout, ws,
                                           (T *)grad, s)))
             return rc;
-        fb = FbTiles{nullptr, p->counter + kBlkRanges, 0, n, (uint32_t)bops, p->blk.ranges};
-        block = kBlkWindow;
+        if (p->timing) OT_HIP(hipEventRecord(p->ev[1], s));
+        return spread ? spread_epilogue(t, ws, p->dtype, p->mode, p->accumulate, fout, n, s) : OT_OK;
     }
 #define OT_KBATCH_S(PERV, GRADV, SV)                                                                               \
-    hipLaunchKernelGGL((k_batch<T, MODE, PERV, GRADV, SV>), dim3(p->grid), dim3(block), 0, s, t->view,               \
-                       p->tile_start, p->tile_info, p->n_tiles, queue, kv, rs, kpos, (const T *)field, kforce,       \
-                       kids, (T *)vel, (T *)fout, ws.acc, ws.fx, (T *)grad, fb)
+    hipLaunchKernelGGL((k_batch<T, MODE, PERV, GRADV, SV>), dim3(p->grid), dim3(p->block), 0, s, t->view,            \
+                       p->tile_start, p->tile_info, p->n_tiles, p->counter, kv, rs, kpos, (const T *)field, kforce,       \
+                       kids, (T *)vel, (T *)fout, ws.acc, fx, (T *)grad, fb)
 #define OT_KBATCH(PERV, GRADV)                                                                                     \
     do {                                                                                                           \
-        if (p->small_table && !p->use_blocks) OT_KBATCH_S(PERV, GRADV, kSmallSlots);                                                \
+        if (p->small_table) OT_KBATCH_S(PERV, GRADV, kSmallSlots);                                                \
         else OT_KBATCH_S(PERV, GRADV, (SinkSlots<T, MODE>::value));                                                \
     } while (0)
     if (p->grad_plan) {
@@ -216,7 +231,7 @@ int enqueue(ot_batch_plan *p, const void *field, const void *force, const void *
     OT_HIP(hipGetLastError());
     if (p->timing) OT_HIP(hipEventRecord(p->ev[1], s));
     if (p->ops_union & kOpSpread)
-        if ((rc = spread_epilogue(t, ws, p->dtype, p->mode, 0, fout, s))) return rc;
+        if ((rc = spread_epilogue(t, ws, p->dtype, p->mode, p->accumulate, fout, n, s))) return rc;
     OT_HIP(hipGetLastError());
     return OT_OK;
 }

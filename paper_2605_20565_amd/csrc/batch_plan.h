@@ -19,11 +19,14 @@ struct BlkWork {
     unsigned *words;
     BlkTile *root_tiles, *sub_tiles;
     uint2 *ranges;
-    int root_grid, sub_grid; // persistent workgroups
+    int grid;                // persistent workgroups of each pass
 };
 int64_t blk_bytes(const ot_tree *t, int64_t n);       // device bytes besides the words
 void blk_layout(const ot_tree *t, int64_t n, void *mem, unsigned *words, BlkWork *w);
-bool blk_rule(const ot_tree *t, int64_t n);           // whether sorted points take the block pass
+bool node_rule(const ot_tree *t, int64_t n, int ops); // ... or the node-parallel pass
+bool small_rule(int64_t n, int ops);                  // ... or the unsorted passes of plain calls
+constexpr int64_t kSortMinSpread = 55000;             // plain calls that spread sort from here on
+bool blk_rule(const ot_tree *t, int64_t n, int ops);  // whether sorted points take the block pass
 }  // namespace ot
 
 struct ot_batch_plan {
@@ -53,7 +56,10 @@ struct ot_batch_plan {
     void *srec[2];            // position (+ force) records in sorted order
     void *sws;                // counting workspace
     void *fxws;               // fixed-point spreading workspace (FIXED plans that spread)
+    int accumulate;           // add to field_out (plain calls)
     bool use_blocks;          // block pass
+    bool use_small;           // unsorted passes of a plain call
+    bool use_nodes;           // node-parallel pass over all sorted points
     ot::BlkWork blk;
     void *blk_mem;
     // host-major pass (sorted forward plans with OT_TUNE_HOST_MAJOR)

@@ -1,5 +1,7 @@
 // Host side of the block pass (block_pass.h): its device memory and the rule
 // that chooses it.
+#include <algorithm>
+
 #include "batch_plan.h"
 #include "block_pass.h"
 
@@ -7,9 +9,17 @@ namespace ot {
 
 namespace {
 int64_t align256(int64_t b) { return (b + 255) & ~int64_t(255); }
-// a dense block of c points gets ceil(c / kBlkTilePts) tiles; a run of sparse
+// a dense block of c points gets ceil(c / blk_tile_pts) tiles; a run of sparse
 // blocks ends at a dense block or at the end of a workgroup's keys
-int64_t max_tiles(int64_t n) { return n / kBlkDense + n / kBlkTilePts + 1; }
+int64_t max_tiles(int64_t n) { return n / kBlkDense + n / kBlkTileMin + 1; }
+
+// Points per tile: whole blocks in large runs, and in smaller ones short tiles
+// for two workgroups per CU (a tile of 2,000 points takes ~50 us alone).
+int64_t blk_tile_pts(const ot_tree *t, int64_t n)
+{
+    return std::min<int64_t>(kBlkTilePts, std::max<int64_t>(kBlkTileMin, n / (2 * t->cus)));
+}
+
 int64_t max_ranges(const ot_tree *t, int64_t n)
 {
     return n / kBlkWindow + n / kBlkDense + (int64_t)t->view.nblk / 64 + 4;
@@ -22,8 +32,8 @@ int64_t max_ranges(const ot_tree *t, int64_t n)
 // consecutive keys; eight lanes find a key's first point, probing eight places
 // of the remaining range at once, so a search is ~log_9 n dependent loads.
 constexpr int kBlkKeys = 128;
-__global__ __launch_bounds__(kBlkKeys * 8) void k_block_bounds(const uint64_t *__restrict__ kv, int64_t n, uint32_t nblk,
-                                                               uint32_t blk1, unsigned *__restrict__ words,
+__global__ __launch_bounds__(kBlkKeys * 8) void k_block_bounds(TreeView tv, const uint64_t *__restrict__ kv, int64_t n,
+                                                               uint32_t tile_pts, unsigned *__restrict__ words,
                                                                BlkTile *__restrict__ root_tiles,
                                                                BlkTile *__restrict__ sub_tiles,
                                                                uint2 *__restrict__ ranges)
@@ -31,6 +41,7 @@ __global__ __launch_bounds__(kBlkKeys * 8) void k_block_bounds(const uint64_t *_
     __shared__ uint32_t st[kBlkKeys];
     __shared__ uint64_t sparse[kBlkKeys / 64];
     __shared__ unsigned cnt[3], base[3];   // root tiles, sub-table tiles, ranges
+    const uint32_t nblk = (uint32_t)tv.nblk, blk1 = (uint32_t)tv.blk1;
     const int grp = threadIdx.x >> 3, sub = threadIdx.x & 7, seg = (threadIdx.x & 63) & ~7;
     const uint32_t key = blockIdx.x * (uint32_t)(kBlkKeys - 1) + (uint32_t)grp;
     if (threadIdx.x < 3) cnt[threadIdx.x] = 0u;
@@ -38,7 +49,7 @@ __global__ __launch_bounds__(kBlkKeys * 8) void k_block_bounds(const uint64_t *_
     int64_t lo = key > nblk ? n : 0, hi = n;
     while (__any(lo < hi)) {
         const int64_t p = lo + (hi - lo) * (sub + 1) / 9;
-        const bool less = lo < hi && (uint32_t)(kv[p] >> 32) < key;
+        const bool less = lo < hi && ((uint32_t)(kv[p] >> 32) & kIdMask) < key;
         const unsigned m = (unsigned)(__ballot(less) >> seg) & 255u;
         if (lo < hi) {
             const int c = __popc(m);
@@ -63,7 +74,7 @@ __global__ __launch_bounds__(kBlkKeys * 8) void k_block_bounds(const uint64_t *_
     __syncthreads();
     uint32_t nt = 0, nr = 0, at = 0, rs = 0, re = 0;
     if (dense) {
-        nt = (c + kBlkTilePts - 1) / kBlkTilePts;
+        nt = (c + tile_pts - 1) / tile_pts;
         at = atomicAdd(&cnt[which], nt);
     } else if (mine && (g == 0 || !((sparse[(g - 1) >> 6] >> ((g - 1) & 63)) & 1ull))) {
         // the first of consecutive sparse keys takes the points of all of them
@@ -87,9 +98,20 @@ __global__ __launch_bounds__(kBlkKeys * 8) void k_block_bounds(const uint64_t *_
     __syncthreads();
     if (nt) {
         BlkTile *out = (which ? sub_tiles : root_tiles) + base[which] + at;
+        // the block's cell, its level l0 and the levels d below it
+        int l0 = tv.lev[0] - kBlkBits, d = kBlkBits;
+        uint64_t m = k;
+        if (which) {
+            int u = 1;
+            while (u + 1 < tv.nlev && (int64_t)k >= tv.blk_base[u + 1]) ++u;
+            l0 = min(tv.lev[0] + 3 * (u - 1), tv.L);
+            d = min(tv.lev[0] + 3 * u, tv.L) - l0;
+            m = tv.blk_anchor[k - blk1] >> (3 * (tv.L - l0));
+        }
+        const uint32_t a[3] = {compact3_21(m), compact3_21(m >> 1), compact3_21(m >> 2)};
         for (uint32_t i = 0; i < nt; ++i) {
             const uint32_t b = (uint32_t)((uint64_t)c * i / nt), e = (uint32_t)((uint64_t)c * (i + 1) / nt);
-            out[i] = BlkTile{(int64_t)s + b, e - b, k};
+            out[i] = BlkTile{s + b, e - b, k, l0, {a[0], a[1], a[2]}, d};
         }
     }
     for (uint32_t i = 0; i < nr; ++i)
@@ -102,11 +124,9 @@ void enqueue_bounds(const ot_tree *t, BlkWork &w, const uint64_t *kv, hipStream_
 {
     const TreeView &tv = t->view;
     const unsigned nb = (unsigned)((tv.nblk + kBlkKeys - 1) / (kBlkKeys - 1));   // keys 0 .. nblk
-    hipLaunchKernelGGL(k_block_bounds, dim3(nb), dim3(kBlkKeys * 8), 0, s, kv, w.n, (uint32_t)tv.nblk,
-                       (uint32_t)tv.blk1, w.words, w.root_tiles, w.sub_tiles, w.ranges);
+    hipLaunchKernelGGL(k_block_bounds, dim3(nb), dim3(kBlkKeys * 8), 0, s, tv, kv, w.n,
+                       (uint32_t)blk_tile_pts(t, w.n), w.words, w.root_tiles, w.sub_tiles, w.ranges);
 }
-
-int block_threads(bool root) { return root ? BlkThreads<float, true>::value : BlkThreads<float, false>::value; }
 
 int64_t blk_bytes(const ot_tree *t, int64_t n)
 {
@@ -117,6 +137,7 @@ void blk_layout(const ot_tree *t, int64_t n, void *mem, unsigned *words, BlkWork
 {
     char *p = (char *)mem;
     w->n = n;
+    w->grid = 2 * t->cus;   // as many as fit in FP32; later ones find the queue empty
     w->words = words;
     w->root_tiles = (BlkTile *)p;
     p += align256((int64_t)sizeof(BlkTile) * max_tiles(n));
@@ -127,10 +148,43 @@ void blk_layout(const ot_tree *t, int64_t n, void *mem, unsigned *words, BlkWork
 
 // Root cubes need a root of at least 8^3 cells.  Fewer than 64 points per
 // block on average leave most blocks to the per-point pass, which then does
-// better on points sorted by groups of 64 leaves.
-bool blk_rule(const ot_tree *t, int64_t n)
+// better on points sorted by groups of 64 leaves.  The pass has three launches
+// more.  Measured, FP32, per-point against block pass: spreading 200 k points
+// on 38 k leaves 122 against 139 us, 400 k 214 -> 141, 1 M 419 -> 168; on 0.5 M
+// leaves 400 k 155 against 163, 1 M 229 -> 188.  Interpolation alone 1 M 107
+// against 132 and 143 against 138, 3 M 213 against 234 and 270 -> 242; on 2.7 M
+// leaves 3 M 322 -> 226.
+// Calls that only spread change over later: their node ranges need no buffer
+// for gathered values in LDS.  Markers in order on 38 k leaves, 331 k points, node ranges
+// against block pass: FP32 115 against 126 us, FP64 128 against 148; with
+// interpolation 137 against 136, FP64 190 against 163.
+constexpr int64_t kBlkMinSpread = 400000, kBlkMinBoth = 300000;
+constexpr int64_t kBlkMinGather = 2000000;
+bool blk_rule(const ot_tree *t, int64_t n, int ops)
 {
-    return t->view.lev[0] >= kBlkBits && n >= 64 * (int64_t)t->view.nblk && n < (int64_t(1) << 31);
+    if (!(ops & ~kOpLocate)) return false;
+    const bool gathers = (ops & (kOpInterp | kOpGrad)) != 0;
+    const int64_t least = !(ops & kOpSpread) ? kBlkMinGather : gathers ? kBlkMinBoth : kBlkMinSpread;
+    return t->view.lev[0] >= kBlkBits && n >= 64 * (int64_t)t->view.nblk && n >= least && n < (int64_t(1) << 31);
+}
+
+// Sorted runs that spread fewer points than this take the node-parallel pass
+// (its launch is 40 us where the per-point pass, one long chain per point,
+// takes 63 to 111 at 200 k points on 38 k leaves; at 1 M the block pass is as
+// fast), or rarer points than a quarter of the leaves (400 k points on 2.7 M
+// leaves 299 us in the per-point pass).
+constexpr int64_t kNodeMaxSpread = 400000;
+bool node_rule(const ot_tree *t, int64_t n, int ops)
+{
+    return (ops & kOpSpread) && (n < kNodeMaxSpread || 4 * n < t->n_leaves);
+}
+
+// Sorted plans of so few points that the plain passes are faster unsorted
+// (30 k points on 38 k leaves: spreading 51 against 61 us, interpolation 10
+// against 47; 100 k: spreading 66 sorted against 134, interpolation 16).
+bool small_rule(int64_t n, int ops)
+{
+    return n > 0 && (ops & ~kOpLocate) && n < ((ops & kOpSpread) ? kSortMinSpread : int64_t(100000));
 }
 
 }  // namespace ot

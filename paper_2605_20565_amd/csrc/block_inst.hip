@@ -12,7 +12,7 @@
 namespace ot {
 
 template <typename T, int MODE>
-const void *block_fn(int ops, bool root)
+static const void *block_fn(int ops, bool root)
 {
     // passes that do not spread are the same in both modes
 #define OT_FN(OPSV)                                                                                                 \
@@ -45,15 +45,15 @@ int enqueue_blocks(const ot_tree *t, BlkWork &w, int ops, const uint64_t *kv, co
         if (root ? tv.blk1 == 0 : tv.nblk == tv.blk1) continue;
         TreeView tvv = tv;
         unsigned long long *acc = ws.acc;
-        const FxState *fx = ws.fx;
-        void *args[] = {&tvv, &tiles, &count, &queue, &kv, &rec, &field, &vel, &fout, &acc, &fx, &grad};
-        OT_HIP(hipLaunchKernel(block_fn<T, MODE>(ops, root), dim3(root ? w.root_grid : w.sub_grid),
+        FxRef fx{ws.fx, w.n};
+        bool stream = 3 * w.n * (int64_t)sizeof(T) > kBlkStreamBytes;
+        void *args[] = {&tvv, &tiles, &count, &queue, &kv, &rec, &field, &vel, &fout, &acc, &fx, &grad, &stream};
+        OT_HIP(hipLaunchKernel(block_fn<T, MODE>(ops, root), dim3(w.grid),
                                dim3(root ? BlkThreads<T, true>::value : BlkThreads<T, false>::value), args, 0, s));
     }
     return OT_OK;
 }
 
-template const void *block_fn<OT_INST_T, OT_INST_MODE>(int ops, bool root);
 template int enqueue_blocks<OT_INST_T, OT_INST_MODE>(const ot_tree *t, BlkWork &w, int ops, const uint64_t *kv,
                                                     const OT_INST_T *rec, const OT_INST_T *field, OT_INST_T *vel,
                                                     OT_INST_T *fout, const FxWs &ws, OT_INST_T *grad, hipStream_t s);

@@ -41,10 +41,14 @@
 
 namespace ot {
 
-// Points [start, start + count) of block `key`.
+// Points [start, start + count) of block `key`: a cell at level l0 with
+// coordinates a there, whose hosts are at levels l0 + 1 .. l0 + d (root cubes:
+// l0 + d).
 struct BlkTile {
-    int64_t start;
-    uint32_t count, key;
+    uint32_t start, count, key;
+    int32_t l0;
+    uint32_t a[3];
+    int32_t d;
 };
 
 // Device words of a plan's block pass, zeroed before each run: counts of
@@ -58,7 +62,8 @@ constexpr int kBlkWindow = 256;     // most points per range of the per-point pa
 // points 0.95 + 0.81, from 24 points 0.80 + 1.37.
 constexpr int kBlkDense = 192;
 constexpr int kBlkTilePts = 3072;   // most points per tile
-constexpr int kRun = 8;             // most points per run
+constexpr int kBlkTileMin = 768;    // least points a block's tiles are cut down to
+constexpr int kRun = 6;             // most points per run (8: +3% on shells, 4: +1 to 2%)
 
 // Nodes of a block's grids: the 10^3 grid first, then (sub-tables) 6^3 and 4^3.
 template <bool ROOT>
@@ -71,11 +76,15 @@ __device__ __forceinline__ int blk_edge(int g) { return (1 << g) + 2; }
 
 constexpr uint32_t kBlkNoNode = 0xFFFFFFFFu;   // a node beyond a wall, or of a grid the block does not have
 
-// Threads of a workgroup: with two workgroups per CU the LDS below fits 160 KiB
-// in FP32; FP64 takes one workgroup.
+// Threads of a workgroup.  Root cubes: two workgroups of 512 per CU (FP32; one
+// of 1024 was 13% slower).  Sub-tables: one of 768 (two of 384 took 7.35 ms in
+// shells of 10^8 points against 5.74: the grids and lookups of a tile then
+// serve twice the threads, and the tiles in flight fit an XCD's L2, where the
+// points are read a second time in host order; 512 and 1024 took 6.4 and 6.0).
+// FP64: one workgroup either way, 512 threads to keep 256 registers.
 template <typename T, bool ROOT>
 struct BlkThreads {
-    static constexpr int value = ROOT ? 512 : 384;
+    static constexpr int value = (ROOT || sizeof(T) == 8) ? 512 : 768;
     static constexpr int waves = sizeof(T) == 8 ? 2 : (ROOT ? 4 : 3);   // per SIMD
 };
 
@@ -96,38 +105,85 @@ struct BlkShared {
     uint32_t runs[kSpread ? NT : 1];  // first point | host node << 10 | (points - 1) << 21
     uint32_t rcnt[kRun], rcur[kRun];
     uint32_t wsum[NT / 64];
-    unsigned tile;
+    unsigned next;                    // the tile after this one
+    BlkTile tile;
 };
 
-// Level-table step of a block: its cell's level l0, the levels d it spans and
-// its cell's coordinates at level l0.
-template <bool ROOT>
-__device__ __forceinline__ void blk_decode(const TreeView &tv, uint32_t key, const uint32_t I0[3], int &l0, int &d,
-                                           uint32_t a[3])
+// Level-l cell of coordinate x along one axis (wrapped when periodic; hosted
+// points of walled domains lie inside), exact as point_cell's.
+template <typename T>
+__device__ __forceinline__ int blk_cell(T x, int l, int periodic)
 {
-    if (ROOT) {
-        l0 = tv.lev[0] - kBlkBits;
-        d = kBlkBits;
-        a[0] = compact3_21(key);
-        a[1] = compact3_21((uint64_t)key >> 1);
-        a[2] = compact3_21((uint64_t)key >> 2);
-    } else {
-        int t = 1;
-        while (t + 1 < tv.nlev &&
-               (int64_t)key >= ((const __attribute__((address_space(1))) int64_t *)tv.blk_base)[t + 1])
-            ++t;
-        l0 = min(tv.lev[0] + 3 * (t - 1), tv.L);
-        d = min(tv.lev[0] + 3 * t, tv.L) - l0;
+    const T sc = (T)(1 << l);
+    T f = floor(x * sc);
+    if (periodic) f -= floor(f * ldexp(T(1), -l)) * sc;
+    return (int)f;
+}
+
+// One point's result at its input row.  stream: an output larger than the
+// memory-side cache, whose scattered rows only push other lines out (measured
+// in shells of 10^8 points: 7.9 -> 7.4 ms; on 10^7 points 0.58 -> 0.64, not taken).
+template <typename T>
+__device__ __forceinline__ void blk_store(T *p, const T (&v)[3], bool stream)
+{
+    if (stream) {
 #pragma unroll
-        for (int c = 0; c < 3; ++c) a[c] = I0[c] >> (tv.L - l0);
+        for (int c = 0; c < 3; ++c) __builtin_nontemporal_store(v[c], p + c);
+    } else {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) p[c] = v[c];
     }
+}
+constexpr int64_t kBlkStreamBytes = int64_t(256) << 20;
+
+// The node that stands for the leaf of node q (grid g, cell n at level
+// l0 + g) when the leaf is coarser than the grid: the leaf's cell in the grid
+// of its own level, or of its cells in the coarsest grid the first one there.
+// All of a leaf's nodes then reach device memory with one add, as one table
+// slot of the per-point pass would (FP32 atomic sums are rounded there).
+__device__ __forceinline__ int blk_canonical(int level, int l0, const uint32_t a[3], int g, const int n[3])
+{
+    const int gg = max(level - l0, 1), k = max(l0 + 1 - level, 0);
+    int q = blk_off(gg), s = 1;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        const int lo = (int)(a[c] << gg) - 1;
+        const int m = ((n[c] >> (g - gg)) >> k) << k;
+        q += s * (max(m, lo) - lo);
+        s *= blk_edge(gg);
+    }
+    return q;
+}
+
+// Grid, and coordinates inside it, of node q.
+template <bool ROOT>
+__device__ __forceinline__ int blk_node(int q, int x[3])
+{
+    if (ROOT || q < 1000) {
+        x[0] = q % 10;
+        x[1] = (q / 10) % 10;
+        x[2] = q / 100;
+        return 3;
+    }
+    if (q < 1216) {
+        q -= 1000;
+        x[0] = q % 6;
+        x[1] = (q / 6) % 6;
+        x[2] = q / 36;
+        return 2;
+    }
+    q -= 1216;
+    x[0] = q & 3;
+    x[1] = (q >> 2) & 3;
+    x[2] = q >> 4;
+    return 1;
 }
 
 template <typename T, int MODE, int OPS, bool ROOT>
 __global__ __launch_bounds__((BlkThreads<T, ROOT>::value), (BlkThreads<T, ROOT>::waves)) void k_block(
     TreeView tv, const BlkTile *__restrict__ tiles, const unsigned *__restrict__ n_tiles, unsigned *__restrict__ queue,
     const uint64_t *__restrict__ kv, const T *__restrict__ rec, const T *__restrict__ field, T *__restrict__ vel,
-    T *__restrict__ fout, unsigned long long *__restrict__ facc, const FxState *__restrict__ fx, T *__restrict__ grad)
+    T *__restrict__ fout, unsigned long long *__restrict__ facc, FxRef fx, T *__restrict__ grad, bool stream)
 {
     using Sh = BlkShared<T, MODE, OPS, ROOT>;
     using Acc = typename Sh::Acc;
@@ -137,144 +193,110 @@ __global__ __launch_bounds__((BlkThreads<T, ROOT>::value), (BlkThreads<T, ROOT>:
     static_assert(kBlkTilePts % NT == 0 && NT <= 1024 && NN <= 2048 && kRun <= 8, "packing of runs");
     __shared__ Sh sh;
     const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-    const double scale = (Sh::kSpread && MODE == kModeFixed) ? fx->scale : 1.0;
+    const double scale = (Sh::kSpread && MODE == kModeFixed) ? fx_scale<T>(fx) : 1.0;
     const unsigned nt = *n_tiles;
     const int rsh = tv.L - tv.lev[0];
+    if (nt == 0u) return;
+    if (tid == 0) {
+        sh.next = atomicAdd(queue, 1u);
+        if (sh.next < nt) sh.tile = tiles[sh.next];
+    }
+    __syncthreads();
 
     for (;;) {
-        if (tid == 0) sh.tile = atomicAdd(queue, 1u);
-        __syncthreads();
-        const unsigned ti = sh.tile;
-        if (ti >= nt) break;   // uniform
-        const BlkTile tile = tiles[ti];
+        if (sh.next >= nt) break;   // uniform
+        const BlkTile tile = sh.tile;
         const int cnt = (int)tile.count;
-        int l0, d;
-        uint32_t a[3];
-        {
-            uint32_t I0[3];
-            (void)point_cell<T>(tv, rec[RS * tile.start], rec[RS * tile.start + 1], rec[RS * tile.start + 2], I0);
-            blk_decode<ROOT>(tv, tile.key, I0, l0, d, a);
-        }
+        const int l0 = ROOT ? tv.lev[0] - kBlkBits : tile.l0, d = ROOT ? kBlkBits : tile.d;
+        const uint32_t a[3] = {tile.a[0], tile.a[1], tile.a[2]};
+        const T *trec = rec + (int64_t)RS * tile.start;
+        const uint64_t *tkv = kv + tile.start;
+        // the next tile is claimed now and its description loaded before the
+        // flush, so neither is waited for
+        unsigned nxt = 0u;
+        if (tid == 0) nxt = atomicAdd(queue, 1u);
 
-        // ---- node leaves and their field values; sums and host counts cleared
-        constexpr int kN = (NN + NT - 1) / NT;
-        {
-            uint32_t e[kN], N[kN][3];
-            bool in[kN];
+        // ---- the points' positions (and host levels), and the nodes' root
+        // entries, all in flight together; sums and host counts cleared
+        T X[kPer][3];
+        uint32_t hi[ROOT ? 1 : kPer];
 #pragma unroll
-            for (int j = 0; j < kN; ++j) {
-                const int q = j * NT + tid;
-                int r = q, E = 10, g = 3;
-                if (!ROOT && q >= 1000) {
-                    g = q >= 1216 ? 1 : 2;
-                    r = q - (q >= 1216 ? 1216 : 1000);
-                    E = g == 1 ? 4 : 6;
-                }
-                int x[3];
-                if (ROOT || g == 3) {
-                    x[0] = r % 10;
-                    x[1] = (r / 10) % 10;
-                    x[2] = r / 100;
-                } else {
-                    x[0] = r % E;
-                    x[1] = (r / E) % E;
-                    x[2] = r / (E * E);
-                }
-                const int l = l0 + g, s = tv.L - l;
-                const int32_t M = 1 << l;
-                in[j] = q < NN && (ROOT || g <= d);
+        for (int j = 0; j < kPer; ++j) {
+            const int i = j * NT + tid < cnt ? j * NT + tid : 0;
 #pragma unroll
-                for (int c = 0; c < 3; ++c) {
-                    int32_t n = (int32_t)(a[c] << g) + x[c] - 1;
-                    if (tv.periodic) n &= M - 1;
-                    else in[j] = in[j] && n >= 0 && n < M;
-                    N[j][c] = in[j] ? ((uint32_t)n << s) | (s > 0 ? 1u << (s - 1) : 0u) : 0u;
-                }
-                e[j] = ld_table(tv, in[j] ? interleave3(N[j][0] >> rsh, N[j][1] >> rsh, N[j][2] >> rsh) : 0u);
-            }
-            uint32_t e1[kN];
-#pragma unroll
-            for (int j = 0; j < kN; ++j) e1[j] = ld_table(tv, step1_index(tv, e[j], N[j][0], N[j][1], N[j][2]));
-#pragma unroll
-            for (int j = 0; j < kN; ++j) {
-                if (e[j] & kSplit) e[j] = e1[j];
-                if (e[j] & kSplit) e[j] = descend_from_level2(tv, e[j], N[j][0], N[j][1], N[j][2]);
-            }
-            if constexpr (Sh::kGather) {
-                T f[kN][3];
-#pragma unroll
-                for (int j = 0; j < kN; ++j) {
-                    const int64_t i = 3 * (int64_t)(in[j] ? e[j] & kIdMask : 0u);
-#pragma unroll
-                    for (int c = 0; c < 3; ++c) f[j][c] = field[i + c];
-                }
-#pragma unroll
-                for (int j = 0; j < kN; ++j) {
-                    const int q = j * NT + tid;
-                    if (q < NN) {
-#pragma unroll
-                        for (int c = 0; c < 3; ++c) sh.u[c][q] = in[j] ? f[j][c] : T(0);
-                    }
-                }
-            }
-#pragma unroll
-            for (int j = 0; j < kN; ++j) {
-                const int q = j * NT + tid;
-                if (q < NN) {
-                    sh.ent[q] = in[j] ? e[j] : kBlkNoNode;
-                    if constexpr (Sh::kSpread) {
-                        sh.acc[q][0] = Acc(0);
-                        sh.acc[q][1] = Acc(0);
-                        sh.acc[q][2] = Acc(0);
-                    }
-                }
-            }
-            for (int i = tid; i < NN / 2 + 1; i += NT) sh.bins[i] = 0u;
+            for (int c = 0; c < 3; ++c) X[j][c] = trec[RS * i + c];
+            if (!ROOT) hi[j] = reinterpret_cast<const uint32_t *>(tkv)[2 * i + 1];
         }
+        constexpr int kN = (NN + NT - 1) / NT;
+        uint32_t e[kN], N[kN][3];
+        bool in[kN];
+#pragma unroll
+        for (int j = 0; j < kN; ++j) {
+            const int q = j * NT + tid;
+            int x[3];
+            const int g = blk_node<ROOT>(q, x);
+            const int l = l0 + g, s = tv.L - l;
+            const int32_t M = 1 << l;
+            in[j] = q < NN && (ROOT || g <= d);
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                int32_t n = (int32_t)(a[c] << g) + x[c] - 1;
+                if (tv.periodic) n &= M - 1;
+                else in[j] = in[j] && n >= 0 && n < M;
+                N[j][c] = in[j] ? ((uint32_t)n << s) | (s > 0 ? 1u << (s - 1) : 0u) : 0u;
+            }
+            e[j] = ld_table(tv, in[j] ? interleave3(N[j][0] >> rsh, N[j][1] >> rsh, N[j][2] >> rsh) : 0u);
+        }
+        if constexpr (Sh::kSpread) {
+            Acc *z = &sh.acc[0][0];
+            for (int i = tid; i < 3 * NN; i += NT) z[i] = Acc(0);
+            if (tid < kRun) {
+                sh.rcnt[tid] = 0u;
+                sh.rcur[tid] = 0u;
+            }
+        }
+        for (int i = tid; i < NN / 2 + 1; i += NT) sh.bins[i] = 0u;
         __syncthreads();
 
-        // Host of a point: its node in the grid of the host's level, and that level.
-        auto host_node = [&](const uint32_t (&I)[3], int &g) -> int {
-            const int s = tv.L - l0 - d;
-            int f[3];
+        // ---- counting sort of the tile's points by host: host counts
+        uint32_t hr[kPer];
 #pragma unroll
-            for (int c = 0; c < 3; ++c) f[c] = (int)((I[c] >> s) - (a[c] << d));
-            g = d;
-            if (!ROOT) {
-                const int E = blk_edge(d);
-                const uint32_t e = sh.ent[blk_off(d) + f[0] + 1 + E * (f[1] + 1 + E * (f[2] + 1))];
-                g = (int)((e >> kLevelShift) & 31u) - l0;
-#pragma unroll
-                for (int c = 0; c < 3; ++c) f[c] >>= d - g;
-            }
+        for (int j = 0; j < kPer; ++j) {
+            if (j * NT >= cnt) break;   // uniform
+            const int g = ROOT ? kBlkBits : (int)((hi[j] >> kLevelShift) & 31u) - l0;
             const int E = ROOT ? 10 : blk_edge(g);
-            return (ROOT ? 0 : blk_off(g)) + f[0] + 1 + E * (f[1] + 1 + E * (f[2] + 1));
-        };
-
-        // ---- counting sort of the tile's points by host
+            int h = ROOT ? 0 : blk_off(g), s = 1;
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                h += s * (blk_cell<T>(X[j][c], l0 + g, tv.periodic) - (int)(a[c] << g) + 1);
+                s *= E;
+            }
+            if (j * NT + tid < cnt) {
+                const int sft = 16 * (h & 1);
+                hr[j] = (uint32_t)h << 16 | ((atomicAdd(&sh.bins[h >> 1], 1u << sft) >> sft) & 0xFFFFu);
+            }
+        }
+        // the nodes' level-1 entries and deeper, then their field rows (in
+        // flight during the rest of the sort)
+        uint32_t e1[kN];
+#pragma unroll
+        for (int j = 0; j < kN; ++j) e1[j] = ld_table(tv, step1_index(tv, e[j], N[j][0], N[j][1], N[j][2]));
+#pragma unroll
+        for (int j = 0; j < kN; ++j) {
+            if (e[j] & kSplit) e[j] = e1[j];
+            if (e[j] & kSplit) e[j] = descend_from_level2(tv, e[j], N[j][0], N[j][1], N[j][2]);
+        }
+        T f[Sh::kGather ? kN : 1][3];
+        if constexpr (Sh::kGather) {
+#pragma unroll
+            for (int j = 0; j < kN; ++j) {
+                const int64_t i = 3 * (int64_t)(in[j] ? e[j] & kIdMask : 0u);
+#pragma unroll
+                for (int c = 0; c < 3; ++c) f[j][c] = field[i + c];
+            }
+        }
+        __syncthreads();
         {
-            T X[kPer][3];
-#pragma unroll
-            for (int j = 0; j < kPer; ++j) {
-                const int i = j * NT + tid;
-                const int64_t k = tile.start + (i < cnt ? i : 0);
-#pragma unroll
-                for (int c = 0; c < 3; ++c) X[j][c] = rec[RS * k + c];
-            }
-            uint32_t hr[kPer];
-#pragma unroll
-            for (int j = 0; j < kPer; ++j) {
-                if (j * NT >= cnt) break;   // uniform
-                uint32_t I[3];
-                (void)point_cell<T>(tv, X[j][0], X[j][1], X[j][2], I);
-                int g;
-                const int h = host_node(I, g);
-                if (j * NT + tid < cnt) {
-                    const int sft = 16 * (h & 1);
-                    hr[j] = (uint32_t)h << 16 | ((atomicAdd(&sh.bins[h >> 1], 1u << sft) >> sft) & 0xFFFFu);
-                }
-            }
-            __syncthreads();
             // exclusive prefix of the counts, in place
             constexpr int kW = (NN / 2 + NT - 1) / NT;   // packed words per thread
             uint32_t v[kW], sum = 0u;
@@ -304,48 +326,54 @@ __global__ __launch_bounds__((BlkThreads<T, ROOT>::value), (BlkThreads<T, ROOT>:
             }
             if (tid == NT - 1) sh.bins[NN / 2] = (uint32_t)cnt;
             __syncthreads();
-            const uint16_t *first = reinterpret_cast<const uint16_t *>(sh.bins);
-#pragma unroll
-            for (int j = 0; j < kPer; ++j) {
-                if (j * NT >= cnt) break;
-                if (j * NT + tid < cnt) sh.perm[first[hr[j] >> 16] + (hr[j] & 0xFFFFu)] = (uint16_t)(j * NT + tid);
-            }
-            __syncthreads();
         }
         const uint16_t *first = reinterpret_cast<const uint16_t *>(sh.bins);
-
-        // ---- chunks of NT sorted points
-        for (int c0 = 0; c0 < cnt; c0 += NT) {
-            if constexpr (Sh::kSpread) {
-                if (tid < kRun) {
-                    sh.rcnt[tid] = 0u;
-                    sh.rcur[tid] = 0u;
+#pragma unroll
+        for (int j = 0; j < kPer; ++j) {
+            if (j * NT >= cnt) break;
+            if (j * NT + tid < cnt) sh.perm[first[hr[j] >> 16] + (hr[j] & 0xFFFFu)] = (uint16_t)(j * NT + tid);
+        }
+#pragma unroll
+        for (int j = 0; j < kN; ++j) {
+            const int q = j * NT + tid;
+            if (q < NN) {
+                sh.ent[q] = in[j] ? e[j] : kBlkNoNode;
+                if constexpr (Sh::kGather) {
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) sh.u[c][q] = in[j] ? f[j][c] : T(0);
                 }
-                __syncthreads();
             }
+        }
+        __syncthreads();
+
+        // ---- chunks of NT sorted points.  (Loading a chunk's records during
+        // the one before it cost registers that spilled: 529 -> 574 us.)
+        for (int c0 = 0; c0 < cnt; c0 += NT) {
             const int i = c0 + tid;
             const int cend = min(c0 + NT, cnt);
             int rl = 0, h = 0;   // this thread's run (0: none starts here)
             if (i < cnt) {
-                const int64_t k = tile.start + sh.perm[i];
-                const T X[3] = {rec[RS * k], rec[RS * k + 1], rec[RS * k + 2]};
+                const int k = sh.perm[i];
+                const T Y[3] = {trec[RS * k], trec[RS * k + 1], trec[RS * k + 2]};
                 T F[3] = {T(0), T(0), T(0)};
                 if (RS == 6) {
-                    F[0] = rec[RS * k + 3];
-                    F[1] = rec[RS * k + 4];
-                    F[2] = rec[RS * k + 5];
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) F[c] = trec[RS * k + 3 + c];
                 }
-                const int64_t kd = (int64_t)(uint32_t)kv[k];
-                uint32_t I[3];
-                (void)point_cell<T>(tv, X[0], X[1], X[2], I);
-                int g;
-                h = host_node(I, g);
-                const T sc = (T)(1 << (l0 + g));
+                const uint64_t wd = tkv[k];
+                const int64_t kd = (int64_t)(uint32_t)wd;
+                const int g = ROOT ? kBlkBits : (int)((uint32_t)(wd >> 58) & 31u) - l0;
+                const int E = ROOT ? 10 : blk_edge(g), l = l0 + g;
+                const T sc = (T)(1 << l);
                 T w[3][3], dw[3][3];
+                h = ROOT ? 0 : blk_off(g);
+                int s = 1;
 #pragma unroll
                 for (int c = 0; c < 3; ++c) {
+                    h += s * (blk_cell<T>(Y[c], l, tv.periodic) - (int)(a[c] << g) + 1);
+                    s *= E;
                     T t, r;
-                    cell_offsets<T>(X[c] * sc, t, r);
+                    cell_offsets<T>(Y[c] * sc, t, r);
                     delta3<T>(t, r, w[c]);
                     if (OPS & kOpGrad) {
                         T wt[3];
@@ -362,14 +390,13 @@ __global__ __launch_bounds__((BlkThreads<T, ROOT>::value), (BlkThreads<T, ROOT>:
                         for (int o = 0; o < 3; ++o) rw[4 * c + o] = w[c][o];
                         rw[4 * c + 3] = F[c];
                     }
-                    const int s = max((int)first[h], c0), e = min((int)first[h + 1], cend);
-                    if (((i - s) & (kRun - 1)) == 0) {
-                        rl = min(kRun, e - i);
+                    const int b = max((int)first[h], c0), z = min((int)first[h + 1], cend);
+                    if ((i - b) % kRun == 0) {
+                        rl = min(kRun, z - i);
                         atomicAdd(&sh.rcnt[rl - 1], 1u);
                     }
                 }
                 if constexpr (Sh::kGather) {
-                    const int E = ROOT ? 10 : blk_edge(g);
                     T U[3] = {T(0), T(0), T(0)}, G[3] = {T(0), T(0), T(0)};
 #pragma unroll
                     for (int oz = 0; oz < 3; ++oz) {
@@ -394,16 +421,8 @@ __global__ __launch_bounds__((BlkThreads<T, ROOT>::value), (BlkThreads<T, ROOT>:
                             }
                         }
                     }
-                    if (OPS & kOpInterp) {
-                        vel[3 * kd] = U[0];
-                        vel[3 * kd + 1] = U[1];
-                        vel[3 * kd + 2] = U[2];
-                    }
-                    if (OPS & kOpGrad) {
-                        grad[3 * kd] = G[0];
-                        grad[3 * kd + 1] = G[1];
-                        grad[3 * kd + 2] = G[2];
-                    }
+                    if (OPS & kOpInterp) blk_store(vel + 3 * kd, U, stream);
+                    if (OPS & kOpGrad) blk_store(grad + 3 * kd, G, stream);
                 }
             }
             if constexpr (Sh::kSpread) {
@@ -421,6 +440,10 @@ __global__ __launch_bounds__((BlkThreads<T, ROOT>::value), (BlkThreads<T, ROOT>:
                     sh.runs[at] = (uint32_t)tid | (uint32_t)h << 10 | (uint32_t)(rl - 1) << 21;
                 }
                 __syncthreads();
+                if (tid < kRun) {   // for the next chunk
+                    sh.rcnt[tid] = 0u;
+                    sh.rcur[tid] = 0u;
+                }
                 const int grp = lane / 3, oz = lane - 3 * grp;
                 for (uint32_t j0 = (uint32_t)wid * 21u; j0 < nruns; j0 += (NT / 64) * 21u) {
                     const uint32_t j = j0 + (uint32_t)grp;
@@ -465,16 +488,46 @@ __global__ __launch_bounds__((BlkThreads<T, ROOT>::value), (BlkThreads<T, ROOT>:
                 __syncthreads();
             }
         }
+        BlkTile nd;
+        if (tid == 0 && nxt < nt) nd = tiles[nxt];
 
         // ---- the nodes' sums to device memory, neighbouring lanes on one
         // node's three components
         if constexpr (Sh::kSpread) {
-            for (int e = tid; e < 3 * NN; e += NT) {
-                const int q = e / 3, c = e - 3 * q;
+            if (!ROOT) {
+                // nodes of leaves coarser than their grid add to one of them
+                for (int q = tid; q < NN; q += NT) {
+                    int x[3];
+                    const int g = blk_node<ROOT>(q, x);
+                    const uint32_t en = sh.ent[q];
+                    const int lv = (int)((en >> kLevelShift) & 31u);
+                    if (g > d || en == kBlkNoNode || lv >= l0 + g) continue;
+                    int n[3];
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) n[c] = (int)(a[c] << g) + x[c] - 1;
+                    const int to = blk_canonical(lv, l0, a, g, n);
+                    if (to == q) continue;
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) {
+                        const Acc v = sh.acc[q][c];
+                        if (v != Acc(0)) {
+                            atomicAdd(&sh.acc[to][c], v);
+                            sh.acc[q][c] = Acc(0);
+                        }
+                    }
+                }
+                __syncthreads();
+            }
+            for (int i = tid; i < 3 * NN; i += NT) {
+                const int q = i / 3, c = i - 3 * q;
                 const Acc v = sh.acc[q][c];
                 const uint32_t en = sh.ent[q];
                 if (v != Acc(0) && en != kBlkNoNode) global_add<T, MODE>(fout, facc, 3 * (int64_t)(en & kIdMask) + c, v);
             }
+        }
+        if (tid == 0) {
+            sh.next = nxt;
+            if (nxt < nt) sh.tile = nd;
         }
         __syncthreads();   // the next tile reuses everything
     }

@@ -130,7 +130,7 @@ __global__ __launch_bounds__(kHmThreads) void k_hm(TreeView tv, int64_t n, int64
                                                    int rs, const T *__restrict__ rec, const T *__restrict__ field,
                                                    T *__restrict__ vel, T *__restrict__ fout,
                                                    unsigned long long *__restrict__ facc,
-                                                   const FxState *__restrict__ fx, uint32_t *__restrict__ fb_list,
+                                                   FxRef fx, uint32_t *__restrict__ fb_list,
                                                    unsigned *__restrict__ fb_count)
 {
     using Acc = typename AccType<T, MODE>::type;
@@ -141,7 +141,7 @@ __global__ __launch_bounds__(kHmThreads) void k_hm(TreeView tv, int64_t n, int64
     constexpr bool kInterp = (OPS & kOpInterp) != 0;
     constexpr bool kSpread = (OPS & kOpSpread) != 0;
     // the fixed-point state exists only for plans that spread
-    const double scale = (kSpread && MODE == kModeFixed) ? fx->scale : 1.0;
+    const double scale = (kSpread && MODE == kModeFixed) ? fx_scale<T>(fx) : 1.0;
     const int rsh = tv.L - tv.lev[0];
 
     for (int i = tid; i < kSlots; i += kHmThreads) {

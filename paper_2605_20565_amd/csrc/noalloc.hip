@@ -14,8 +14,10 @@
 
 #include "ot_common.h"
 
-extern "C" int ot_spread(const ot_tree *t, const void *force, const void *pos, const int32_t *ids, int32_t dtype,
-                         int64_t n, int32_t mode, int32_t accumulate, void *field_out, void *work, void *stream);
+namespace ot {
+int spread_noalloc(const ot_tree *t, const void *force, const void *pos, const int32_t *ids, int32_t dtype, int64_t n,
+                   int32_t mode, int32_t accumulate, void *field_out, void *work, void *stream);   // track.hip
+}
 
 namespace {
 
@@ -54,7 +56,7 @@ extern "C" int ot_spread_noalloc(const ot_tree *t, const void *force, const void
     if (!t) return ot::fail(OT_ERR_INVALID, "tree is NULL");
     if (mode != OT_SPREAD_FIXED) {
         // ATOMIC spreading needs no workspace: the plain call allocates nothing
-        return ot_spread(t, force, pos, ids, dtype, n, mode, accumulate, field_out, nullptr, stream);
+        return ot::spread_noalloc(t, force, pos, ids, dtype, n, mode, accumulate, field_out, nullptr, stream);
     }
     if (t->n_leaves > (int64_t)OT_NOALLOC_MAX_LEAVES)
         return ot::fail(OT_ERR_CAPACITY, "ot_spread_noalloc: the tree has more leaves than the static workspace "
@@ -65,5 +67,5 @@ extern "C" int ot_spread_noalloc(const ot_tree *t, const void *force, const void
     if (dev != t->device) return ot::fail(OT_ERR_INVALID, "ot_spread_noalloc: the tree lives on another device");
     void *work = scratch_on(dev);
     if (!work) return OT_ERR_HIP;
-    return ot_spread(t, force, pos, ids, dtype, n, mode, accumulate, field_out, work, stream);
+    return ot::spread_noalloc(t, force, pos, ids, dtype, n, mode, accumulate, field_out, work, stream);
 }

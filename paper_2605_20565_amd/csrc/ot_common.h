@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <mutex>
 #include <string>
 
 #include "../../include/octrack.h"
@@ -59,6 +60,7 @@ struct TreeView {
     // blocks.  Only trees with lev[0] >= kBlkBits have root cubes.
     int32_t blk1, nblk;
     const int64_t *blk_base;
+    const uint64_t *blk_anchor;   // Morton key of the cell of sub-table block blk1 + i
 };
 constexpr int kBlkBits = 3;
 
@@ -132,7 +134,8 @@ __device__ __forceinline__ int64_t step1_index(const TreeView &tv, uint32_t e, u
 // the root).  The level of each table step is computed and its pool offset
 // read from device memory: a lane-dependent index into the by-value tree
 // view would put a copy of the struct in per-lane scratch memory.
-// BLK: also the block key of the sub-table that holds the leaf.
+// BLK: also the block key of the sub-table that holds the leaf, and how many
+// levels above the sub-table's cells the leaf ends (see k_point_keys).
 template <bool BLK = false>
 __device__ __forceinline__ uint32_t descend_from_level2(const TreeView &tv, uint32_t e, uint32_t ix, uint32_t iy,
                                                         uint32_t iz, uint32_t *key = nullptr)
@@ -193,7 +196,7 @@ template <typename T>
 __device__ __forceinline__ bool point_cell(const TreeView &tv, T x, T y, T z, uint32_t I[3])
 {
     const double sc = (double)(int64_t(1) << tv.L);
-    const double inv = 1.0 / sc;   // a power of two: exact
+    const double inv = ldexp(1.0, -tv.L);
     const double v[3] = {(double)x * sc, (double)y * sc, (double)z * sc};
     bool ok = true;
 #pragma unroll
@@ -217,7 +220,7 @@ template <>
 __device__ __forceinline__ bool point_cell<float>(const TreeView &tv, float x, float y, float z, uint32_t I[3])
 {
     const float sc = (float)(1 << tv.L);
-    const float inv = 1.0f / sc;
+    const float inv = ldexpf(1.0f, -tv.L);
     const float v[3] = {x * sc, y * sc, z * sc};
     bool ok = true;
 #pragma unroll
@@ -318,6 +321,29 @@ void radix_sort_pairs(uint64_t *k0, int32_t *v0, uint64_t *k1, int32_t *v1, int6
                       uint64_t **k_res, int32_t **v_res, hipStream_t s);
 int fail(int code, const std::string &msg);
 
+// Working memory of plain calls that sort their points, kept with the tree
+// between calls (the runtime's stream-ordered allocator took ~50 us of host time
+// a call).  A call takes a buffer nobody is using, waits on its stream for the
+// event of the buffer's last call, and records the event anew when its kernels
+// are enqueued: calls may come from several threads and streams.  At most
+// kScratchSlots buffers and kScratchKeep bytes are kept (more is allocated for
+// the call and freed with it); they are given back with the tree.
+constexpr int kScratchSlots = 4;
+constexpr size_t kScratchKeep = size_t(1) << 30;
+struct ScratchSlot {
+    void *p;
+    size_t bytes;
+    hipEvent_t done;     // the last call's kernels
+    hipStream_t stream;  // and its stream
+    bool busy;           // a call is enqueueing
+};
+struct Scratch {
+    void *p;   // null: none to be had
+    int slot;  // -1: allocated for this call
+};
+Scratch scratch_take(const ot_tree *t, size_t bytes, hipStream_t s);
+void scratch_give(const ot_tree *t, const Scratch &m, hipStream_t s);
+
 // Fixed-point spreading workspace: a 256-byte header (FxState) followed by
 // the n_leaves x 3 int64 accumulators.
 constexpr int64_t kFxHeader = 256;
@@ -342,6 +368,9 @@ struct ot_tree {
     uint32_t *table;     // descent table (root + pools)
     int64_t table_entries;
     ot::TreeView view;
+    // working memory kept for plain calls (scratch_take), under its lock
+    mutable std::mutex scratch_lock;
+    mutable ot::ScratchSlot scratch[ot::kScratchSlots];
     // Read-only after the build: the workspace of fixed-point spreading
     // belongs to each call (or batch plan), so calls on one tree may run on
     // several streams at once.

@@ -26,7 +26,17 @@ struct PointSortResult {
     int stride;           // 6 with forces, 3 without
 };
 
+// Of exactly the n that is sorted: fewer points can make more tiles.
 int64_t point_sort_ws_bytes(int64_t n);
+
+// Memory the key launch clears for the kernels after it: `words` 32-bit words
+// at p (a spreading target or workspace, or none), and a plan's counters.
+struct SortZero {
+    uint32_t *p;
+    int64_t words;
+    unsigned *counters;
+    int n_counters;
+};
 
 // What a sort orders by: bits [shift, shift + bits) of a key, and the key of
 // a point without a host (`none`, which sorts last).
@@ -65,6 +75,7 @@ inline PointSortKey point_sort_by_block(int32_t nblk)
 // sets maxbits[1] when a component is not finite.
 template <typename T>
 void point_sort(const TreeView &tv, int64_t n, const PointSortKey &key, const T *pos, const T *force, int32_t *ids,
-                PointSortBufs<T> &b, unsigned long long *maxbits, hipStream_t s, PointSortResult<T> &out);
+                PointSortBufs<T> &b, const SortZero &zero, unsigned long long *maxbits, hipStream_t s,
+                PointSortResult<T> &out);
 
 }  // namespace ot

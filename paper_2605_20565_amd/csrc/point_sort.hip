@@ -30,8 +30,9 @@ namespace ot {
 namespace {
 
 constexpr int kThreads = 256;
-constexpr int kItems = 8;
-constexpr int kTile = kThreads * kItems;   // 2048
+// Points per thread and tile: 8 (2048 points), fewer in small sorts, whose
+// kernels are a few waves' latency (items_for).
+constexpr int kMaxItems = 8;
 constexpr int kBits = 8;
 constexpr int kBuckets = 1 << kBits;
 static_assert(kThreads == kBuckets, "one digit per thread in the digit scan");
@@ -74,7 +75,6 @@ __device__ __forceinline__ int xcd_tile(int nblocks)
 // LDS index with one pad word per 32: the blocked reads (stride kItems) and
 // the striped writes both spread over the banks.
 __device__ __forceinline__ int pad(int i) { return i + (i >> 5); }
-constexpr int kPadded = kTile + kTile / 32;
 
 __device__ __forceinline__ uint32_t exscan_256(uint32_t v, uint32_t *sh_w, uint32_t &total)
 {
@@ -121,6 +121,30 @@ __device__ __forceinline__ void block_max_to(unsigned long long v, unsigned long
     }
 }
 
+// Part `part` of `parts` of what the key launch clears.
+__device__ __forceinline__ void zero_share(const SortZero &z, int part, int parts)
+{
+    const int64_t step = (int64_t)parts * kThreads, t = (int64_t)part * kThreads + threadIdx.x;
+    if (((uintptr_t)z.p & 15u) == 0) {
+        const int64_t n4 = z.words >> 2;
+        uint4 *q = reinterpret_cast<uint4 *>(z.p);
+        for (int64_t i = t; i < n4; i += step) q[i] = make_uint4(0u, 0u, 0u, 0u);
+        if (t < (z.words & 3)) z.p[4 * n4 + t] = 0u;
+    } else {
+        for (int64_t i = t; i < z.words; i += step) z.p[i] = 0u;
+    }
+    if (part == 0 && (int)threadIdx.x < z.n_counters) z.counters[threadIdx.x] = 0u;
+}
+
+// A tile's digit counts: digit by digit for the scan, or (by_tile) tile by
+// tile for the scatter to sum up itself.
+__device__ __forceinline__ void put_counts(const uint32_t *hist, uint32_t dmask, uint32_t *__restrict__ counts, int tile,
+                                           int nblocks, bool by_tile)
+{
+    for (int d = threadIdx.x; d <= (int)dmask; d += kThreads)
+        counts[by_tile ? (int64_t)tile * (dmask + 1) + d : (int64_t)d * nblocks + tile] = hist[d];
+}
+
 // Host leaf of every point (and ids when asked): kv = entry << 32 | index
 // with the host's leaf entry (level << 26 | id); points without a host get
 // n_leaves.  Digits are taken from the id bits only.  Workgroup b covers the first
@@ -128,12 +152,18 @@ __device__ __forceinline__ void block_max_to(unsigned long long v, unsigned long
 // A thread's kItems points go through the descent together: all positions,
 // then all root-table loads, then the deeper levels, so that the table loads
 // (the pass's latency) are in flight at once rather than one after another.
-template <typename T, bool BLK>
+template <typename T, bool BLK, int kItems>
 __global__ __launch_bounds__(kThreads) void k_point_keys(TreeView tv, int64_t n, const T *__restrict__ pos,
                                                          int32_t *__restrict__ ids, uint64_t *__restrict__ kv,
                                                          uint32_t none, int shift, uint32_t dmask,
-                                                         uint32_t *__restrict__ counts, int nblocks)
+                                                         uint32_t *__restrict__ counts, int nblocks, bool by_tile,
+                                                         SortZero zero)
 {
+    if ((int)blockIdx.x >= nblocks) {   // the workgroups after the tiles' clear
+        zero_share(zero, (int)blockIdx.x - nblocks, (int)gridDim.x - nblocks);
+        return;
+    }
+    constexpr int kTile = kThreads * kItems;
     __shared__ uint32_t hist[kBuckets];
     for (int i = threadIdx.x; i < kBuckets; i += kThreads) hist[i] = 0;
     __syncthreads();
@@ -182,6 +212,7 @@ __global__ __launch_bounds__(kThreads) void k_point_keys(TreeView tv, int64_t n,
         if (e[j] & kSplit) e[j] = descend_from_level2<BLK>(tv, e[j], I[j][0], I[j][1], I[j][2], &key[j]);
         if (!BLK) key[j] = e[j];
         else if (!ok[j]) key[j] = none;
+        else key[j] |= (e[j] & ~kIdMask);   // the host's level above the key's 26 bits
     }
 #pragma unroll
     for (int j = 0; j < kItems; ++j) {
@@ -195,12 +226,15 @@ __global__ __launch_bounds__(kThreads) void k_point_keys(TreeView tv, int64_t n,
         }
     }
     __syncthreads();
-    for (int d = threadIdx.x; d <= (int)dmask; d += kThreads) counts[(int64_t)d * nblocks + tile] = hist[d];
+    put_counts(hist, dmask, counts, tile, nblocks, by_tile);
 }
 
+template <int kItems>
 __global__ __launch_bounds__(kThreads) void k_point_hist(const uint64_t *__restrict__ kv, int64_t n, int shift,
-                                                         uint32_t dmask, uint32_t *__restrict__ counts, int nblocks)
+                                                         uint32_t dmask, uint32_t *__restrict__ counts, int nblocks,
+                                                         bool by_tile)
 {
+    constexpr int kTile = kThreads * kItems;
     __shared__ uint32_t hist[kBuckets];
     for (int i = threadIdx.x; i < kBuckets; i += kThreads) hist[i] = 0;
     __syncthreads();
@@ -217,20 +251,21 @@ __global__ __launch_bounds__(kThreads) void k_point_hist(const uint64_t *__restr
     for (int j = 0; j < kItems; ++j)
         if (base + j * kThreads + threadIdx.x < n) atomicAdd(&hist[((hk[j] & kIdMask) >> shift) & dmask], 1u);
     __syncthreads();
-    for (int d = threadIdx.x; d <= (int)dmask; d += kThreads) counts[(int64_t)d * nblocks + tile] = hist[d];
+    put_counts(hist, dmask, counts, tile, nblocks, by_tile);
 }
 
 // One counting pass over tiles of kTile points, stable except the first
 // (first != 0).  Records come from rin (R values per point) or, in the first
 // pass, from pos (3 per point) and force (3 per point, R = 6 only).
 // maxbits != null: also max |F| over the finite force components.
-template <typename T, int R>
+template <typename T, int R, int kItems>
 __global__ __launch_bounds__(kThreads) void k_point_scatter(
     const uint64_t *__restrict__ kin, const T *__restrict__ rin, const T *__restrict__ pos,
     const T *__restrict__ force, uint64_t *__restrict__ kout, T *__restrict__ rout, int64_t n, int shift,
-    int pbits, const uint32_t *__restrict__ offs, const uint32_t *__restrict__ offs_hi, int nblocks,
+    int pbits, bool by_tile, const uint32_t *__restrict__ offs, const uint32_t *__restrict__ offs_hi, int nblocks,
     unsigned long long *__restrict__ maxbits, int first)
 {
+    constexpr int kTile = kThreads * kItems, kPadded = kTile + kTile / 32;
     __shared__ uint32_t sk[kPadded];
     __shared__ uint16_t si[kPadded];
     __shared__ uint32_t sh_w[kThreads / 64];
@@ -238,6 +273,7 @@ __global__ __launch_bounds__(kThreads) void k_point_scatter(
     __shared__ uint32_t dcount[kBuckets];
     __shared__ uint32_t dcur[kBuckets];
     __shared__ unsigned long long sh_max[kThreads / 64];
+    __shared__ uint32_t goff[kBuckets];   // by_tile: where this tile's run of each digit starts
 
     const uint32_t dmask = (1u << pbits) - 1u;
     const int tile = xcd_tile(nblocks);
@@ -306,6 +342,27 @@ __global__ __launch_bounds__(kThreads) void k_point_scatter(
         uint32_t tot;
         const uint32_t c = dcount[threadIdx.x];
         dstart[threadIdx.x] = exscan_256(c, sh_w, tot);
+    }
+    if (by_tile) {
+        // offs holds every tile's counts: few tiles, so each workgroup sums
+        // the digit totals and its own prefix itself (no scan launches)
+        uint32_t all = 0u, before = 0u;
+        if (threadIdx.x <= dmask) {
+            const uint32_t *c = offs + threadIdx.x;
+            constexpr int kU = 32;
+            for (int t0 = 0; t0 < nblocks; t0 += kU) {
+                uint32_t v[kU];
+#pragma unroll
+                for (int u = 0; u < kU; ++u) v[u] = c[(int64_t)min(t0 + u, nblocks - 1) * (dmask + 1)];
+#pragma unroll
+                for (int u = 0; u < kU; ++u) {
+                    all += t0 + u < nblocks ? v[u] : 0u;
+                    before += t0 + u < tile ? v[u] : 0u;
+                }
+            }
+        }
+        uint32_t tot;
+        goff[threadIdx.x] = exscan_256(all, sh_w, tot) + before;
     }
     __syncthreads();
     if (first) {
@@ -388,8 +445,13 @@ __global__ __launch_bounds__(kThreads) void k_point_scatter(
         const int i = j * kThreads + threadIdx.x;
         const uint32_t key = sk[pad(i)];
         const uint32_t d = ((key & kIdMask) >> shift) & dmask;
-        const int64_t oi = (int64_t)d * nblocks + tile;
-        const int64_t o = (int64_t)offs[oi] + (offs_hi ? (int64_t)offs_hi[oi / kScanBlock] : 0);
+        int64_t o;
+        if (by_tile) {
+            o = (int64_t)goff[d];
+        } else {
+            const int64_t oi = (int64_t)d * nblocks + tile;
+            o = (int64_t)offs[oi] + (offs_hi ? (int64_t)offs_hi[oi / kScanBlock] : 0);
+        }
         dstv[j] = i < valid ? o + (i - (int)dstart[d]) : -1;
         srcv[j] = i < valid ? (int)si[pad(i)] : 0;
     }
@@ -439,35 +501,55 @@ __global__ __launch_bounds__(kThreads) void k_point_scatter(
     }
 }
 
-template <typename T, int R>
-void sort_passes(const TreeView &tv, int64_t n, const PointSortKey &key, const T *pos, const T *force, int32_t *ids,
-                 PointSortBufs<T> &b, unsigned long long *maxbits, hipStream_t s, PointSortResult<T> &out)
+// Sorts of at most this many tiles leave the digit offsets to the scatter,
+// which sums the tiles' counts while it waits for its records; the scan's two
+// launches a pass are saved.  Spreading 300 k markers in order took 125 us with
+// the line at 128 tiles, 122 at 256 and 512; 1 M took 180, 180 and 193.
+constexpr int kByTile = 256;
+
+// Points per thread: as few as make kSmallTiles tiles or less, since a small
+// sort's kernels are a few waves' latency (spreading 60 k points 62 -> 58 us,
+// 100 k 67 -> 63).
+constexpr int kSmallTiles = 128;
+int items_for(int64_t n)
 {
+    return n <= kSmallTiles * kThreads * 2 ? 2 : (n <= kSmallTiles * kThreads * 4 ? 4 : kMaxItems);
+}
+
+template <typename T, int R, int ITEMS>
+void sort_passes(const TreeView &tv, int64_t n, const PointSortKey &key, const T *pos, const T *force, int32_t *ids,
+                 PointSortBufs<T> &b, const SortZero &zero, unsigned long long *maxbits, hipStream_t s,
+                 PointSortResult<T> &out)
+{
+    constexpr int kTile = kThreads * ITEMS;
     const int nb = (int)((n + kTile - 1) / kTile);
     // the passes share the key bits evenly: fewer digits make longer runs
     const int passes = (key.bits + kBits - 1) / kBits;
     const int pbits = (key.bits + passes - 1) / passes;
     const uint32_t dmask = (1u << pbits) - 1u;
     const int64_t nc = (int64_t)(dmask + 1) * nb;
+    const bool by_tile = nb <= kByTile;
     uint32_t *counts = (uint32_t *)b.ws, *offs = counts + nc, *tmp = offs + nc;
+    const int nz = (int)std::min<int64_t>(1024, (zero.words + 4 * kThreads - 1) / (4 * kThreads)) + (zero.n_counters ? 1 : 0);
     if (key.blocks)
-        hipLaunchKernelGGL((k_point_keys<T, true>), dim3(nb), dim3(kThreads), 0, s, tv, n, pos, ids, b.kv[0], key.none,
-                           key.shift, dmask, counts, nb);
+        hipLaunchKernelGGL((k_point_keys<T, true, ITEMS>), dim3(nb + nz), dim3(kThreads), 0, s, tv, n, pos, ids, b.kv[0],
+                           key.none, key.shift, dmask, counts, nb, by_tile, zero);
     else
-        hipLaunchKernelGGL((k_point_keys<T, false>), dim3(nb), dim3(kThreads), 0, s, tv, n, pos, ids, b.kv[0], key.none,
-                           key.shift, dmask, counts, nb);
+        hipLaunchKernelGGL((k_point_keys<T, false, ITEMS>), dim3(nb + nz), dim3(kThreads), 0, s, tv, n, pos, ids, b.kv[0],
+                           key.none, key.shift, dmask, counts, nb, by_tile, zero);
     const uint64_t *kin = b.kv[0];
     const T *rin = nullptr;
     int cur = 0;
     for (int p = 0; p < passes; ++p) {
         const int o = cur ^ 1;   // write buffer: 1, 0, 1, ...
         const int sh = key.shift + p * pbits;
-        if (p > 0) hipLaunchKernelGGL(k_point_hist, dim3(nb), dim3(kThreads), 0, s, kin, n, sh, dmask, counts, nb);
+        if (p > 0)
+            hipLaunchKernelGGL(k_point_hist<ITEMS>, dim3(nb), dim3(kThreads), 0, s, kin, n, sh, dmask, counts, nb, by_tile);
         // the digit offsets: each 2048-count block's own scan, plus the
         // blocks' scanned sums, which the scatter adds (one launch less)
-        const uint32_t *offs_hi = exclusive_scan_split(counts, offs, nc, tmp, s);
-        hipLaunchKernelGGL((k_point_scatter<T, R>), dim3(nb), dim3(kThreads), 0, s, kin, rin, pos, force, b.kv[o],
-                           b.rec[o], n, sh, pbits, (const uint32_t *)offs, offs_hi, nb,
+        const uint32_t *offs_hi = by_tile ? nullptr : exclusive_scan_split(counts, offs, nc, tmp, s);
+        hipLaunchKernelGGL((k_point_scatter<T, R, ITEMS>), dim3(nb), dim3(kThreads), 0, s, kin, rin, pos, force, b.kv[o],
+                           b.rec[o], n, sh, pbits, by_tile, (const uint32_t *)(by_tile ? counts : offs), offs_hi, nb,
                            p == 0 ? maxbits : (unsigned long long *)nullptr, p == 0 ? 1 : 0);
         kin = b.kv[o];
         rin = b.rec[o];
@@ -477,29 +559,42 @@ void sort_passes(const TreeView &tv, int64_t n, const PointSortKey &key, const T
     out.rec = rin;
 }
 
+template <typename T, int R>
+void sort_sized(const TreeView &tv, int64_t n, const PointSortKey &key, const T *pos, const T *force, int32_t *ids,
+                PointSortBufs<T> &b, const SortZero &zero, unsigned long long *maxbits, hipStream_t s,
+                PointSortResult<T> &out)
+{
+    switch (items_for(n)) {
+    case 2: sort_passes<T, R, 2>(tv, n, key, pos, force, ids, b, zero, maxbits, s, out); break;
+    case 4: sort_passes<T, R, 4>(tv, n, key, pos, force, ids, b, zero, maxbits, s, out); break;
+    default: sort_passes<T, R, kMaxItems>(tv, n, key, pos, force, ids, b, zero, maxbits, s, out); break;
+    }
+    out.stride = R;
+}
+
 }  // namespace
 
 int64_t point_sort_ws_bytes(int64_t n)
 {
-    const int64_t nb = (n + kTile - 1) / kTile;
+    const int64_t tile = kThreads * items_for(n), nb = (n + tile - 1) / tile;
     const int64_t nc = (int64_t)kBuckets * nb;
     return 4 * (2 * nc + scan_tmp_words(nc)) + 256;
 }
 
 template <typename T>
 void point_sort(const TreeView &tv, int64_t n, const PointSortKey &key, const T *pos, const T *force, int32_t *ids,
-                PointSortBufs<T> &b, unsigned long long *maxbits, hipStream_t s, PointSortResult<T> &out)
+                PointSortBufs<T> &b, const SortZero &zero, unsigned long long *maxbits, hipStream_t s,
+                PointSortResult<T> &out)
 {
-    if (force) sort_passes<T, 6>(tv, n, key, pos, force, ids, b, maxbits, s, out);
-    else sort_passes<T, 3>(tv, n, key, pos, nullptr, ids, b, nullptr, s, out);
-    out.stride = force ? 6 : 3;
+    if (force) sort_sized<T, 6>(tv, n, key, pos, force, ids, b, zero, maxbits, s, out);
+    else sort_sized<T, 3>(tv, n, key, pos, nullptr, ids, b, zero, nullptr, s, out);
 }
 
 template void point_sort<float>(const TreeView &, int64_t, const PointSortKey &, const float *, const float *,
-                                int32_t *, PointSortBufs<float> &, unsigned long long *, hipStream_t,
+                                int32_t *, PointSortBufs<float> &, const SortZero &, unsigned long long *, hipStream_t,
                                 PointSortResult<float> &);
 template void point_sort<double>(const TreeView &, int64_t, const PointSortKey &, const double *, const double *,
-                                 int32_t *, PointSortBufs<double> &, unsigned long long *, hipStream_t,
+                                 int32_t *, PointSortBufs<double> &, const SortZero &, unsigned long long *, hipStream_t,
                                  PointSortResult<double> &);
 
 }  // namespace ot

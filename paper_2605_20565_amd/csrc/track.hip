@@ -9,6 +9,7 @@
 // int64 fixed point for order-independent sums).
 #include <hip/hip_runtime.h>
 
+#include "batch_plan.h"
 #include "ot_common.h"
 #include "track_device.h"
 
@@ -27,19 +28,35 @@ int dispatch_nodes(int ops, const ot_tree *t, hipStream_t s, int64_t n, const vo
                    const void *force, int32_t *ids, void *vel, void *fout, void *grad, const FxWs &ws,
                    const int32_t *hid);
 
+// A plain call as one run of a sorted plan (batch.hip).
+int sorted_pass(const ot_tree *t, int ops, const void *field, const void *force, const void *pos, int dtype, int64_t n,
+                int mode, int accumulate, int32_t *ids, void *vel, void *fout, void *grad, void *work, hipStream_t s,
+                bool &handled);
+
 constexpr int kMaxPointsPerThread = 4;
 
-// Point sets up to these sizes take the node-parallel pass (node_pass.h).
-// Measured, FP32, random points on 38 k leaves, kernel alone, per-point pass
-// against this one.  Interpolation: 1 k points 6.6 -> 4.5 us, 10 k 7.1 -> 4.9,
-// 25 k 8.4 -> 5.0, 49 k 9.8 -> 7.4 (with the gradient 10.1 -> 11.1, and slower on
-// larger trees from 25 k).  Spreading: 1 k 37 -> 9.2 us, 10 k 49 -> 18, 49 k 174
-// -> 61; from 65,536 points the per-point pass takes tiles of 128 points with
-// the large table, and markers in order on few leaves are faster there (100 k:
-// 66 against 134 us a call).  A whole fused FP32 fixed-point call on 11 k points:
-// 53.5 -> 25.9 us (three launches instead of five).
+// Unsorted point sets up to these sizes take the node-parallel pass
+// (node_pass.h).  Measured, FP32, random points on 38 k leaves, kernel alone,
+// per-point pass against this one.  Interpolation: 1 k points 6.6 -> 4.5 us, 10 k
+// 7.1 -> 4.9, 25 k 8.4 -> 5.0, 49 k 9.8 -> 7.4 (with the gradient 10.1 -> 11.1, and
+// slower on larger trees from 25 k).  Spreading: 1 k 37 -> 9.2 us, 10 k 49 -> 18,
+// 49 k 174 -> 61; calls that may not sort take it up to 65,535 points (from
+// there the per-point pass takes tiles of 128 points with the large table, and
+// markers in order on few leaves are faster there: 100 k 66 against 134 us a
+// call).  A whole fused FP32 fixed-point call on 11 k points: 53.5 -> 25.9 us
+// (three launches instead of five).
 constexpr int64_t kNodesMaxSpread = 65535;
 constexpr int64_t kNodesMaxGather = 16384;
+// Larger sets are sorted first, as a sorted plan does, when the call searches
+// the hosts itself and may allocate: calls that spread from kSortMinSpread
+// points (random points on 38 k leaves, fixed point: 60 k 88 -> 58 us, 100 k
+// 238 -> 63, 1 M 3406 -> 160; markers in order 100 k 66 -> 63, 1 M 236 -> 179;
+// FP64 forward and backward of 50 k random points 118 unsorted, 132 sorted),
+// others from
+// kSortMinGather, gradients apart (3 M random points 350 -> 217 us on 38 k
+// leaves, 828 -> 246 on 2.7 M; markers in order 212 -> 220, 270 -> 234; with the
+// gradient markers in order lost, 218 -> 315).
+constexpr int64_t kSortMinGather = 2000000;
 
 // Prepare the spreading target before a pass: zero the output (atomic mode,
 // overwrite) or the fixed-point accumulators and compute the scale.
@@ -107,7 +124,8 @@ void nodes_end(const ot_tree *t, const FxWs &ws, int accumulate, void *fout, int
 {
     const int64_t n3 = t->n_leaves * 3;
     const unsigned gb = (unsigned)std::min<int64_t>((n3 + 255) / 256, 8192);
-    hipLaunchKernelGGL((k_fx_finalize<T, true>), dim3(gb), dim3(256), 0, s, ws.acc, (T *)fout, n3, ws.fx, accumulate, n);
+    hipLaunchKernelGGL((k_fx_finalize<T, true>), dim3(gb), dim3(256), 0, s, ws.acc, (T *)fout, n3, FxRef{ws.fx, n},
+                       accumulate);
 }
 
 }  // namespace
@@ -123,8 +141,8 @@ int spread_begin(const ot_tree *t, const FxWs &ws, int dtype, int mode, int accu
         }
         if (counters) hipLaunchKernelGGL(k_fill<unsigned>, dim3(1), dim3(64), 0, s, counters, n_counters, 0u);
     } else {
-        // the whole header (max |F|, the non-finite flag; the scale is set
-        // later) and the accumulators after it, and the counters
+        // the whole header (max |F|, the non-finite flag) and the accumulators
+        // after it, and the counters
         hipLaunchKernelGGL(k_zero2, dim3(1024), dim3(256), 0, s, (unsigned long long *)ws.fx,
                            kFxHeader / 8 + n3, counters, n_counters);
     }
@@ -132,42 +150,32 @@ int spread_begin(const ot_tree *t, const FxWs &ws, int dtype, int mode, int accu
     return OT_OK;
 }
 
-int spread_scale(const ot_tree *t, const FxWs &ws, int dtype, int mode, const void *force, int64_t n, hipStream_t s)
+int spread_max(const FxWs &ws, int dtype, int mode, const void *force, int64_t n, hipStream_t s)
 {
-    (void)t;
-    if (mode != OT_SPREAD_FIXED) return OT_OK;
-    const int64_t m = force ? n * 3 : 0;
-    if (m > 0) {
-        unsigned gb = (unsigned)std::min<int64_t>((m + 1023) / 1024, 1024);
-        if (dtype == OT_F32)
-            hipLaunchKernelGGL(k_maxabs<float>, dim3(gb), dim3(256), 0, s, (const float *)force, m, &ws.fx->maxbits);
-        else
-            hipLaunchKernelGGL(k_maxabs<double>, dim3(gb), dim3(256), 0, s, (const double *)force, m, &ws.fx->maxbits);
-    }
-    if (dtype == OT_F32) hipLaunchKernelGGL(k_fx_prepare<float>, dim3(1), dim3(64), 0, s, ws.fx, n);
-    else hipLaunchKernelGGL(k_fx_prepare<double>, dim3(1), dim3(64), 0, s, ws.fx, n);
+    const int64_t m = n * 3;
+    if (mode != OT_SPREAD_FIXED || !force || m <= 0) return OT_OK;
+    unsigned gb = (unsigned)std::min<int64_t>((m + 1023) / 1024, 1024);
+    if (dtype == OT_F32)
+        hipLaunchKernelGGL(k_maxabs<float>, dim3(gb), dim3(256), 0, s, (const float *)force, m, &ws.fx->maxbits);
+    else
+        hipLaunchKernelGGL(k_maxabs<double>, dim3(gb), dim3(256), 0, s, (const double *)force, m, &ws.fx->maxbits);
     OT_HIP(hipGetLastError());
     return OT_OK;
 }
 
-int spread_prologue(const ot_tree *t, const FxWs &ws, int dtype, int mode, int accumulate, const void *force,
-                    int64_t n, void *fout, hipStream_t s)
-{
-    int rc = spread_begin(t, ws, dtype, mode, accumulate, fout, s);
-    return rc ? rc : spread_scale(t, ws, dtype, mode, force, n, s);
-}
-
-int spread_epilogue(const ot_tree *t, const FxWs &ws, int dtype, int mode, int accumulate, void *fout, hipStream_t s)
+int spread_epilogue(const ot_tree *t, const FxWs &ws, int dtype, int mode, int accumulate, void *fout, int64_t n,
+                    hipStream_t s)
 {
     if (mode != OT_SPREAD_FIXED) return OT_OK;
     const int64_t n3 = t->n_leaves * 3;
     const unsigned gb = (unsigned)std::min<int64_t>((n3 + 255) / 256, 8192);
+    const FxRef fx{ws.fx, n};
     if (dtype == OT_F32)
-        hipLaunchKernelGGL((k_fx_finalize<float, false>), dim3(gb), dim3(256), 0, s, ws.acc, (float *)fout, n3, ws.fx,
-                           accumulate, (int64_t)0);
+        hipLaunchKernelGGL((k_fx_finalize<float, false>), dim3(gb), dim3(256), 0, s, ws.acc, (float *)fout, n3, fx,
+                           accumulate);
     else
-        hipLaunchKernelGGL((k_fx_finalize<double, false>), dim3(gb), dim3(256), 0, s, ws.acc, (double *)fout, n3, ws.fx,
-                           accumulate, (int64_t)0);
+        hipLaunchKernelGGL((k_fx_finalize<double, false>), dim3(gb), dim3(256), 0, s, ws.acc, (double *)fout, n3, fx,
+                           accumulate);
     OT_HIP(hipGetLastError());
     return OT_OK;
 }
@@ -251,7 +259,7 @@ int launch_ops(const ot_tree *t, int ops, const void *field, const void *force, 
 // (FIXED spreading only; NULL: allocated on the stream for this call).
 int run_pass(const ot_tree *t, int ops, const void *field, const void *force, const void *pos, int dtype, int64_t n,
              int mode, int accumulate, int32_t *ids, void *vel, void *fout, void *grad, const int32_t *hid,
-             void *work, hipStream_t s)
+             void *work, hipStream_t s, bool may_sort = true)
 {
     int rc = check_common(t, dtype, n, pos);
     if (rc) return rc;
@@ -278,6 +286,15 @@ int run_pass(const ot_tree *t, int ops, const void *field, const void *force, co
         work = owned;
     }
     const FxWs ws = fx_ws(work);
+    if (may_sort && !hid && (ops & ~kOpLocate) && n <= INT32_MAX &&
+        (spread ? n >= kSortMinSpread : n >= kSortMinGather && !(ops & kOpGrad))) {
+        bool handled;
+        rc = sorted_pass(t, ops, field, force, pos, dtype, n, mode, accumulate, ids, vel, fout, grad, work, s, handled);
+        if (handled) {
+            if (owned) (void)hipFreeAsync(owned, s);
+            return rc;
+        }
+    }
     if (n > 0 && (ops & ~kOpLocate) && n <= (spread ? kNodesMaxSpread : kNodesMaxGather)) {
         rc = dtype == OT_F32 ? nodes_pass<float>(t, ops, field, force, pos, dtype, n, mode, accumulate, ids, vel, fout,
                                                  grad, ws, hid, s)
@@ -286,14 +303,30 @@ int run_pass(const ot_tree *t, int ops, const void *field, const void *force, co
         if (owned) (void)hipFreeAsync(owned, s);
         return rc;
     }
-    if (spread) rc = spread_prologue(t, ws, dtype, mode, accumulate, force, n, fout, s);
+    if (spread) rc = spread_begin(t, ws, dtype, mode, accumulate, fout, s);
+    if (!rc && spread) rc = spread_max(ws, dtype, mode, force, n, s);
     if (!rc) rc = launch_ops(t, ops, field, force, pos, dtype, n, mode, ids, vel, fout, grad, ws, hid, s);
-    if (!rc && spread) rc = spread_epilogue(t, ws, dtype, mode, accumulate, fout, s);
+    if (!rc && spread) rc = spread_epilogue(t, ws, dtype, mode, accumulate, fout, n, s);
     if (owned) (void)hipFreeAsync(owned, s);
     return rc;
 }
 
 }  // namespace
+
+// A plain call as it is, unsorted (a plan of few points).
+int plain_pass(const ot_tree *t, int ops, const void *field, const void *force, const void *pos, int dtype, int64_t n,
+               int mode, int32_t *ids, void *vel, void *fout, void *grad, void *work, hipStream_t s)
+{
+    return run_pass(t, ops, field, force, pos, dtype, n, mode, 0, ids, vel, fout, grad, nullptr, work, s, false);
+}
+
+// ot_spread without any allocation (work given, or ATOMIC).
+int spread_noalloc(const ot_tree *t, const void *force, const void *pos, const int32_t *ids, int32_t dtype, int64_t n,
+                   int32_t mode, int32_t accumulate, void *field_out, void *work, void *stream)
+{
+    return run_pass(t, kOpSpread, nullptr, force, pos, dtype, n, mode, accumulate, nullptr, nullptr, field_out,
+                    nullptr, ids, work, (hipStream_t)stream, false);
+}
 
 }  // namespace ot
 

@@ -21,14 +21,18 @@ enum : int { kModeAtomic = OT_SPREAD_ATOMIC, kModeFixed = OT_SPREAD_FIXED };
 struct FxState {
     unsigned long long maxbits;   // bit pattern of max |F| (IEEE order == value order for >= 0)
     unsigned long long nonfinite; // != 0: some force component is NaN or infinite
-    double scale;                 // 2^s
-    double inv;                   // 2^-s
+    unsigned long long unused[2];
     // Small calls: max |F| bits of each workgroup of the clearing kernel (bit
     // 63: it saw a non-finite component), which the later kernels reduce
     // themselves (fx_scale); nothing to clear first and no atomics.
     unsigned long long parts[28];
 };
 constexpr int kFxParts = 28;
+// The state and the number of points, which give the scale 2^s (fx_shift).
+struct FxRef {
+    const FxState *st;
+    int64_t n;
+};
 static_assert(sizeof(FxState) == kFxHeader, "the header of a spreading workspace");
 
 // A spreading workspace: header and n_leaves x 3 int64 accumulators.
@@ -314,9 +318,8 @@ __device__ __forceinline__ bool host_from_id(const TreeView &tv, int32_t h, uint
 // force[rs k + 0..2] (rs = 3 for the caller's arrays, the record stride for
 // sorted records).  For sorted points, word is the point's sort word (the
 // host's leaf entry << 32 | input index): the host comes from the word,
-// found by the sort's key pass on the same position (word_host; else the
-// word holds no host and the descent finds it), and the per-point outputs go
-// to the input index.  Otherwise the host is hid[k] when the
+// found by the sort's key pass on the same position, and the per-point
+// outputs go to the input index.  Otherwise the host is hid[k] when the
 // caller gives host ids (Algorithm 1's host_cell_id; -1 or an id out of
 // range: no host), else the table descent finds it.  With kOpGrad, force[k]
 // is also the vector the gradient contracts the field with, and the
@@ -326,15 +329,14 @@ __device__ __forceinline__ void track_point_at(const TreeView &tv, int64_t k, bo
                                                const T (&X)[3], int rs, const T *__restrict__ field,
                                                const T *__restrict__ force, int32_t *__restrict__ ids,
                                                T *__restrict__ vel, Sink &sink, T *__restrict__ grad,
-                                               const int32_t *__restrict__ hid, const T *Fpre = nullptr,
-                                               bool word_host = true)
+                                               const int32_t *__restrict__ hid, const T *Fpre = nullptr)
 {
     const int64_t kd = sorted ? (int64_t)(uint32_t)word : k;
     const int64_t kp = (int64_t)rs * k;
     uint32_t I[3];
     bool ok = point_cell<T>(tv, X[0], X[1], X[2], I);
     uint32_t e = 0u;
-    if (sorted && word_host) e = (uint32_t)(word >> 32);
+    if (sorted) e = (uint32_t)(word >> 32);
     else if (hid) ok = host_from_id(tv, hid[k], e) && ok;
     else if (ok) e = descend(tv, I[0], I[1], I[2]);
     if (!ok) e = 0u;
@@ -557,45 +559,45 @@ __device__ __forceinline__ int fx_shift(unsigned long long maxbits, int64_t n)
     return s;
 }
 
-// Scale, its inverse and the non-finite flag from a small call's parts.
+// 2^s of a run: every workgroup forms it from max |F| itself (a few scalar
+// instructions, against a launch of its own).
 template <typename T>
-__device__ __forceinline__ void fx_scale(const FxState *fx, int64_t n, double &scale, double &inv, bool &poison)
+__device__ __forceinline__ double fx_scale(const FxRef &fx)
+{
+    return ldexp(1.0, fx_shift<T>(fx.st->maxbits, fx.n));
+}
+
+// A small call's shift and non-finite flag, from its parts.
+template <typename T>
+__device__ __forceinline__ int fx_parts_shift(const FxRef &fx, bool &poison)
 {
     unsigned long long m = 0ull, any = 0ull;
 #pragma unroll
     for (int i = 0; i < kFxParts; ++i) {
-        const unsigned long long v = fx->parts[i];
+        const unsigned long long v = fx.st->parts[i];
         any |= v;
         m = std::max(m, v & 0x7FFFFFFFFFFFFFFFull);
     }
-    const int s = fx_shift<T>(m, n);
-    scale = ldexp(1.0, s);
-    inv = ldexp(1.0, -s);
     poison = (any >> 63) != 0ull;
-}
-
-template <typename T>
-__global__ void k_fx_prepare(FxState *fx, int64_t n)
-{
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    const int s = fx_shift<T>(fx->maxbits, n);
-    fx->scale = ldexp(1.0, s);
-    fx->inv = ldexp(1.0, -s);
+    return fx_shift<T>(m, fx.n);
 }
 
 // Accumulators to field_out.  A non-finite force cannot be carried by the
 // integer sums, so when one was seen every output value becomes NaN.
-// PARTS: a small call of n points, whose scale comes from the parts.
+// PARTS: a small call, whose scale comes from the parts.
 template <typename T, bool PARTS>
-__global__ void k_fx_finalize(const unsigned long long *__restrict__ acc, T *__restrict__ out, int64_t n3,
-                              const FxState *__restrict__ fx, int accumulate, int64_t n)
+__global__ void k_fx_finalize(const unsigned long long *__restrict__ acc, T *__restrict__ out, int64_t n3, FxRef fx,
+                              int accumulate)
 {
-    double inv = fx->inv;
-    bool poison = fx->nonfinite != 0ull;
+    bool poison;
+    int s;
     if (PARTS) {
-        double scale;
-        fx_scale<T>(fx, n, scale, inv, poison);
+        s = fx_parts_shift<T>(fx, poison);
+    } else {
+        s = fx_shift<T>(fx.st->maxbits, fx.n);
+        poison = fx.st->nonfinite != 0ull;
     }
+    const double inv = ldexp(1.0, -s);
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n3; i += (int64_t)gridDim.x * blockDim.x) {
         const T v = poison ? T(NAN) : (T)((double)(long long)acc[i] * inv);
         out[i] = accumulate ? out[i] + v : v;
@@ -622,8 +624,7 @@ __device__ __forceinline__ void track_range(const TreeView &tv, int64_t start, i
                                             const uint64_t *__restrict__ kv, int rs, const T *__restrict__ pos,
                                             const T *__restrict__ field, const T *__restrict__ force,
                                             int32_t *__restrict__ ids, T *__restrict__ vel, Sink &sink,
-                                            T *__restrict__ grad = nullptr, const int32_t *__restrict__ hid = nullptr,
-                                            bool word_host = true)
+                                            T *__restrict__ grad = nullptr, const int32_t *__restrict__ hid = nullptr)
 {
     if (!kv) {
         for (int64_t k = start + threadIdx.x; k < end; k += blockDim.x)
@@ -661,7 +662,7 @@ __device__ __forceinline__ void track_range(const TreeView &tv, int64_t start, i
             Fn[2] = force[(int64_t)rs * kc + 2];
         }
         track_point_at<T, OPS, PER, Sink>(tv, k, true, w, X, rs, field, force, ids, vel, sink, grad, nullptr,
-                                          kF ? F : nullptr, word_host);
+                                          kF ? F : nullptr);
         if (!more) break;
         k = kn;
         w = wn;
@@ -689,14 +690,14 @@ constexpr int64_t kSmallTile = 64;
 constexpr int kSmallSlots = 512;
 
 // Host side of spreading (track.hip): clear the target (ATOMIC overwrite) or
-// the workspace's accumulators, take the fixed-point scale (max |F| over
-// `force` unless the caller already maxed it into ws.fx), and convert the
-// accumulators into field_out.
+// the workspace, take max |F| over n forces, and convert the accumulators
+// into field_out (n: the run's points, which the scale depends on).
 // counters (optional): 32-bit words to zero in the same launch (a batch plan's).
 int spread_begin(const ot_tree *t, const FxWs &ws, int dtype, int mode, int accumulate, void *fout, hipStream_t s,
                  unsigned *counters = nullptr, int64_t n_counters = 0);
-int spread_scale(const ot_tree *t, const FxWs &ws, int dtype, int mode, const void *force, int64_t n, hipStream_t s);
-int spread_epilogue(const ot_tree *t, const FxWs &ws, int dtype, int mode, int accumulate, void *fout, hipStream_t s);
+int spread_max(const FxWs &ws, int dtype, int mode, const void *force, int64_t n, hipStream_t s);
+int spread_epilogue(const ot_tree *t, const FxWs &ws, int dtype, int mode, int accumulate, void *fout, int64_t n,
+                    hipStream_t s);
 FxWs fx_ws(void *work);
 
 }  // namespace ot

@@ -19,7 +19,7 @@ __global__ __launch_bounds__(512) void k_track(TreeView tv, int64_t n, int64_t t
                                                const T *__restrict__ field, const T *__restrict__ force,
                                                int32_t *__restrict__ ids, T *__restrict__ vel,
                                                T *__restrict__ fout, unsigned long long *__restrict__ facc,
-                                               const FxState *__restrict__ fx, T *__restrict__ grad,
+                                               FxRef fx, T *__restrict__ grad,
                                                const int32_t *__restrict__ hid)
 {
     const int64_t start = (int64_t)blockIdx.x * tile;
@@ -28,7 +28,7 @@ __global__ __launch_bounds__(512) void k_track(TreeView tv, int64_t n, int64_t t
         using Acc = typename AccType<T, MODE>::type;
         __shared__ uint32_t keys[S];
         __shared__ Acc vals[LdsSink<T, MODE, S>::kVals];
-        const double scale = MODE == kModeFixed ? fx->scale : 0.0;
+        const double scale = MODE == kModeFixed ? fx_scale<T>(fx) : 0.0;
         LdsSink<T, MODE, S> sink{keys, vals, fout, facc, scale};
         sink.clear();
         __syncthreads();
@@ -46,10 +46,10 @@ void launch_track(const ot_tree *t, dim3 g, dim3 b, int64_t tile, hipStream_t s,
 {
     if (t->view.periodic)
         hipLaunchKernelGGL((k_track<T, OPS, MODE, true, S>), g, b, 0, s, t->view, n, tile, P, Fd, Fo, ids, V, O,
-                           ws.acc, ws.fx, Gr, hid);
+                           ws.acc, FxRef{ws.fx, n}, Gr, hid);
     else
         hipLaunchKernelGGL((k_track<T, OPS, MODE, false, S>), g, b, 0, s, t->view, n, tile, P, Fd, Fo, ids, V, O,
-                           ws.acc, ws.fx, Gr, hid);
+                           ws.acc, FxRef{ws.fx, n}, Gr, hid);
 }
 
 template <typename T, int MODE>

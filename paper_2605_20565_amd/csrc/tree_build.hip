@@ -311,9 +311,11 @@ __global__ void k_fill_u32(uint32_t *p, int64_t n, uint32_t v)
 
 // Write the entries of table level t.  Leaves with lev[t-1] < level <= lev[t]
 // fill the 8^(lev[t]-level) entries they cover; the first leaf of each split
-// level-lev[t] cell writes the pointer to its sub-table.
+// level-lev[t] cell writes the pointer to its sub-table and the sub-table's
+// anchor (anchors: of the next table level).
 __global__ void k_write_level(const uint64_t *__restrict__ keys, const uint8_t *__restrict__ lv, int64_t n,
-                              TreeView tv, uint32_t *__restrict__ table, int t, const uint32_t *__restrict__ sub_ids)
+                              TreeView tv, uint32_t *__restrict__ table, int t, const uint32_t *__restrict__ sub_ids,
+                              uint64_t *__restrict__ anchors)
 {
     int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (j >= n) return;
@@ -351,7 +353,10 @@ __global__ void k_write_level(const uint64_t *__restrict__ keys, const uint8_t *
         for (int64_t c = 0; c < cnt; ++c) table[base + digit + c] = ent;
     } else {
         const uint64_t cell = 1ull << (3 * (L - tv.lev[t]));
-        if ((k & (cell - 1)) == 0) table[base + digit] = kSplit | sub_ids[j];
+        if ((k & (cell - 1)) == 0) {
+            table[base + digit] = kSplit | sub_ids[j];
+            anchors[sub_ids[j]] = k;
+        }
     }
 }
 
@@ -436,6 +441,101 @@ void radix_sort_pairs(uint64_t *k0, int32_t *v0, uint64_t *k1, int32_t *v1, int6
 
 }  // namespace ot
 
+namespace ot {
+
+namespace {
+// A graph capture that another stream or thread has under way (in its default,
+// global mode) forbids allocating and asking events; scratch memory never takes
+// part in one, so the calls here are made in relaxed mode.
+struct RelaxedCapture {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    bool set;
+    RelaxedCapture() : set(hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess) {}
+    ~RelaxedCapture()
+    {
+        if (set) (void)hipThreadExchangeStreamCaptureMode(&mode);
+    }
+    RelaxedCapture(const RelaxedCapture &) = delete;
+    RelaxedCapture &operator=(const RelaxedCapture &) = delete;
+};
+}  // namespace
+
+Scratch scratch_take(const ot_tree *t, size_t bytes, hipStream_t s)
+{
+    std::lock_guard<std::mutex> lock(t->scratch_lock);
+    const RelaxedCapture relaxed;
+    ScratchSlot *best = nullptr, *empty = nullptr;
+    size_t kept = 0;
+    for (ScratchSlot &c : t->scratch) {
+        kept += c.bytes;
+        if (c.busy) continue;
+        if (!c.p) empty = &c;
+        else if (c.bytes >= bytes && (c.stream == s || hipEventQuery(c.done) == hipSuccess) &&
+                 (!best || c.bytes < best->bytes))
+            best = &c;
+    }
+    (void)hipGetLastError();   // an event not reached yet is no error
+    if (!best) {
+        // a new buffer, or one that is too small made larger
+        if (!empty) {
+            for (ScratchSlot &c : t->scratch)
+                if (!c.busy && c.bytes < bytes && (!empty || c.bytes < empty->bytes)) empty = &c;
+            if (empty) {
+                kept -= empty->bytes;
+                (void)hipFree(empty->p);   // waits for its last call
+                empty->p = nullptr;
+                empty->bytes = 0;
+            }
+        }
+        const size_t want = (bytes + bytes / 4 + 0xFFFFF) & ~size_t(0xFFFFF);
+        if (empty && kept + want <= kScratchKeep) {
+            if (!empty->done && hipEventCreateWithFlags(&empty->done, hipEventDisableTiming) != hipSuccess) empty->done = nullptr;
+            if (empty->done && hipMalloc(&empty->p, want) == hipSuccess) {
+                empty->bytes = want;
+                empty->stream = s;
+                empty->busy = true;
+                return {empty->p, (int)(empty - t->scratch)};
+            }
+            empty->p = nullptr;
+            (void)hipGetLastError();
+        }
+        void *p = nullptr;
+        if (hipMallocAsync(&p, bytes, s) != hipSuccess) {
+            (void)hipGetLastError();
+            p = nullptr;
+        }
+        return {p, -1};
+    }
+    if (hipStreamWaitEvent(s, best->done, 0) != hipSuccess) {
+        (void)hipGetLastError();
+        return {nullptr, -1};
+    }
+    best->busy = true;
+    return {best->p, (int)(best - t->scratch)};
+}
+
+void scratch_give(const ot_tree *t, const Scratch &m, hipStream_t s)
+{
+    const RelaxedCapture relaxed;
+    if (m.slot < 0) {
+        if (m.p) (void)hipFreeAsync(m.p, s);
+        return;
+    }
+    std::lock_guard<std::mutex> lock(t->scratch_lock);
+    ScratchSlot &c = t->scratch[m.slot];
+    c.stream = s;
+    if (hipEventRecord(c.done, s) != hipSuccess) {
+        // without the event the buffer cannot be handed on in order
+        (void)hipGetLastError();
+        (void)hipFree(c.p);
+        c.p = nullptr;
+        c.bytes = 0;
+    }
+    c.busy = false;
+}
+
+}  // namespace ot
+
 using namespace ot;
 
 extern "C" int ot_encode_keys(const uint32_t *anchors, int64_t n, int32_t l_max, uint64_t *keys, void *stream)
@@ -503,11 +603,12 @@ extern "C" int ot_build_tree(const uint64_t *keys, const uint8_t *levels, int64_
     if (herr & kErrDup) return fail(OT_ERR_UNSORTED_DUP, "ot_build_tree: two leaves share a Morton key");
     if (herr & kErrPartition) return fail(OT_ERR_NOT_PARTITION, "ot_build_tree: leaves do not tile the unit cube");
 
-    int64_t entries = int64_t(1) << (3 * tv.lev[0]);
+    int64_t entries = int64_t(1) << (3 * tv.lev[0]), n_sub = 0;
     tv.off[0] = 0;
     for (int t = 1; t < tv.nlev; ++t) {
         tv.off[t] = entries;
         entries += (int64_t)hcnt[t - 1] << (3 * (tv.lev[t] - tv.lev[t - 1]));
+        n_sub += (int64_t)hcnt[t - 1];
     }
     if (entries >= (int64_t(1) << 40)) return fail(OT_ERR_CAPACITY, "ot_build_tree: descent table too large");
     // the pool offsets follow the entries, 8-byte aligned, then the root's
@@ -517,8 +618,10 @@ extern "C" int ot_build_tree(const uint64_t *keys, const uint8_t *levels, int64_
     // (both pool offsets and block-key bases, int64 each)
     const int64_t sum_at = off_at + 4 * kMaxTabLevels;
     const int64_t sum_cells = tv.lev[0] >= 1 ? (int64_t(1) << (3 * (tv.lev[0] - 1))) : 0;
+    // and the anchors of the sub-tables, in the order of their block keys
+    const int64_t anc_at = (sum_at + sum_cells + 1) & ~int64_t(1);
     DevBuf table, flags, ids, stmp;
-    if ((rc = dalloc(table, (sum_at + sum_cells) * 4)) || (rc = dalloc(flags, n * 4)) || (rc = dalloc(ids, n * 4)) ||
+    if ((rc = dalloc(table, (anc_at + 2 * n_sub) * 4)) || (rc = dalloc(flags, n * 4)) || (rc = dalloc(ids, n * 4)) ||
         (rc = dalloc(stmp, scan_tmp_words(n) * 4)))
         return rc;
     hipLaunchKernelGGL(k_fill_u32, dim3(2048), dim3(256), 0, s, (uint32_t *)table.p, entries, 0xFFFFFFFFu);
@@ -542,7 +645,8 @@ extern "C" int ot_build_tree(const uint64_t *keys, const uint8_t *levels, int64_
             exclusive_scan((uint32_t *)flags.p, (uint32_t *)ids.p, n, (uint32_t *)stmp.p, s);
         }
         hipLaunchKernelGGL(k_write_level, dim3(nblk(n)), dim3(256), 0, s, ks, (const uint8_t *)lvs.p, n, tv,
-                           (uint32_t *)table.p, t, (const uint32_t *)ids.p);
+                           (uint32_t *)table.p, t, (const uint32_t *)ids.p,
+                           (uint64_t *)((uint32_t *)table.p + anc_at) + (t + 1 < tv.nlev ? bb[t + 1] - tv.blk1 : 0));
     }
     if (sum_cells)
         hipLaunchKernelGGL(k_root_summary, dim3(nblk(sum_cells)), dim3(256), 0, s, (const uint32_t *)table.p, sum_cells,
@@ -573,6 +677,7 @@ extern "C" int ot_build_tree(const uint64_t *keys, const uint8_t *levels, int64_
     tv.table = tr->table;
     tv.pool_off = (const int64_t *)(tr->table + off_at);
     tv.blk_base = tv.pool_off + kMaxTabLevels;
+    tv.blk_anchor = (const uint64_t *)(tr->table + anc_at);
     tv.summary = sum_cells ? tr->table + sum_at : nullptr;
     tv.levels = tr->levels;
     tv.nleaf = (int32_t)n;
@@ -588,6 +693,10 @@ extern "C" int ot_destroy_tree(ot_tree *t)
     (void)hipGetDevice(&cur);
     (void)hipSetDevice(t->device);
     (void)hipDeviceSynchronize();
+    for (ScratchSlot &c : t->scratch) {
+        if (c.p) (void)hipFree(c.p);
+        if (c.done) (void)hipEventDestroy(c.done);
+    }
     (void)hipFree(t->keys);
     (void)hipFree(t->levels);
     (void)hipFree(t->table);
