@@ -307,7 +307,7 @@ __device__ __forceinline__ void delta3_grad(T t, T s, T w[3], T dw[3])
 void set_error(const std::string &msg);
 
 // Device-wide helpers (tree_build.hip): exclusive scan of uint32 and the
-// LDS-staged LSD radix sort of (uint64 key, int32 value) pairs.
+// LDS-staged LSD radix sort of keys (32 or 64 bits) with their positions.
 int64_t scan_tmp_words(int64_t n);
 void exclusive_scan(const uint32_t *in, uint32_t *out, int64_t n, uint32_t *tmp, hipStream_t s);
 // The same scan without its last pass: out holds every 2048-value block's
@@ -317,8 +317,9 @@ void exclusive_scan(const uint32_t *in, uint32_t *out, int64_t n, uint32_t *tmp,
 const uint32_t *exclusive_scan_split(const uint32_t *in, uint32_t *out, int64_t n, uint32_t *tmp, hipStream_t s);
 constexpr int64_t kScanBlock = 2048;
 int64_t radix_ws_bytes(int64_t n);
-void radix_sort_pairs(uint64_t *k0, int32_t *v0, uint64_t *k1, int32_t *v1, int64_t n, int bits, void *ws,
-                      uint64_t **k_res, int32_t **v_res, hipStream_t s);
+template <typename K>
+void radix_sort_pairs(const K *kin, K *ka, int32_t *va, K *kb, int32_t *vb, int64_t n, int bits, void *ws, K **k_res,
+                      int32_t **v_res, hipStream_t s);
 int fail(int code, const std::string &msg);
 
 // Working memory of plain calls that sort their points, kept with the tree

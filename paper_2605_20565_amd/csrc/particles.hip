@@ -138,20 +138,19 @@ __global__ __launch_bounds__(256) void k_particle_step(TreeView tv, int l_min, i
 // leaf id, or n_leaves when it has none (those go last); value: its index.
 template <typename T>
 __global__ __launch_bounds__(256) void k_particle_keys(TreeView tv, int64_t n, const T *__restrict__ pos,
-                                                       uint64_t *__restrict__ key, int32_t *__restrict__ val)
+                                                       uint32_t *__restrict__ key)
 {
     const int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (k >= n) return;
     uint32_t I[3];
     const bool ok = point_cell<T>(tv, pos[3 * k], pos[3 * k + 1], pos[3 * k + 2], I);
-    key[k] = ok ? (uint64_t)(descend(tv, I[0], I[1], I[2]) & kIdMask) : (uint64_t)tv.nleaf;
-    val[k] = (int32_t)k;
+    key[k] = ok ? descend(tv, I[0], I[1], I[2]) & kIdMask : (uint32_t)tv.nleaf;
 }
 
 // Row i of the outputs is input row src[i] of each state array.
 template <typename T>
-__global__ __launch_bounds__(256) void k_particle_gather(int64_t n, const uint64_t *__restrict__ key,
-                                                         const int32_t *__restrict__ src, uint64_t nleaf,
+__global__ __launch_bounds__(256) void k_particle_gather(int64_t n, const uint32_t *__restrict__ key,
+                                                         const int32_t *__restrict__ src, uint32_t nleaf,
                                                          const T *__restrict__ pos, const T *__restrict__ vel,
                                                          const T *__restrict__ vel_prev,
                                                          const T *__restrict__ acc_prev, T *__restrict__ pos_o,
@@ -248,8 +247,8 @@ extern "C" int ot_particle_sort(const ot_tree *t, int32_t dtype, int64_t n, cons
         work = owned;
     }
     char *w = (char *)work;
-    uint64_t *k0 = (uint64_t *)w;
-    uint64_t *k1 = (uint64_t *)(w + psort_align(8 * n));
+    uint32_t *k0 = (uint32_t *)w;
+    uint32_t *k1 = (uint32_t *)(w + psort_align(8 * n));
     int32_t *v0 = (int32_t *)(w + 2 * psort_align(8 * n));
     int32_t *v1 = (int32_t *)(w + 2 * psort_align(8 * n) + psort_align(4 * n));
     void *rws = w + 2 * psort_align(8 * n) + 2 * psort_align(4 * n);
@@ -258,15 +257,15 @@ extern "C" int ot_particle_sort(const ot_tree *t, int32_t dtype, int64_t n, cons
     while (bits < 31 && ((int64_t)1 << bits) <= t->n_leaves) ++bits;
     const dim3 g((unsigned)((n + 255) / 256)), b(256);
     if (dtype == OT_F32)
-        hipLaunchKernelGGL(k_particle_keys<float>, g, b, 0, s, t->view, n, (const float *)pos, k0, v0);
+        hipLaunchKernelGGL(k_particle_keys<float>, g, b, 0, s, t->view, n, (const float *)pos, k0);
     else
-        hipLaunchKernelGGL(k_particle_keys<double>, g, b, 0, s, t->view, n, (const double *)pos, k0, v0);
-    uint64_t *ks = nullptr;
+        hipLaunchKernelGGL(k_particle_keys<double>, g, b, 0, s, t->view, n, (const double *)pos, k0);
+    uint32_t *ks = nullptr;
     int32_t *vs = nullptr;
-    radix_sort_pairs(k0, v0, k1, v1, n, bits, rws, &ks, &vs, s);
+    radix_sort_pairs(k0, k1, v1, k0, v0, n, bits, rws, &ks, &vs, s);
 #define OT_PGATHER(TT)                                                                                           \
-    hipLaunchKernelGGL(k_particle_gather<TT>, g, b, 0, s, n, (const uint64_t *)ks, (const int32_t *)vs,          \
-                       (uint64_t)t->n_leaves, (const TT *)pos, (const TT *)vel, (const TT *)vel_prev,            \
+    hipLaunchKernelGGL(k_particle_gather<TT>, g, b, 0, s, n, (const uint32_t *)ks, (const int32_t *)vs,          \
+                       (uint32_t)t->n_leaves, (const TT *)pos, (const TT *)vel, (const TT *)vel_prev,            \
                        (const TT *)acc_prev, (TT *)pos_out, (TT *)vel_out, (TT *)vel_prev_out, (TT *)acc_prev_out, \
                        ids_out, perm_out)
     if (dtype == OT_F32) OT_PGATHER(float);
