@@ -31,6 +31,7 @@ __global__ __launch_bounds__(kThreads) void k_body_sums(const T *__restrict__ ve
     const int64_t hi = min(max(offsets[b + 1], lo), n);
     const double c[3] = {(double)centres[3 * b], (double)centres[3 * b + 1], (double)centres[3 * b + 2]};
     double acc[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+#pragma unroll 4
     for (int64_t k = lo + threadIdx.x; k < hi; k += kThreads) {
         double r[3], v[3];
         const double w = dv ? (double)dv[k] : dv_all;

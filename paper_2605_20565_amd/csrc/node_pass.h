@@ -55,6 +55,45 @@ struct NodeLane {
     }
 };
 
+// A lane's three nodes: leaf entry, root cell, and whether the node exists.
+struct NodeRow {
+    uint32_t ent[3], root[3];
+    bool in[3];
+};
+
+// The leaves of this lane's row of nodes of the cell I at its host level l.
+template <bool PER>
+__device__ __forceinline__ void node_row(const TreeView &tv, const NodeLane &ln, const uint32_t (&I)[3], int l, bool ok,
+                                         NodeRow &nr)
+{
+    const int sh = tv.L - l, rsh = tv.L - tv.lev[0];
+    const int32_t M = 1 << l;
+    const uint32_t half = sh > 0 ? 1u << (sh - 1) : 0u;
+    uint32_t N[3][3], sub[3];
+#pragma unroll
+    for (int ox = 0; ox < 3; ++ox) {
+        const int o[3] = {ox, ln.oy, ln.oz};
+        nr.in[ox] = ok;
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            int32_t c = (int32_t)(I[d] >> sh) + o[d] - 1;
+            if (PER) c &= M - 1;
+            else nr.in[ox] = nr.in[ox] && c >= 0 && c < M;
+            N[ox][d] = ((uint32_t)c << sh) | half;
+        }
+        if (!nr.in[ox]) N[ox][0] = N[ox][1] = N[ox][2] = 0u;
+        nr.root[ox] = interleave3(N[ox][0] >> rsh, N[ox][1] >> rsh, N[ox][2] >> rsh);
+        nr.ent[ox] = ld_table(tv, nr.root[ox]);
+    }
+#pragma unroll
+    for (int ox = 0; ox < 3; ++ox) sub[ox] = ld_table(tv, step1_index(tv, nr.ent[ox], N[ox][0], N[ox][1], N[ox][2]));
+#pragma unroll
+    for (int ox = 0; ox < 3; ++ox) {
+        if (nr.ent[ox] & kSplit) nr.ent[ox] = sub[ox];
+        if (nr.ent[ox] & kSplit) nr.ent[ox] = descend_from_level2(tv, nr.ent[ox], N[ox][0], N[ox][1], N[ox][2]);
+    }
+}
+
 // One point per nine lanes, all threads of the workgroup: position X, host
 // entry e (ok: it has one), force F; results to index kd (have: there is a
 // point).  buf: LDS, one entry per point of the workgroup.
@@ -69,10 +108,8 @@ __device__ __forceinline__ void node_step(const TreeView &tv, const NodeLane &ln
     using Acc = typename AccType<T, MODE>::type;
     const int row = ln.row, oy = ln.oy, oz = ln.oz, slot = ln.slot;
     // the stencil's 1-D weights, and this lane's three nodes
-    const int l = (int)((e >> kLevelShift) & 31u), sh = tv.L - l, rsh = tv.L - tv.lev[0];
-    const int32_t M = 1 << l;
-    const uint32_t half = sh > 0 ? 1u << (sh - 1) : 0u;
-    const T sc = (T)M;
+    const int l = (int)((e >> kLevelShift) & 31u);
+    const T sc = (T)(1 << l);
     T w[3][3], dw[3][3];
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
@@ -86,31 +123,10 @@ __device__ __forceinline__ void node_step(const TreeView &tv, const NodeLane &ln
             for (int o = 0; o < 3; ++o) dw[d][o] *= sc;
         }
     }
-    uint32_t ent[3], root[3], N[3][3];
-    bool in[3];
-#pragma unroll
-    for (int ox = 0; ox < 3; ++ox) {
-        const int o[3] = {ox, oy, oz};
-        in[ox] = ok;
-#pragma unroll
-        for (int d = 0; d < 3; ++d) {
-            int32_t c = (int32_t)(I[d] >> sh) + o[d] - 1;
-            if (PER) c &= M - 1;
-            else in[ox] = in[ox] && c >= 0 && c < M;
-            N[ox][d] = ((uint32_t)c << sh) | half;
-        }
-        if (!in[ox]) N[ox][0] = N[ox][1] = N[ox][2] = 0u;
-        root[ox] = interleave3(N[ox][0] >> rsh, N[ox][1] >> rsh, N[ox][2] >> rsh);
-        ent[ox] = ld_table(tv, root[ox]);
-    }
-    uint32_t sub[3];
-#pragma unroll
-    for (int ox = 0; ox < 3; ++ox) sub[ox] = ld_table(tv, step1_index(tv, ent[ox], N[ox][0], N[ox][1], N[ox][2]));
-#pragma unroll
-    for (int ox = 0; ox < 3; ++ox) {
-        if (ent[ox] & kSplit) ent[ox] = sub[ox];
-        if (ent[ox] & kSplit) ent[ox] = descend_from_level2(tv, ent[ox], N[ox][0], N[ox][1], N[ox][2]);
-    }
+    NodeRow nr;
+    node_row<PER>(tv, ln, I, l, ok, nr);
+    const uint32_t (&ent)[3] = nr.ent, (&root)[3] = nr.root;
+    const bool (&in)[3] = nr.in;
     // a lane's own row of weights, picked without indexing registers by lane
     const T wy = oy == 0 ? w[1][0] : oy == 1 ? w[1][1] : w[1][2];
     const T wz = oz == 0 ? w[2][0] : oz == 1 ? w[2][1] : w[2][2];
