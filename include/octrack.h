@@ -48,6 +48,9 @@
  *     the next such call (at most four buffers and 1 GiB, for one call each
  *     at a time, freed with the tree).  Where there is none to be had, and in
  *     calls that are captured in a graph, the points are taken as they are.
+ *   - Memory of destroyed trees and of builds is kept for the trees built
+ *     next on its device: at most six blocks and 256 MiB in the process,
+ *     given back when an allocation for a build fails.
  *   - Host ids (`ids` arguments marked "input"): the host leaf of every point
  *     as ot_locate returns it (Algorithm 1's host_cell_id, which Sec. 3.2
  *     makes the prerequisite of interpolation and spreading).  When given,

@@ -368,6 +368,7 @@ struct ot_tree {
     uint8_t *levels;     // levels in sorted order
     uint32_t *table;     // descent table (root + pools)
     int64_t table_entries;
+    size_t block_bytes[2];   // of the blocks that keys (with levels) and table start
     ot::TreeView view;
     // working memory kept for plain calls (scratch_take), under its lock
     mutable std::mutex scratch_lock;

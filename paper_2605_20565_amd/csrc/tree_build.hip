@@ -10,7 +10,9 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cstddef>
 #include <cstring>
+#include <mutex>
 #include <vector>
 
 #include "ot_common.h"
@@ -323,15 +325,15 @@ __global__ void k_validate(const uint64_t *__restrict__ keys, const uint8_t *__r
 
 // -- descent table ------------------------------------------------------------
 // Number of split cells at each table level t (cells of level lev[t] covered
-// by finer leaves): counted at the first leaf inside each such cell.
+// by finer leaves): counted at the first leaf inside each such cell.  Few
+// workgroups: each ends in an atomic per level on the same words.
 __global__ void k_count_splits(const uint64_t *__restrict__ keys, const uint8_t *__restrict__ lv, int64_t n,
                                TreeView tv, unsigned long long *__restrict__ counts)
 {
     __shared__ unsigned sc[kMaxTabLevels];
     if (threadIdx.x < kMaxTabLevels) sc[threadIdx.x] = 0;
     __syncthreads();
-    int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (j < n) {
+    for (int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; j < n; j += (int64_t)gridDim.x * blockDim.x) {
         const uint64_t k = keys[j];
         const int l = lv[j];
         for (int t = 0; t + 1 < tv.nlev; ++t) {
@@ -436,23 +438,101 @@ __global__ void k_count_value(const uint32_t *__restrict__ p, int64_t n, uint32_
 
 inline unsigned nblk(int64_t n, int b = 256) { return (unsigned)((n + b - 1) / b); }
 
-struct DevBuf {
+// Memory of trees that are gone, for the trees built next: freeing a used
+// buffer of some 20 MB costs the host 250 us or more (of the 2.4 ms in which a
+// tree of 2.7 M leaves was built and destroyed, 1.4 ms went to hipFree).  At
+// most kKeptBlocks blocks and kKeptBytes are kept, the oldest are freed first,
+// and all of a device's are given back when an allocation on it fails.  Blocks
+// come here only when no work on them is left, so any stream may have them next.
+constexpr size_t kKeptBlocks = 6, kKeptBytes = size_t(256) << 20;
+struct Block {
     void *p = nullptr;
-    ~DevBuf() { if (p) (void)hipFree(p); }
-    void *release() { void *q = p; p = nullptr; return q; }
+    size_t bytes = 0;
+    int device = 0;
 };
+// (a plain array: nothing here throws, and trees may be destroyed after the
+// destructors of static objects)
+std::mutex g_kept_lock;
+Block g_kept[kKeptBlocks];   // oldest first
+size_t g_n_kept = 0;
 
-int dalloc(DevBuf &b, size_t bytes)
+Block kept_remove(size_t i)
 {
-    if (bytes == 0) bytes = 16;
-    hipError_t e = hipMalloc(&b.p, bytes);
-    if (e != hipSuccess) {
-        b.p = nullptr;
+    const Block b = g_kept[i];
+    for (--g_n_kept; i < g_n_kept; ++i) g_kept[i] = g_kept[i + 1];
+    return b;
+}
+
+// A block of at least `bytes` on the current device; p = null: none.
+Block block_take(size_t bytes)
+{
+    Block b;
+    b.bytes = (bytes + 0xFFFF) & ~size_t(0xFFFF);
+    (void)hipGetDevice(&b.device);
+    std::lock_guard<std::mutex> lock(g_kept_lock);
+    size_t best = kKeptBlocks;
+    for (size_t i = 0; i < g_n_kept; ++i) {
+        const Block &c = g_kept[i];
+        // not more than twice what is asked for
+        if (c.device == b.device && c.bytes >= b.bytes && c.bytes / 2 <= b.bytes &&
+            (best == kKeptBlocks || c.bytes < g_kept[best].bytes))
+            best = i;
+    }
+    if (best < kKeptBlocks) return kept_remove(best);
+    if (hipMalloc(&b.p, b.bytes) == hipSuccess) return b;
+    (void)hipGetLastError();
+    for (size_t i = g_n_kept; i-- > 0;)
+        if (g_kept[i].device == b.device) (void)hipFree(kept_remove(i).p);
+    if (hipMalloc(&b.p, b.bytes) != hipSuccess) {
         (void)hipGetLastError();
+        b.p = nullptr;
+    }
+    return b;
+}
+
+void block_give(const Block &b)
+{
+    if (!b.p) return;
+    std::lock_guard<std::mutex> lock(g_kept_lock);
+    size_t kept = b.bytes;
+    for (size_t i = 0; i < g_n_kept; ++i) kept += g_kept[i].bytes;
+    while (g_n_kept && (kept > kKeptBytes || g_n_kept == kKeptBlocks)) {
+        const Block old = kept_remove(0);
+        kept -= old.bytes;
+        (void)hipFree(old.p);
+    }
+    if (kept > kKeptBytes) (void)hipFree(b.p);
+    else g_kept[g_n_kept++] = b;
+}
+
+// A build's block: given back at the end, when the build's work on it is done.
+struct BuildBlock {
+    Block b;
+    hipStream_t s;
+    explicit BuildBlock(hipStream_t st) : s(st) {}
+    BuildBlock(const BuildBlock &) = delete;
+    BuildBlock &operator=(const BuildBlock &) = delete;
+    ~BuildBlock()
+    {
+        if (!b.p) return;
+        if (hipStreamSynchronize(s) == hipSuccess) block_give(b);
+        else (void)hipFree(b.p);
+    }
+    int take(size_t bytes)
+    {
+        b = block_take(bytes);
+        if (b.p) return OT_OK;
         return fail(OT_ERR_OOM, "device allocation of " + std::to_string(bytes) + " bytes failed");
     }
-    return OT_OK;
-}
+    Block release()
+    {
+        const Block r = b;
+        b.p = nullptr;
+        return r;
+    }
+};
+
+size_t align256(int64_t b) { return (size_t)((b + 255) & ~int64_t(255)); }
 
 }  // namespace
 
@@ -627,19 +707,30 @@ extern "C" int ot_build_tree(const uint64_t *keys, const uint8_t *levels, int64_
     hipStream_t s = (hipStream_t)stream;
     int rc;
 
-    DevBuf ka, kb, va, vb, lvs, scratch;
-    if ((rc = dalloc(ka, n * 8)) || (rc = dalloc(kb, n * 8)) || (rc = dalloc(va, n * 4)) || (rc = dalloc(vb, n * 4)) ||
-        (rc = dalloc(lvs, n)) || (rc = dalloc(scratch, 256)))
+    // the tree's own block: sorted keys and levels; the build's: the other key
+    // buffer (later the split flags and ids), two position buffers and scratch
+    BuildBlock own(s), tmp(s);
+    const size_t nk = align256(8 * n), nv = align256(4 * n);
+    if ((rc = own.take(nk + align256(n))) ||
+        (rc = tmp.take(2 * nv + 2 * nv + align256(radix_ws_bytes(n)) + align256(4 * scan_tmp_words(n)) + 256)))
         return rc;
+    uint64_t *keys_own = (uint64_t *)own.b.p;
+    uint8_t *lvs = (uint8_t *)own.b.p + nk;
+    char *q = (char *)tmp.b.p;
+    uint32_t *flags = (uint32_t *)q, *ids = (uint32_t *)(q + nv);
+    uint64_t *keys_tmp = (uint64_t *)q;   // 8n bytes fit in 2 nv
+    int32_t *va = (int32_t *)(q + 2 * nv), *vb = (int32_t *)(q + 3 * nv);
+    void *sws = q + 4 * nv;
+    uint32_t *stmp = (uint32_t *)((char *)sws + align256(radix_ws_bytes(n)));
+    void *scratch = (char *)stmp + align256(4 * scan_tmp_words(n));
+    // Keys of a valid tree use 3L bits; sort on those (others fail validation).
+    // The last pass writes the tree's own buffer.
+    const bool odd = ((3 * L + kRadixBits - 1) / kRadixBits) % 2 != 0 || L == 0;
     uint64_t *ks;
     int32_t *perm;
-    DevBuf sws;
-    if ((rc = dalloc(sws, radix_ws_bytes(n)))) return rc;
-    // Keys of a valid tree use 3L bits; sort on those (others fail validation).
-    radix_sort_pairs(keys, (uint64_t *)ka.p, (int32_t *)va.p, (uint64_t *)kb.p, (int32_t *)vb.p, n, 3 * L, sws.p,
-                     &ks, &perm, s);
+    radix_sort_pairs(keys, odd ? keys_own : keys_tmp, va, odd ? keys_tmp : keys_own, vb, n, 3 * L, sws, &ks, &perm, s);
     OT_HIP(hipGetLastError());
-    hipLaunchKernelGGL(k_gather_levels, dim3(nblk(n)), dim3(256), 0, s, levels, perm, (uint8_t *)lvs.p, n);
+    hipLaunchKernelGGL(k_gather_levels, dim3(nblk(n)), dim3(256), 0, s, levels, perm, lvs, n);
 
     // Table layout: root level r = min(l_min, 8), then steps of <= 3 levels.
     TreeView tv{};
@@ -652,11 +743,11 @@ extern "C" int ot_build_tree(const uint64_t *keys, const uint8_t *levels, int64_
         tv.nlev++;
     }
 
-    unsigned *err = (unsigned *)scratch.p;
-    unsigned long long *cnt = (unsigned long long *)((char *)scratch.p + 64);
-    hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, s, (uint32_t *)scratch.p, (int64_t)64, 0u);
-    hipLaunchKernelGGL(k_validate, dim3(nblk(n)), dim3(256), 0, s, ks, (const uint8_t *)lvs.p, n, l_min, L, err);
-    hipLaunchKernelGGL(k_count_splits, dim3(nblk(n)), dim3(256), 0, s, ks, (const uint8_t *)lvs.p, n, tv, cnt);
+    unsigned *err = (unsigned *)scratch;
+    unsigned long long *cnt = (unsigned long long *)((char *)scratch + 64);
+    hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, s, (uint32_t *)scratch, (int64_t)64, 0u);
+    hipLaunchKernelGGL(k_validate, dim3(nblk(n)), dim3(256), 0, s, ks, (const uint8_t *)lvs, n, l_min, L, err);
+    hipLaunchKernelGGL(k_count_splits, dim3(std::min(nblk(n), 512u)), dim3(256), 0, s, ks, (const uint8_t *)lvs, n, tv, cnt);
     OT_HIP(hipGetLastError());
     unsigned herr = 0;
     unsigned long long hcnt[kMaxTabLevels] = {0};
@@ -684,11 +775,10 @@ extern "C" int ot_build_tree(const uint64_t *keys, const uint8_t *levels, int64_
     const int64_t sum_cells = tv.lev[0] >= 1 ? (int64_t(1) << (3 * (tv.lev[0] - 1))) : 0;
     // and the anchors of the sub-tables, in the order of their block keys
     const int64_t anc_at = (sum_at + sum_cells + 1) & ~int64_t(1);
-    DevBuf table, flags, ids, stmp;
-    if ((rc = dalloc(table, (anc_at + 2 * n_sub) * 4)) || (rc = dalloc(flags, n * 4)) || (rc = dalloc(ids, n * 4)) ||
-        (rc = dalloc(stmp, scan_tmp_words(n) * 4)))
-        return rc;
-    hipLaunchKernelGGL(k_fill_u32, dim3(2048), dim3(256), 0, s, (uint32_t *)table.p, entries, 0xFFFFFFFFu);
+    BuildBlock table_block(s);
+    if ((rc = table_block.take((size_t)(anc_at + 2 * n_sub) * 4))) return rc;
+    uint32_t *table = (uint32_t *)table_block.b.p;
+    hipLaunchKernelGGL(k_fill_u32, dim3(2048), dim3(256), 0, s, table, entries, 0xFFFFFFFFu);
     // block keys: the root cubes, then the sub-tables level by level
     int64_t heads[2 * kMaxTabLevels] = {0};
     std::memcpy(heads, tv.off, sizeof(tv.off));
@@ -701,22 +791,22 @@ extern "C" int ot_build_tree(const uint64_t *keys, const uint8_t *levels, int64_
         blocks += (int64_t)hcnt[t - 1];
     }
     tv.nblk = (int32_t)blocks;   // at most 8^5 + n_leaves / 8
-    OT_HIP(hipMemcpyAsync((uint32_t *)table.p + off_at, heads, sizeof(heads), hipMemcpyHostToDevice, s));
+    OT_HIP(hipMemcpyAsync(table + off_at, heads, sizeof(heads), hipMemcpyHostToDevice, s));
     for (int t = 0; t < tv.nlev; ++t) {
         if (t + 1 < tv.nlev) {
-            hipLaunchKernelGGL(k_split_flags, dim3(nblk(n)), dim3(256), 0, s, ks, (const uint8_t *)lvs.p, n, L,
-                               tv.lev[t], (uint32_t *)flags.p);
-            exclusive_scan((uint32_t *)flags.p, (uint32_t *)ids.p, n, (uint32_t *)stmp.p, s);
+            hipLaunchKernelGGL(k_split_flags, dim3(nblk(n)), dim3(256), 0, s, ks, (const uint8_t *)lvs, n, L,
+                               tv.lev[t], flags);
+            exclusive_scan(flags, ids, n, stmp, s);
         }
-        hipLaunchKernelGGL(k_write_level, dim3(nblk(n)), dim3(256), 0, s, ks, (const uint8_t *)lvs.p, n, tv,
-                           (uint32_t *)table.p, t, (const uint32_t *)ids.p,
-                           (uint64_t *)((uint32_t *)table.p + anc_at) + (t + 1 < tv.nlev ? bb[t + 1] - tv.blk1 : 0));
+        hipLaunchKernelGGL(k_write_level, dim3(nblk(n)), dim3(256), 0, s, ks, (const uint8_t *)lvs, n, tv,
+                           table, t, (const uint32_t *)ids,
+                           (uint64_t *)(table + anc_at) + (t + 1 < tv.nlev ? bb[t + 1] - tv.blk1 : 0));
     }
     if (sum_cells)
-        hipLaunchKernelGGL(k_root_summary, dim3(nblk(sum_cells)), dim3(256), 0, s, (const uint32_t *)table.p, sum_cells,
-                           tv.lev[0], (uint32_t *)table.p + sum_at);
-    hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, s, (uint32_t *)scratch.p, (int64_t)1, 0u);
-    hipLaunchKernelGGL(k_count_value, dim3(1024), dim3(256), 0, s, (const uint32_t *)table.p, entries, 0xFFFFFFFFu, err);
+        hipLaunchKernelGGL(k_root_summary, dim3(nblk(sum_cells)), dim3(256), 0, s, (const uint32_t *)table, sum_cells,
+                           tv.lev[0], table + sum_at);
+    hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, s, (uint32_t *)scratch, (int64_t)1, 0u);
+    hipLaunchKernelGGL(k_count_value, dim3(1024), dim3(256), 0, s, (const uint32_t *)table, entries, 0xFFFFFFFFu, err);
     OT_HIP(hipGetLastError());
     OT_HIP(hipMemcpyAsync(&herr, err, sizeof(herr), hipMemcpyDeviceToHost, s));
     if (perm_out) OT_HIP(hipMemcpyAsync(perm_out, perm, n * 4, hipMemcpyDeviceToDevice, s));
@@ -732,11 +822,13 @@ extern "C" int ot_build_tree(const uint64_t *keys, const uint8_t *levels, int64_
     tr->l_max = L;
     tr->periodic = tv.periodic;
     tr->n_leaves = n;
-    // keep the sorted keys in whichever buffer holds them
-    if (ks == (uint64_t *)ka.p) tr->keys = (uint64_t *)ka.release();
-    else tr->keys = (uint64_t *)kb.release();
-    tr->levels = (uint8_t *)lvs.release();
-    tr->table = (uint32_t *)table.release();
+    tr->block_bytes[0] = own.b.bytes;
+    tr->block_bytes[1] = table_block.b.bytes;
+    (void)own.release();
+    (void)table_block.release();
+    tr->keys = keys_own;
+    tr->levels = lvs;
+    tr->table = table;
     tr->table_entries = entries;
     tv.table = tr->table;
     tv.pool_off = (const int64_t *)(tr->table + off_at);
@@ -756,14 +848,18 @@ extern "C" int ot_destroy_tree(ot_tree *t)
     int cur = 0;
     (void)hipGetDevice(&cur);
     (void)hipSetDevice(t->device);
-    (void)hipDeviceSynchronize();
+    const bool idle = hipDeviceSynchronize() == hipSuccess;
     for (ScratchSlot &c : t->scratch) {
         if (c.p) (void)hipFree(c.p);
         if (c.done) (void)hipEventDestroy(c.done);
     }
-    (void)hipFree(t->keys);
-    (void)hipFree(t->levels);
-    (void)hipFree(t->table);
+    if (idle) {
+        block_give(Block{t->keys, t->block_bytes[0], t->device});
+        block_give(Block{t->table, t->block_bytes[1], t->device});
+    } else {
+        (void)hipFree(t->keys);
+        (void)hipFree(t->table);
+    }
     (void)hipSetDevice(cur);
     delete t;
     return OT_OK;
