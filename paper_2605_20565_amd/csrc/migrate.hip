@@ -23,6 +23,7 @@ namespace {
 constexpr int kThreads = 256;
 constexpr int kMaxOwners = 4096;
 
+template <int THREADS>
 __device__ __forceinline__ void block_count_to(unsigned long long v, unsigned long long *sh, unsigned long long *out)
 {
 #pragma unroll
@@ -30,21 +31,21 @@ __device__ __forceinline__ void block_count_to(unsigned long long v, unsigned lo
     if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
     __syncthreads();
     if (threadIdx.x == 0) {
-        for (int w = 1; w < kThreads / 64; ++w) v += sh[w];
+        for (int w = 1; w < THREADS / 64; ++w) v += sh[w];
         if (v) atomicAdd(out, v);
     }
 }
 
-// Cells of a thread's ITEMS points of one tile (ITEMS * kThreads points from
+// Cells of a thread's ITEMS points of one tile (ITEMS * THREADS points from
 // base), all loaded before any is used, at clamped indices.
-template <typename T, int ITEMS>
+template <typename T, int ITEMS, int THREADS>
 __device__ __forceinline__ void tile_cells(const TreeView &tv, const T *__restrict__ pos, int64_t n, int64_t base,
                                            uint32_t (&I)[ITEMS][3], bool (&ok)[ITEMS])
 {
     T X[ITEMS][3];
 #pragma unroll
     for (int j = 0; j < ITEMS; ++j) {
-        const int64_t k = base + j * kThreads + threadIdx.x;
+        const int64_t k = base + j * THREADS + threadIdx.x;
         const int64_t kc = k < n ? k : n - 1;
 #pragma unroll
         for (int d = 0; d < 3; ++d) X[j][d] = pos[3 * kc + d];
@@ -57,26 +58,26 @@ __device__ __forceinline__ void tile_cells(const TreeView &tv, const T *__restri
 // ITEMS points per thread whose table loads are in flight together, and adds
 // its count of moved points once: one add per 256 points had put 39,000 adds
 // on one address (10 ns each on this target) and the kernel at 478 us for 10^7
-// points; relocation with its count and find_owner together 615 -> 191 us.
-template <typename T, int ITEMS>
-__global__ __launch_bounds__(kThreads) void k_relocate(TreeView tv, const T *__restrict__ pos, int64_t n,
+// points; it takes 79 now.
+template <typename T, int ITEMS, int THREADS>
+__global__ __launch_bounds__(THREADS) void k_relocate(TreeView tv, const T *__restrict__ pos, int64_t n,
                                                        int32_t *__restrict__ ids,
                                                        unsigned long long *__restrict__ moved)
 {
-    __shared__ unsigned long long sh[kThreads / 64];
+    __shared__ unsigned long long sh[THREADS / 64];
     const int rsh = tv.L - tv.lev[0];
     unsigned long long changed = 0;
-    for (int64_t base = blockIdx.x * (int64_t)(kThreads * ITEMS); base < n;
-         base += gridDim.x * (int64_t)(kThreads * ITEMS)) {
+    for (int64_t base = blockIdx.x * (int64_t)(THREADS * ITEMS); base < n;
+         base += gridDim.x * (int64_t)(THREADS * ITEMS)) {
         uint32_t I[ITEMS][3], root[ITEMS], e[ITEMS];
         int32_t prev[ITEMS];
         bool ok[ITEMS];
 #pragma unroll
         for (int j = 0; j < ITEMS; ++j) {
-            const int64_t k = base + j * kThreads + threadIdx.x;
+            const int64_t k = base + j * THREADS + threadIdx.x;
             prev[j] = ids[k < n ? k : n - 1];
         }
-        tile_cells<T, ITEMS>(tv, pos, n, base, I, ok);
+        tile_cells<T, ITEMS, THREADS>(tv, pos, n, base, I, ok);
         // root summary, the root where it has no answer, then deeper levels
 #pragma unroll
         for (int j = 0; j < ITEMS; ++j) {
@@ -90,7 +91,7 @@ __global__ __launch_bounds__(kThreads) void k_relocate(TreeView tv, const T *__r
         }
 #pragma unroll
         for (int j = 0; j < ITEMS; ++j) {
-            const int64_t k = base + j * kThreads + threadIdx.x;
+            const int64_t k = base + j * THREADS + threadIdx.x;
             const int32_t id = ok[j] ? (int32_t)(e[j] & kIdMask) : -1;
             if (k < n) {
                 ids[k] = id;
@@ -98,7 +99,7 @@ __global__ __launch_bounds__(kThreads) void k_relocate(TreeView tv, const T *__r
             }
         }
     }
-    if (moved) block_count_to(changed, sh, moved);
+    if (moved) block_count_to<THREADS>(changed, sh, moved);
 }
 
 __global__ void k_leaf_splitters(const uint64_t *__restrict__ keys, int64_t n_leaves, int P, int L,
@@ -113,31 +114,33 @@ __global__ void k_leaf_splitters(const uint64_t *__restrict__ keys, int64_t n_le
 
 // Splitters staged in LDS.  A workgroup walks over tiles of ITEMS points per
 // thread, loaded together (one after another they had taken 112 us for 10^7
-// points and 8 owners), and adds its counts to device memory once.
+// points and 8 owners), and adds its counts to device memory once.  LDS is
+// sized by the owners: at 48 KB for the most there can be, three of a CU's four
+// workgroups fitted, and the last quarter of the walkers ran alone (80 us).
 // Counts: for up to kBallotOwners owners every wave counts each owner with
 // one ballot (no same-address atomics), else LDS atomics.
 constexpr int kBallotOwners = 32;
 
-template <typename T, int ITEMS>
-__global__ __launch_bounds__(kThreads) void k_find_owner(TreeView tv, const int64_t *__restrict__ split, int P,
+template <typename T, int ITEMS, int THREADS>
+__global__ __launch_bounds__(THREADS) void k_find_owner(TreeView tv, const int64_t *__restrict__ split, int P,
                                                          const T *__restrict__ pos, int64_t n,
                                                          int32_t *__restrict__ owner,
                                                          unsigned long long *__restrict__ counts)
 {
-    __shared__ int64_t s_split[kMaxOwners + 1];
-    __shared__ unsigned int hist[kMaxOwners];
-    for (int i = threadIdx.x; i <= P; i += kThreads) s_split[i] = split[i];
-    for (int i = threadIdx.x; i < P; i += kThreads) hist[i] = 0u;
+    extern __shared__ int64_t s_split[];   // P + 1 splitters, then P counts
+    unsigned int *hist = reinterpret_cast<unsigned int *>(s_split + P + 1);
+    for (int i = threadIdx.x; i <= P; i += THREADS) s_split[i] = split[i];
+    for (int i = threadIdx.x; i < P; i += THREADS) hist[i] = 0u;
     __syncthreads();
-    for (int64_t base = blockIdx.x * (int64_t)(kThreads * ITEMS); base < n;
-         base += gridDim.x * (int64_t)(kThreads * ITEMS)) {
+    for (int64_t base = blockIdx.x * (int64_t)(THREADS * ITEMS); base < n;
+         base += gridDim.x * (int64_t)(THREADS * ITEMS)) {
         uint32_t I[ITEMS][3];
         bool ok[ITEMS];
         int32_t o[ITEMS];
-        tile_cells<T, ITEMS>(tv, pos, n, base, I, ok);
+        tile_cells<T, ITEMS, THREADS>(tv, pos, n, base, I, ok);
 #pragma unroll
         for (int j = 0; j < ITEMS; ++j) {
-            const int64_t k = base + j * kThreads + threadIdx.x;
+            const int64_t k = base + j * THREADS + threadIdx.x;
             const int64_t key = (int64_t)(split3_21(I[j][0]) | (split3_21(I[j][1]) << 1) | (split3_21(I[j][2]) << 2));
             // largest r in [0, P) with split[r] <= key
             int lo = 0, hi = P;
@@ -166,25 +169,47 @@ __global__ __launch_bounds__(kThreads) void k_find_owner(TreeView tv, const int6
     }
     if (counts) {
         __syncthreads();
-        for (int i = threadIdx.x; i < P; i += kThreads)
+        for (int i = threadIdx.x; i < P; i += THREADS)
             if (hist[i]) atomicAdd(&counts[i], (unsigned long long)hist[i]);
     }
 }
 
 // Launch of the two kernels above: kWide points per thread once that still
-// gives every CU a workgroup, and at most kWalkers workgroups, so that the
-// shared counters see few adds.
-constexpr int kWide = 4;
-constexpr int kWalkers = 1024;
-struct Walk {
-    bool wide;
-    unsigned grid;
-};
-Walk walk(int64_t n)
+// gives every CU a workgroup.  find_owner's workgroups end in an add per owner
+// to the same few words, so its large calls take few of them, of kManyThreads
+// threads: 10^7 points and 8 owners 52 us, and 57 in workgroups of 256 (64
+// owners 53 and 63).  Relocation, with one add each, takes 79 us either way,
+// and with 2, 4 or 8 points per thread.
+constexpr int kWide = 4, kWalkers = 1024;
+constexpr int kManyThreads = 1024, kManyWalkers = 512;
+
+unsigned walkers(int64_t n, int64_t per) { return (unsigned)std::min<int64_t>((n + per - 1) / per, kWalkers); }
+
+template <typename T>
+void relocate(const TreeView &tv, const T *pos, int64_t n, int32_t *ids, unsigned long long *moved, hipStream_t s)
 {
-    const bool wide = n >= (int64_t)kThreads * kWide * 256;
-    const int64_t per = (int64_t)kThreads * (wide ? kWide : 1);
-    return {wide, (unsigned)std::min<int64_t>((n + per - 1) / per, kWalkers)};
+    if (n >= (int64_t)kThreads * kWide * 256)
+        hipLaunchKernelGGL((k_relocate<T, kWide, kThreads>), dim3(walkers(n, kThreads * kWide)), dim3(kThreads), 0, s,
+                           tv, pos, n, ids, moved);
+    else
+        hipLaunchKernelGGL((k_relocate<T, 1, kThreads>), dim3(walkers(n, kThreads)), dim3(kThreads), 0, s, tv, pos, n,
+                           ids, moved);
+}
+
+template <typename T>
+void find_owner(const TreeView &tv, const int64_t *split, int P, const T *pos, int64_t n, int32_t *owner,
+                unsigned long long *counts, hipStream_t s)
+{
+    const size_t lds = sizeof(int64_t) * ((size_t)P + 1) + sizeof(unsigned) * (size_t)P;   // 48 KB at most
+    if (n >= (int64_t)kManyThreads * kWide * 256)
+        hipLaunchKernelGGL((k_find_owner<T, kWide, kManyThreads>), dim3(kManyWalkers), dim3(kManyThreads), lds, s, tv,
+                           split, P, pos, n, owner, counts);
+    else if (n >= (int64_t)kThreads * kWide * 256)
+        hipLaunchKernelGGL((k_find_owner<T, kWide, kThreads>), dim3(walkers(n, kThreads * kWide)), dim3(kThreads), lds,
+                           s, tv, split, P, pos, n, owner, counts);
+    else
+        hipLaunchKernelGGL((k_find_owner<T, 1, kThreads>), dim3(walkers(n, kThreads)), dim3(kThreads), lds, s, tv, split,
+                           P, pos, n, owner, counts);
 }
 
 }  // namespace
@@ -203,16 +228,8 @@ extern "C" int ot_relocate(const ot_tree *t, const void *pos, int32_t dtype, int
     unsigned long long *mv = (unsigned long long *)moved;
     if (mv) hipLaunchKernelGGL(k_fill<unsigned long long>, dim3(1), dim3(64), 0, s, mv, (int64_t)1, 0ull);
     if (n > 0) {
-        const Walk w = walk(n);
-        if (dtype == OT_F32) {
-            const float *x = (const float *)pos;
-            if (w.wide) hipLaunchKernelGGL((k_relocate<float, kWide>), dim3(w.grid), dim3(kThreads), 0, s, t->view, x, n, ids, mv);
-            else hipLaunchKernelGGL((k_relocate<float, 1>), dim3(w.grid), dim3(kThreads), 0, s, t->view, x, n, ids, mv);
-        } else {
-            const double *x = (const double *)pos;
-            if (w.wide) hipLaunchKernelGGL((k_relocate<double, kWide>), dim3(w.grid), dim3(kThreads), 0, s, t->view, x, n, ids, mv);
-            else hipLaunchKernelGGL((k_relocate<double, 1>), dim3(w.grid), dim3(kThreads), 0, s, t->view, x, n, ids, mv);
-        }
+        if (dtype == OT_F32) relocate<float>(t->view, (const float *)pos, n, ids, mv, s);
+        else relocate<double>(t->view, (const double *)pos, n, ids, mv, s);
     }
     OT_HIP(hipGetLastError());
     return OT_OK;
@@ -243,18 +260,8 @@ extern "C" int ot_find_owner(const int64_t *splitters, int32_t P, int32_t l_max,
     tv.L = l_max;
     tv.periodic = periodic ? 1 : 0;
     if (n > 0) {
-        const Walk w = walk(n);
-#define OT_OWNER(TT, ITEMS)                                                                                        \
-    hipLaunchKernelGGL((k_find_owner<TT, ITEMS>), dim3(w.grid), dim3(kThreads), 0, s, tv, splitters, (int)P,        \
-                       (const TT *)pos, n, owner, cnt)
-        if (dtype == OT_F32) {
-            if (w.wide) OT_OWNER(float, kWide);
-            else OT_OWNER(float, 1);
-        } else {
-            if (w.wide) OT_OWNER(double, kWide);
-            else OT_OWNER(double, 1);
-        }
-#undef OT_OWNER
+        if (dtype == OT_F32) find_owner<float>(tv, splitters, (int)P, (const float *)pos, n, owner, cnt, s);
+        else find_owner<double>(tv, splitters, (int)P, (const double *)pos, n, owner, cnt, s);
     }
     OT_HIP(hipGetLastError());
     return OT_OK;
