@@ -118,7 +118,7 @@ int sorted_pass(const ot_tree *t, int ops, const void *field, const void *force,
     p.grad_plan = (ops & kOpGrad) != 0;
     p.n_points = n;
     p.sort_points = true;
-    p.fxws = work;
+    p.fxws = mode == OT_SPREAD_FIXED ? work : nullptr;
     p.use_blocks = blk_rule(t, n, ops);
     p.use_nodes = !p.use_blocks && node_rule(t, n, ops);
     p.sort_key = p.use_blocks ? point_sort_by_block(t->view.nblk) : point_sort_by_host(t->n_leaves);
@@ -216,11 +216,21 @@ extern "C" int ot_batch_plan_create(const ot_tree *tree, const int64_t *offsets,
     p->sort_points = sort_points;
     p->ops_all = ops_all;
     p->grad_plan = (ops_union & kOpGrad) != 0;
-    p->use_small = sort_points && !(tuning->flags & OT_TUNE_HOST_MAJOR) && small_rule(p->n_points, ops_all);
+    const bool f32_sums = dtype == OT_F32 && mode == OT_SPREAD_ATOMIC && (ops_all & kOpSpread);
+    p->use_small = sort_points && !(tuning->flags & OT_TUNE_HOST_MAJOR) && !f32_sums &&
+                   small_rule(p->n_points, ops_all);
     if (sort_points && p->n_points > 0 && !p->use_small) {
         const int64_t n = p->n_points;
         p->use_blocks = !(tuning->flags & OT_TUNE_HOST_MAJOR) && blk_rule(tree, n, ops_all);
         p->use_nodes = !p->use_blocks && !(tuning->flags & OT_TUNE_HOST_MAJOR) && node_rule(tree, n, ops_all);
+        if (f32_sums && (p->use_blocks || p->use_nodes)) {
+            p->wide = hipMalloc(&p->fxws, (size_t)spread_ws_bytes(tree->n_leaves)) == hipSuccess;
+            if (!p->wide) {   // no room for the sums: tiles of points sorted by host
+                (void)hipGetLastError();
+                p->fxws = nullptr;
+                p->use_blocks = p->use_nodes = false;
+            }
+        }
         p->sort_key = p->use_blocks ? point_sort_by_block(tree->view.nblk) : point_sort_by_host(tree->n_leaves);
         const size_t rec = ((ops_all & (kOpSpread | kOpGrad)) ? 6 : 3) * (size_t)n * (dtype == OT_F32 ? 4 : 8);
         hipError_t e = hipSuccess;

@@ -51,7 +51,7 @@ __global__ __launch_bounds__(512) void k_batch(TreeView tv, const int64_t *__res
     __shared__ unsigned s_tile;
     // the fixed-point state exists only for plans that spread (fx null otherwise)
     const double scale = (MODE == kModeFixed && fx.st) ? fx_scale<T>(fx) : 0.0;
-    LdsSink<T, MODE, S> sink{keys, vals, fout, facc, scale};
+    LdsSink<T, MODE, S> sink{keys, vals, fout, fixed_acc<MODE>(facc), scale};
     sink.clear();
     // The next tile is claimed before the flush, so the queue atomic's round
     // trip overlaps it.  Every thread reads s_tile before the flush's first
@@ -118,7 +118,7 @@ int enqueue(ot_batch_plan *p, const void *field, const void *force, const void *
     // windows, [2]: how many windows were handed over, [3..7]: the block pass's
     int rc;
     const bool spread = (p->ops_union & kOpSpread) != 0;
-    const FxWs ws = fx_ws(p->fxws);
+    const FxWs ws = fx_ws(p->fxws);   // ATOMIC: null, or the FP64 sums of a wide run
     const FxRef fx{ws.fx, n};
     const uint64_t *kv = nullptr;
     int rs = 3;
@@ -130,7 +130,7 @@ int enqueue(ot_batch_plan *p, const void *field, const void *force, const void *
         // takes max |F| on the way
         const bool carry_force = (p->ops_all & (kOpSpread | kOpGrad)) != 0;
         SortZero zero{nullptr, 0, p->counter, kCounters};
-        if (spread && p->mode == OT_SPREAD_FIXED) {
+        if (spread && (p->mode == OT_SPREAD_FIXED || p->wide)) {
             zero.p = (uint32_t *)ws.fx;
             zero.words = (kFxHeader + t->n_leaves * 3 * 8) / 4;
         } else if (spread && !p->accumulate) {
@@ -208,6 +208,7 @@ int enqueue(ot_batch_plan *p, const void *field, const void *force, const void *
                                           (T *)grad, s)))
             return rc;
         if (p->timing) OT_HIP(hipEventRecord(p->ev[1], s));
+        if (p->wide) return wide_epilogue(t, (const double *)ws.acc, p->accumulate, (float *)fout, s);
         return spread ? spread_epilogue(t, ws, p->dtype, p->mode, p->accumulate, fout, n, s) : OT_OK;
     }
 #define OT_KBATCH_S(PERV, GRADV, SV)                                                                               \

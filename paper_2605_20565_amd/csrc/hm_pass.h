@@ -116,7 +116,7 @@ __device__ __forceinline__ void hm_add(Acc (*acc)[3], uint32_t s, const Acc (&a)
     for (int c = 0; c < 3; ++c) {
         Acc v = a[c];
         if constexpr (MODE == kModeFixed) v -= (unsigned long long)cnt * kFxMagicBits;
-        if (s & kHmDirect) global_add<T, MODE>(fout, facc, 3 * (int64_t)(s & ~kHmDirect) + c, v);
+        if (s & kHmDirect) global_add<T, MODE>(fout, fixed_acc<MODE>(facc), 3 * (int64_t)(s & ~kHmDirect) + c, v);
         else atomicAdd(&acc[s][c], v);
     }
 }
@@ -452,9 +452,9 @@ __global__ __launch_bounds__(kHmThreads) void k_hm(TreeView tv, int64_t n, int64
             if (key) {
                 if (kSpread) {
                     const int64_t j = 3 * (int64_t)(key - 1u);
-                    global_add<T, MODE>(fout, facc, j, sh.acc[i][0]);
-                    global_add<T, MODE>(fout, facc, j + 1, sh.acc[i][1]);
-                    global_add<T, MODE>(fout, facc, j + 2, sh.acc[i][2]);
+                    global_add<T, MODE>(fout, fixed_acc<MODE>(facc), j, sh.acc[i][0]);
+                    global_add<T, MODE>(fout, fixed_acc<MODE>(facc), j + 1, sh.acc[i][1]);
+                    global_add<T, MODE>(fout, fixed_acc<MODE>(facc), j + 2, sh.acc[i][2]);
                     sh.acc[i][0] = Acc(0);
                     sh.acc[i][1] = Acc(0);
                     sh.acc[i][2] = Acc(0);

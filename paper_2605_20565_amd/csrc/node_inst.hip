@@ -15,6 +15,7 @@ int dispatch_nodes(int ops, const ot_tree *t, hipStream_t s, int64_t n, const vo
                    const void *force, int32_t *ids, void *vel, void *fout, void *grad, const FxWs &ws,
                    const int32_t *hid)
 {
+    constexpr bool f32_sums = std::is_same<T, float>::value && MODE == kModeAtomic;
     const dim3 g((unsigned)((n + kNodePts - 1) / kNodePts)), b(kNodeThreads);
 #define OT_NODES(OPSV, PERV)                                                                                       \
     hipLaunchKernelGGL((k_nodes<T, OPSV, MODE, PERV>), g, b, 0, s, t->view, n, (const T *)pos, (const T *)field,    \
@@ -22,9 +23,12 @@ int dispatch_nodes(int ops, const ot_tree *t, hipStream_t s, int64_t n, const vo
                        (T *)grad, hid)
 #define OT_CASE(OPSV)                                                                                              \
     case OPSV:                                                                                                     \
-        if (t->view.periodic) OT_NODES(OPSV, true);                                                                \
-        else OT_NODES(OPSV, false);                                                                                \
-        break;
+        if constexpr (!f32_sums || !((OPSV) & kOpSpread)) {                                                        \
+            if (t->view.periodic) OT_NODES(OPSV, true);                                                            \
+            else OT_NODES(OPSV, false);                                                                            \
+            break;                                                                                                 \
+        }                                                                                                          \
+        return fail(OT_ERR_INVALID, "sums in FP32 do not take this pass");
     switch (ops) {
         OT_CASE(2) OT_CASE(3) OT_CASE(4) OT_CASE(5) OT_CASE(6) OT_CASE(7)
         OT_CASE(kOpGrad) OT_CASE(kOpGrad | kOpInterp) OT_CASE(kOpGrad | kOpSpread)

@@ -45,7 +45,7 @@ constexpr int kMaxPointsPerThread = 4;
 // markers in order on few leaves are faster there: 100 k 66 against 134 us a
 // call).  A whole fused FP32 fixed-point call on 11 k points: 53.5 -> 25.9 us
 // (three launches instead of five).
-constexpr int64_t kNodesMaxSpread = 65535;
+constexpr int64_t kNodesMaxSpread = 65535;   // sums in FP32 apart (run_pass)
 constexpr int64_t kNodesMaxGather = 16384;
 // Larger sets are sorted first, as a sorted plan does, when the call searches
 // the hosts itself and may allocate: calls that spread from kSortMinSpread
@@ -180,6 +180,26 @@ int spread_epilogue(const ot_tree *t, const FxWs &ws, int dtype, int mode, int a
     return OT_OK;
 }
 
+namespace {
+__global__ void k_wide_finalize(const double *__restrict__ acc, float *__restrict__ out, int64_t n3, int accumulate)
+{
+    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n3; i += (int64_t)gridDim.x * blockDim.x) {
+        const double v = acc[i];
+        if (!accumulate) out[i] = (float)v;
+        else if (v != 0.0) out[i] = (float)((double)out[i] + v);
+    }
+}
+}  // namespace
+
+int wide_epilogue(const ot_tree *t, const double *acc, int accumulate, float *fout, hipStream_t s)
+{
+    const int64_t n3 = t->n_leaves * 3;
+    hipLaunchKernelGGL(k_wide_finalize, dim3((unsigned)std::min<int64_t>((n3 + 255) / 256, 8192)), dim3(256), 0, s, acc,
+                       fout, n3, accumulate);
+    OT_HIP(hipGetLastError());
+    return OT_OK;
+}
+
 FxWs fx_ws(void *work)
 {
     FxWs w;
@@ -285,9 +305,13 @@ int run_pass(const ot_tree *t, int ops, const void *field, const void *force, co
         }
         work = owned;
     }
-    const FxWs ws = fx_ws(work);
+    const FxWs ws = fx_ws(spread && mode == OT_SPREAD_FIXED ? work : nullptr);
+    // Sums in FP32 take the pass with the fewest adds to a leaf: workgroups of
+    // 28 points had made them up to 1.3 times less exact (16 k markers in order:
+    // 1.6e-7 -> 2.1e-7).
+    const bool f32_sums = spread && mode == OT_SPREAD_ATOMIC && dtype == OT_F32;
     if (may_sort && !hid && (ops & ~kOpLocate) && n <= INT32_MAX &&
-        (spread ? n >= kSortMinSpread : n >= kSortMinGather && !(ops & kOpGrad))) {
+        (spread ? n >= (f32_sums ? kSortMinF32Sums : kSortMinSpread) : n >= kSortMinGather && !(ops & kOpGrad))) {
         bool handled;
         rc = sorted_pass(t, ops, field, force, pos, dtype, n, mode, accumulate, ids, vel, fout, grad, work, s, handled);
         if (handled) {
@@ -295,7 +319,7 @@ int run_pass(const ot_tree *t, int ops, const void *field, const void *force, co
             return rc;
         }
     }
-    if (n > 0 && (ops & ~kOpLocate) && n <= (spread ? kNodesMaxSpread : kNodesMaxGather)) {
+    if (n > 0 && (ops & ~kOpLocate) && !f32_sums && n <= (spread ? kNodesMaxSpread : kNodesMaxGather)) {
         rc = dtype == OT_F32 ? nodes_pass<float>(t, ops, field, force, pos, dtype, n, mode, accumulate, ids, vel, fout,
                                                  grad, ws, hid, s)
                              : nodes_pass<double>(t, ops, field, force, pos, dtype, n, mode, accumulate, ids, vel, fout,

@@ -137,9 +137,21 @@ __device__ __forceinline__ void global_add(T *fout, unsigned long long *facc, in
     if constexpr (MODE == kModeFixed)
         __hip_atomic_fetch_add((__attribute__((address_space(1))) unsigned long long *)(facc + j), v, __ATOMIC_RELAXED,
                                __HIP_MEMORY_SCOPE_AGENT);
+    else if (std::is_same<T, float>::value && facc)   // sums in FP64 (ot_batch_plan::wide)
+        __hip_atomic_fetch_add((__attribute__((address_space(1))) double *)((double *)facc + j), (double)v,
+                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     else
         __hip_atomic_fetch_add((__attribute__((address_space(1))) T *)(fout + j), (T)v, __ATOMIC_RELAXED,
                                __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// The accumulators of kernels that wide runs do not use: a null known to the
+// compiler in ATOMIC mode (the check at each add had cost a call of 1,000
+// points 3 us of 38).
+template <int MODE>
+__device__ __forceinline__ unsigned long long *fixed_acc(unsigned long long *facc)
+{
+    return MODE == kModeFixed ? facc : nullptr;
 }
 
 // Straight to device memory with one atomic per component.
@@ -698,6 +710,7 @@ int spread_begin(const ot_tree *t, const FxWs &ws, int dtype, int mode, int accu
 int spread_max(const FxWs &ws, int dtype, int mode, const void *force, int64_t n, hipStream_t s);
 int spread_epilogue(const ot_tree *t, const FxWs &ws, int dtype, int mode, int accumulate, void *fout, int64_t n,
                     hipStream_t s);
+int wide_epilogue(const ot_tree *t, const double *acc, int accumulate, float *fout, hipStream_t s);
 FxWs fx_ws(void *work);
 
 }  // namespace ot

@@ -29,13 +29,13 @@ __global__ __launch_bounds__(512) void k_track(TreeView tv, int64_t n, int64_t t
         __shared__ uint32_t keys[S];
         __shared__ Acc vals[LdsSink<T, MODE, S>::kVals];
         const double scale = MODE == kModeFixed ? fx_scale<T>(fx) : 0.0;
-        LdsSink<T, MODE, S> sink{keys, vals, fout, facc, scale};
+        LdsSink<T, MODE, S> sink{keys, vals, fout, fixed_acc<MODE>(facc), scale};
         sink.clear();
         __syncthreads();
         track_range<T, OPS, PER>(tv, start, end, nullptr, 3, pos, field, force, ids, vel, sink, grad, hid);
         sink.flush();
     } else {
-        DirectSink<T, MODE> sink{fout, facc, 0.0};
+        DirectSink<T, MODE> sink{fout, fixed_acc<MODE>(facc), 0.0};
         track_range<T, OPS, PER>(tv, start, end, nullptr, 3, pos, field, force, ids, vel, sink, grad, hid);
     }
 }
