@@ -45,18 +45,18 @@ PASSES = ("k_block<", "k_node_ranges<", "k_batch<")
 
 def write_traffic(args, fetch_csv, write_csv):
     """HBM bytes per run of the persistent passes (the block pass and the short
-    ranges, or k_batch) from FETCH_SIZE / WRITE_SIZE (KiB per dispatch; one
-    k_fx_finalize a run), each scaled by what the same counter reads for the 1 GiB
+    ranges, or k_batch) from FETCH_SIZE / WRITE_SIZE (KiB per dispatch; a run
+    is a k_fx_finalize dispatch, or without those a dispatch), each scaled by what the same counter reads for the 1 GiB
     calibration copy (which reads and writes exactly COPY_BYTES)."""
     import csv
 
     def per_kernel(path, counter):
         rows = [r for r in csv.DictReader(open(path)) if r["Counter_Name"] == counter]
         batch = [float(r["Counter_Value"]) for r in rows if any(k in r["Kernel_Name"] for k in PASSES)]
-        runs = sum("k_fx_finalize" in r["Kernel_Name"] for r in rows)
+        runs = sum("k_fx_finalize" in r["Kernel_Name"] for r in rows) or len(batch)
         copies = [float(r["Counter_Value"]) for r in rows if "copy" in r["Kernel_Name"].lower()]
-        if not batch or not runs or not copies:
-            raise SystemExit(f"{path}: no pass, finalize or copy dispatch with {counter}")
+        if not batch or not copies:
+            raise SystemExit(f"{path}: no pass or copy dispatch with {counter}")
         return sum(batch) / runs, max(copies)
 
     fb, fc = per_kernel(fetch_csv, "FETCH_SIZE")
