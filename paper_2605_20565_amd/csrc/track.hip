@@ -51,8 +51,10 @@ constexpr int64_t kNodesMaxGather = 16384;
 // the hosts itself and may allocate: calls that spread from kSortMinSpread
 // points (random points on 38 k leaves, fixed point: 60 k 88 -> 58 us, 100 k
 // 238 -> 63, 1 M 3406 -> 160; markers in order 100 k 66 -> 63, 1 M 236 -> 179;
-// FP64 forward and backward of 50 k random points 118 unsorted, 132 sorted),
-// others from
+// FP64 forward and backward of 50 k random points 118 unsorted, 132 sorted), sums
+// in FP32, which do not take the node pass, from kSortMinF32Sums (38 k leaves, 28 k
+// random points 107 us unsorted, 28 k markers in order 53; 40 k 148 -> 52 and
+// 88 -> 45), others from
 // kSortMinGather, gradients apart (3 M random points 350 -> 217 us on 38 k
 // leaves, 828 -> 246 on 2.7 M; markers in order 212 -> 220, 270 -> 234; with the
 // gradient markers in order lost, 218 -> 315).
