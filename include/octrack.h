@@ -87,7 +87,9 @@ extern "C" {
 /* Spreading accumulation.  ATOMIC: atomic adds, order dependent in the last
  * bits; workgroups sum their points' contributions in FP64 (for FP32 inputs
  * the exact products) and add each partial sum to field_out with one atomic
- * in the working precision (FP32 or FP64).  FIXED: every
+ * in the working precision (FP32 or FP64); calls and plans that sort their
+ * points may keep the whole sums of FP32 in FP64 and round them once, where
+ * they would add more often to a leaf than an unsorted call.  FIXED: every
  * contribution is rounded once to a signed 64-bit fixed-point value
  * q = rint(w F 2^s), ties to even, formed with one FP64 fused multiply-add
  * (exact product for FP32 inputs, the exact FP64 product rounded once for

@@ -121,15 +121,18 @@ int sorted_pass(const ot_tree *t, int ops, const void *field, const void *force,
     p.fxws = mode == OT_SPREAD_FIXED ? work : nullptr;
     p.use_blocks = blk_rule(t, n, ops);
     p.use_nodes = !p.use_blocks && node_rule(t, n, ops);
+    const bool f32_sums = dtype == OT_F32 && mode == OT_SPREAD_ATOMIC && (ops & kOpSpread);
+    p.wide = f32_sums && (p.use_blocks || p.use_nodes);
     p.sort_key = p.use_blocks ? point_sort_by_block(t->view.nblk) : point_sort_by_host(t->n_leaves);
-    default_shape(t, n, true, 0, p.block, p.tile);
+    // (sums in FP32 not kept in FP64: tiles as large as an unsorted call's, so as few adds to a leaf)
+    default_shape(t, n, !f32_sums, 0, p.block, p.tile);
     p.small_table = p.tile <= kSmallTile;
     p.n_tiles = (n + p.tile - 1) / p.tile;
     p.grid = t->cus * (p.small_table ? 8 : 2);
     const int64_t rec = ((ops & (kOpSpread | kOpGrad)) ? 6 : 3) * n * (dtype == OT_F32 ? 4 : 8);
     auto up = [](int64_t b) { return (b + 255) & ~int64_t(255); };
     const int64_t total = 2 * up(8 * n) + 2 * up(rec) + up(point_sort_ws_bytes(n)) +
-                          (p.use_blocks ? up(blk_bytes(t, n)) : 0) + 256;
+                          (p.use_blocks ? up(blk_bytes(t, n)) : 0) + (p.wide ? up(spread_ws_bytes(t->n_leaves)) : 0) + 256;
     const Scratch m = scratch_take(t, (size_t)total, s);
     if (!m.p) return OT_OK;
     char *q = (char *)m.p;
@@ -145,6 +148,7 @@ int sorted_pass(const ot_tree *t, int ops, const void *field, const void *force,
     p.sws = take(point_sort_ws_bytes(n));
     p.counter = (unsigned *)take(64);
     if (p.use_blocks) blk_layout(t, n, take(blk_bytes(t, n)), p.counter, &p.blk);
+    if (p.wide) p.fxws = take(spread_ws_bytes(t->n_leaves));
     handled = true;
     const int rc = enqueue_any(&p, field, force, pos, ids, vel, fout, grad, s);
     scratch_give(t, m, s);
