@@ -159,7 +159,7 @@ typedef struct {
  * neighbouring threads share stencil nodes in cache and in the workgroup's
  * spreading table.  Runs of few points (under 55,000 that spread, under
  * 100,000 that do not) are not sorted at all unless OT_TUNE_HOST_MAJOR asks
- * for it or they spread in FP32 with OT_SPREAD_ATOMIC; those plans keep their
+ * for it or they spread with OT_SPREAD_ATOMIC.  FP32 plans that do keep their
  * sums in FP64 (a plan-owned buffer of ot_spread_workspace_bytes) and round
  * them once at the end of a run.  Results are the same bit for bit (FIXED).  Needs the
  * same ops for every instance. */

@@ -202,8 +202,9 @@ int enqueue(ot_batch_plan *p, const void *field, const void *force, const void *
         if (p->use_blocks && (rc = enqueue_blocks<T, MODE>(t, p->blk, bops, kv, kpos, (const T *)field, (T *)vel,
                                                            (T *)fout, ws, (T *)grad, s)))
             return rc;
+        constexpr bool atomic_f64 = sizeof(T) == 8 && MODE == kModeAtomic;
         const NodeRanges nr = p->use_blocks ? NodeRanges{p->blk.ranges, p->counter + kBlkRanges, n, kBlkWindow, false}
-                                            : NodeRanges{nullptr, nullptr, n, node_range_pts(t, n), true};
+                                            : NodeRanges{nullptr, nullptr, n, node_range_pts(t, n, atomic_f64), true};
         if ((rc = enqueue_ranges<T, MODE>(t, bops, nr, p->counter, kv, kpos, (const T *)field, (T *)vel, (T *)fout, ws,
                                           (T *)grad, s)))
             return rc;

@@ -17,6 +17,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "ot_common.h"
 #include "track_device.h"
 
@@ -271,8 +273,19 @@ struct NodeRanges {
 };
 
 // Points of a range of a whole run: what the table holds the nodes of.  Points
-// much rarer than leaves share few nodes (27 each), so one step's worth.
-inline int node_range_pts(const ot_tree *t, int64_t n) { return 4 * n >= t->n_leaves ? 4 * kRangePts : kRangePts; }
+// much rarer than leaves share few nodes (27 each), so one step's worth.  Sums
+// added in FP64 (atomic_f64) are rounded at each add, in the table too: long
+// ranges make long chains there, short ones more adds to device memory.  Steps
+// that grow with the run keep them as exact as the tiles of an unsorted call or
+// of a plan sorted by host (points in host order on 4,096 leaves, relative
+// error of the field by tiles, 4 steps, these: 65 k 3.6e-16, 4.4e-16, 3.5e-16; 100 k
+// 4.2e-16, 4.7e-16, 4.1e-16; spreading 50 k 49 -> 53 us, 100 k 67 -> 71).
+constexpr int64_t kRangeStepPts = 50000;
+inline int node_range_pts(const ot_tree *t, int64_t n, bool atomic_f64)
+{
+    if (4 * n < t->n_leaves) return kRangePts;
+    return (atomic_f64 ? (int)std::max<int64_t>(1, std::min<int64_t>(4, n / kRangeStepPts)) : 4) * kRangePts;
+}
 
 template <typename T, int OPS, int MODE, bool PER>
 __global__ __launch_bounds__(kRangeThreads) void k_node_ranges(TreeView tv, NodeRanges nr, unsigned *__restrict__ queue,
