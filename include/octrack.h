@@ -158,8 +158,9 @@ typedef struct {
  * consecutive ids (two passes up to 4 M leaves, three above), so that
  * neighbouring threads share stencil nodes in cache and in the workgroup's
  * spreading table.  Runs of few points (under 55,000 that spread, under
- * 100,000 that do not) are not sorted at all unless OT_TUNE_HOST_MAJOR asks
- * for it or they spread with OT_SPREAD_ATOMIC.  FP32 plans that do keep their
+ * 100,000 that do not) and runs that spread on at most 512 leaves are not
+ * sorted at all unless OT_TUNE_HOST_MAJOR asks for it or they spread with
+ * OT_SPREAD_ATOMIC.  FP32 plans that do keep their
  * sums in FP64 (a plan-owned buffer of ot_spread_workspace_bytes) and round
  * them once at the end of a run.  Results are the same bit for bit (FIXED).  Needs the
  * same ops for every instance. */

@@ -223,7 +223,7 @@ extern "C" int ot_batch_plan_create(const ot_tree *tree, const int64_t *offsets,
     const bool f32_sums = dtype == OT_F32 && mode == OT_SPREAD_ATOMIC && (ops_all & kOpSpread);
     // atomic sums keep their tiles of sorted points, which split a leaf's sum least
     p->use_small = sort_points && !(tuning->flags & OT_TUNE_HOST_MAJOR) &&
-                   !(mode == OT_SPREAD_ATOMIC && (ops_all & kOpSpread)) && small_rule(p->n_points, ops_all);
+                   !(mode == OT_SPREAD_ATOMIC && (ops_all & kOpSpread)) && small_rule(tree, p->n_points, ops_all);
     if (sort_points && p->n_points > 0 && !p->use_small) {
         const int64_t n = p->n_points;
         p->use_blocks = !(tuning->flags & OT_TUNE_HOST_MAJOR) && blk_rule(tree, n, ops_all);

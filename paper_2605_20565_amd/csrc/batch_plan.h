@@ -24,8 +24,9 @@ struct BlkWork {
 int64_t blk_bytes(const ot_tree *t, int64_t n);       // device bytes besides the words
 void blk_layout(const ot_tree *t, int64_t n, void *mem, unsigned *words, BlkWork *w);
 bool node_rule(const ot_tree *t, int64_t n, int ops); // ... or the node-parallel pass
-bool small_rule(int64_t n, int ops);                  // ... or the unsorted passes of plain calls
+bool small_rule(const ot_tree *t, int64_t n, int ops); // ... or the unsorted passes of plain calls
 constexpr int64_t kSortMinSpread = 55000, kSortMinF32Sums = 30000;             // plain calls that spread sort from here on
+constexpr int64_t kFewLeaves = 512;   // a tree that the smallest spreading table holds (track.hip)
 bool blk_rule(const ot_tree *t, int64_t n, int ops);  // whether sorted points take the block pass
 }  // namespace ot
 

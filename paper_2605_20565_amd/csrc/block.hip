@@ -185,8 +185,9 @@ bool node_rule(const ot_tree *t, int64_t n, int ops)
 // for atomic spreading: an unsorted pass adds to a leaf more often, and the
 // sums were up to 3 times less exact (FP64, 50 k random points on 4,096 leaves
 // 3.5e-16 -> 6.4e-16, on 512 leaves 4.3e-16 -> 1.3e-15).
-bool small_rule(int64_t n, int ops)
+bool small_rule(const ot_tree *t, int64_t n, int ops)
 {
+    if (n > 0 && (ops & kOpSpread) && t->n_leaves <= kFewLeaves) return true;   // (390 k points 219 sorted, 71 us)
     return n > 0 && (ops & ~kOpLocate) && n < ((ops & kOpSpread) ? kSortMinSpread : int64_t(100000));
 }
 

@@ -47,6 +47,16 @@ constexpr int kMaxPointsPerThread = 4;
 // (three launches instead of five).
 constexpr int64_t kNodesMaxSpread = 65535;   // sums in FP32 apart (run_pass)
 constexpr int64_t kNodesMaxGather = 16384;
+// Trees of so few leaves that the smallest spreading table holds them all: the
+// per-point pass then adds a leaf's sum to device memory once a workgroup in
+// any order of the points, and sorting gains nothing (512 leaves, random
+// points, fixed point, per-point pass against sorted: 100 k 47 against 59 us,
+// 1 M 100 against 203, 4 M 294 against 696).  The node-parallel pass saves two
+// launches of fixed-point calls (2 k points 21 -> 17 us, 16 k 23 against 29) and
+// none of atomic ones, whose FP64 sums it makes less exact (8 k points 4.5e-16 ->
+// 5.6e-16, 50 k 9.5e-16 -> 1.28e-15).
+static_assert(kFewLeaves == kSmallSlots, "every leaf has a slot of its own");
+constexpr int64_t kNodesMaxFewLeaves = 8192;
 // Larger sets are sorted first, as a sorted plan does, when the call searches
 // the hosts itself and may allocate: calls that spread from kSortMinSpread
 // points (random points on 38 k leaves, fixed point: 60 k 88 -> 58 us, 100 k
@@ -312,7 +322,8 @@ int run_pass(const ot_tree *t, int ops, const void *field, const void *force, co
     // 28 points had made them up to 1.3 times less exact (16 k markers in order:
     // 1.6e-7 -> 2.1e-7).
     const bool f32_sums = spread && mode == OT_SPREAD_ATOMIC && dtype == OT_F32;
-    if (may_sort && !hid && (ops & ~kOpLocate) && n <= INT32_MAX &&
+    const bool few = spread && t->n_leaves <= kFewLeaves;
+    if (may_sort && !hid && (ops & ~kOpLocate) && n <= INT32_MAX && !few &&
         (spread ? n >= (f32_sums ? kSortMinF32Sums : kSortMinSpread) : n >= kSortMinGather && !(ops & kOpGrad))) {
         bool handled;
         rc = sorted_pass(t, ops, field, force, pos, dtype, n, mode, accumulate, ids, vel, fout, grad, work, s, handled);
@@ -321,7 +332,10 @@ int run_pass(const ot_tree *t, int ops, const void *field, const void *force, co
             return rc;
         }
     }
-    if (n > 0 && (ops & ~kOpLocate) && !f32_sums && n <= (spread ? kNodesMaxSpread : kNodesMaxGather)) {
+    const int64_t nodes_max = !spread ? kNodesMaxGather
+                              : !few  ? (f32_sums ? 0 : kNodesMaxSpread)
+                                      : (mode == OT_SPREAD_FIXED ? kNodesMaxFewLeaves : 0);
+    if (n > 0 && (ops & ~kOpLocate) && n <= nodes_max) {
         rc = dtype == OT_F32 ? nodes_pass<float>(t, ops, field, force, pos, dtype, n, mode, accumulate, ids, vel, fout,
                                                  grad, ws, hid, s)
                              : nodes_pass<double>(t, ops, field, force, pos, dtype, n, mode, accumulate, ids, vel, fout,

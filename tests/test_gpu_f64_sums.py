@@ -47,3 +47,9 @@ def test_sorted_plan(n, order):
         plan.run(X, force=V, field_out=fo)
     assert err(fo) <= 1.5 * _estimate(27.0 * n / spec.n_leaves / 60, 60)
     plan.close()
+
+
+@pytest.mark.parametrize("n", [8000, 50_000, 100_000])
+def test_plain_call_on_few_leaves(n):
+    spec, t, X, V, err = _inputs(3, n, "random")
+    assert err(t.spread(V, X)) <= 1.15 * _estimate(64 * 27.0 / spec.n_leaves, n / 64)
