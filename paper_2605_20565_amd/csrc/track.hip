@@ -64,11 +64,12 @@ constexpr int64_t kNodesMaxFewLeaves = 8192;
 // FP64 forward and backward of 50 k random points 118 unsorted, 132 sorted), sums
 // in FP32, which do not take the node pass, from kSortMinF32Sums (38 k leaves, 28 k
 // random points 107 us unsorted, 28 k markers in order 53; 40 k 148 -> 52 and
-// 88 -> 45), others from
-// kSortMinGather, gradients apart (3 M random points 350 -> 217 us on 38 k
-// leaves, 828 -> 246 on 2.7 M; markers in order 212 -> 220, 270 -> 234; with the
-// gradient markers in order lost, 218 -> 315).
-constexpr int64_t kSortMinGather = 2000000;
+// 88 -> 45).  Calls that only gather take their points as they are: sorting
+// would gain with random points on large trees what it would lose with points
+// in host order, as particles are kept (interpolation of 10^7 points, FP32, on
+// 2.7 M leaves 2743 -> 702 us and 302 -> 535, on 38 k leaves 1175 -> 657 and 179 ->
+// 522), and nothing tells the two apart before the call.  Programs with points
+// in random order have sorted plans.
 
 // Prepare the spreading target before a pass: zero the output (atomic mode,
 // overwrite) or the fixed-point accumulators and compute the scale.
@@ -323,8 +324,7 @@ int run_pass(const ot_tree *t, int ops, const void *field, const void *force, co
     // 1.6e-7 -> 2.1e-7).
     const bool f32_sums = spread && mode == OT_SPREAD_ATOMIC && dtype == OT_F32;
     const bool few = spread && t->n_leaves <= kFewLeaves;
-    if (may_sort && !hid && (ops & ~kOpLocate) && n <= INT32_MAX && !few &&
-        (spread ? n >= (f32_sums ? kSortMinF32Sums : kSortMinSpread) : n >= kSortMinGather && !(ops & kOpGrad))) {
+    if (may_sort && !hid && spread && !few && n <= INT32_MAX && n >= (f32_sums ? kSortMinF32Sums : kSortMinSpread)) {
         bool handled;
         rc = sorted_pass(t, ops, field, force, pos, dtype, n, mode, accumulate, ids, vel, fout, grad, work, s, handled);
         if (handled) {
