@@ -160,11 +160,19 @@ void blk_layout(const ot_tree *t, int64_t n, void *mem, unsigned *words, BlkWork
 // interpolation 137 against 136, FP64 190 against 163.
 constexpr int64_t kBlkMinSpread = 400000, kBlkMinBoth = 300000;
 constexpr int64_t kBlkMinGather = 2000000;
+// Plans that do not spread have only the sharing of lookups and field rows to
+// gain, so their line also asks for leaves that caches do not hold: 4 M random
+// points, interpolation, tiles of points sorted by host against block pass, on
+// 14 k leaves 261 against 321 us, 38 k 273 against 283, 0.6 M 366 -> 293, 2.7 M
+// 449 -> 322 (10^7: 705 against 733, 736 -> 657, 902 -> 675, 978 -> 702); on 512
+// leaves, one block, 10^7 points took 643 against 1907.
+constexpr int64_t kBlkMinGatherLeaves = 131072;
 bool blk_rule(const ot_tree *t, int64_t n, int ops)
 {
     if (!(ops & ~kOpLocate)) return false;
     const bool gathers = (ops & (kOpInterp | kOpGrad)) != 0;
     const int64_t least = !(ops & kOpSpread) ? kBlkMinGather : gathers ? kBlkMinBoth : kBlkMinSpread;
+    if (!(ops & kOpSpread) && t->n_leaves < kBlkMinGatherLeaves) return false;
     return t->view.lev[0] >= kBlkBits && n >= 64 * (int64_t)t->view.nblk && n >= least && n < (int64_t(1) << 31);
 }
 
