@@ -160,9 +160,9 @@ typedef struct {
  * spreading table.  Runs of few points (under 55,000 that spread, under
  * 100,000 that do not) and runs that spread on at most 512 leaves are not
  * sorted at all unless OT_TUNE_HOST_MAJOR asks for it or they spread with
- * OT_SPREAD_ATOMIC.  FP32 plans that do keep their
- * sums in FP64 (a plan-owned buffer of ot_spread_workspace_bytes) and round
- * them once at the end of a run.  Results are the same bit for bit (FIXED).  Needs the
+ * OT_SPREAD_ATOMIC.  FP32 plans that do, on trees that their points are not
+ * too few for, keep their sums in FP64 (a plan-owned buffer of
+ * ot_spread_workspace_bytes) and round them once at the end of a run.  Results are the same bit for bit (FIXED).  Needs the
  * same ops for every instance. */
 #define OT_TUNE_SORT_POINTS 1
 

@@ -119,13 +119,12 @@ int sorted_pass(const ot_tree *t, int ops, const void *field, const void *force,
     p.n_points = n;
     p.sort_points = true;
     p.fxws = mode == OT_SPREAD_FIXED ? work : nullptr;
-    p.use_blocks = blk_rule(t, n, ops);
-    p.use_nodes = !p.use_blocks && node_rule(t, n, ops);
-    const bool f32_sums = dtype == OT_F32 && mode == OT_SPREAD_ATOMIC && (ops & kOpSpread);
-    p.wide = f32_sums && (p.use_blocks || p.use_nodes);
+    const SortedRoute route = sorted_route(t, n, ops, dtype, mode, false);
+    p.use_blocks = route.blocks;
+    p.use_nodes = route.nodes;
+    p.wide = route.wide;
     p.sort_key = p.use_blocks ? point_sort_by_block(t->view.nblk) : point_sort_by_host(t->n_leaves);
-    // (sums in FP32 not kept in FP64: tiles as large as an unsorted call's, so as few adds to a leaf)
-    default_shape(t, n, !f32_sums, 0, p.block, p.tile);
+    default_shape(t, n, true, 0, p.block, p.tile);
     p.small_table = p.tile <= kSmallTile;
     p.n_tiles = (n + p.tile - 1) / p.tile;
     p.grid = t->cus * (p.small_table ? 8 : 2);
@@ -220,15 +219,16 @@ extern "C" int ot_batch_plan_create(const ot_tree *tree, const int64_t *offsets,
     p->sort_points = sort_points;
     p->ops_all = ops_all;
     p->grad_plan = (ops_union & kOpGrad) != 0;
-    const bool f32_sums = dtype == OT_F32 && mode == OT_SPREAD_ATOMIC && (ops_all & kOpSpread);
     // atomic sums keep their tiles of sorted points, which split a leaf's sum least
     p->use_small = sort_points && !(tuning->flags & OT_TUNE_HOST_MAJOR) &&
                    !(mode == OT_SPREAD_ATOMIC && (ops_all & kOpSpread)) && small_rule(tree, p->n_points, ops_all);
     if (sort_points && p->n_points > 0 && !p->use_small) {
         const int64_t n = p->n_points;
-        p->use_blocks = !(tuning->flags & OT_TUNE_HOST_MAJOR) && blk_rule(tree, n, ops_all);
-        p->use_nodes = !p->use_blocks && !(tuning->flags & OT_TUNE_HOST_MAJOR) && node_rule(tree, n, ops_all);
-        if (f32_sums && (p->use_blocks || p->use_nodes)) {
+        SortedRoute route{false, false, false};
+        if (!(tuning->flags & OT_TUNE_HOST_MAJOR)) route = sorted_route(tree, n, ops_all, dtype, mode, true);
+        p->use_blocks = route.blocks;
+        p->use_nodes = route.nodes;
+        if (route.wide) {
             p->wide = hipMalloc(&p->fxws, (size_t)spread_ws_bytes(tree->n_leaves)) == hipSuccess;
             if (!p->wide) {   // no room for the sums: tiles of points sorted by host
                 (void)hipGetLastError();

@@ -23,11 +23,16 @@ struct BlkWork {
 };
 int64_t blk_bytes(const ot_tree *t, int64_t n);       // device bytes besides the words
 void blk_layout(const ot_tree *t, int64_t n, void *mem, unsigned *words, BlkWork *w);
-bool node_rule(const ot_tree *t, int64_t n, int ops); // ... or the node-parallel pass
-bool small_rule(const ot_tree *t, int64_t n, int ops); // ... or the unsorted passes of plain calls
-constexpr int64_t kSortMinSpread = 55000, kSortMinF32Sums = 30000;             // plain calls that spread sort from here on
+// The pass over sorted points: tiles of blocks, short ranges, or neither (tiles
+// of points sorted by host); wide: FP32 sums kept in FP64 (ot_batch_plan::wide).
+struct SortedRoute {
+    bool blocks, nodes, wide;
+};
+SortedRoute sorted_route(const ot_tree *t, int64_t n, int ops, int dtype, int mode, bool plan);
+bool plain_sorts(const ot_tree *t, int64_t n, int ops, int dtype, int mode);   // a plain call's points
+bool small_rule(const ot_tree *t, int64_t n, int ops);   // a sorted plan takes the unsorted passes of plain calls
+constexpr int64_t kSortMinSpread = 55000, kSortMinF32Sums = 30000;   // plain calls that spread sort from here on
 constexpr int64_t kFewLeaves = 512;   // a tree that the smallest spreading table holds (track.hip)
-bool blk_rule(const ot_tree *t, int64_t n, int ops);  // whether sorted points take the block pass
 }  // namespace ot
 
 struct ot_batch_plan {

@@ -146,20 +146,34 @@ void blk_layout(const ot_tree *t, int64_t n, void *mem, unsigned *words, BlkWork
     w->ranges = (uint2 *)p;
 }
 
-// Root cubes need a root of at least 8^3 cells.  Fewer than 64 points per
-// block on average leave most blocks to the per-point pass, which then does
-// better on points sorted by groups of 64 leaves.  The pass has three launches
-// more.  Measured, FP32, per-point against block pass: spreading 200 k points
-// on 38 k leaves 122 against 139 us, 400 k 214 -> 141, 1 M 419 -> 168; on 0.5 M
-// leaves 400 k 155 against 163, 1 M 229 -> 188.  Interpolation alone 1 M 107
-// against 132 and 143 against 138, 3 M 213 against 234 and 270 -> 242; on 2.7 M
-// leaves 3 M 322 -> 226.
-// Calls that only spread change over later: their node ranges need no buffer
-// for gathered values in LDS.  Markers in order on 38 k leaves, 331 k points, node ranges
-// against block pass: FP32 115 against 126 us, FP64 128 against 148; with
-// interpolation 137 against 136, FP64 190 against 163.
+// The pass over sorted points.
+//
+// Blocks.  Root cubes need a root of at least 8^3 cells.  Fewer than 64 points
+// per block on average, or fewer than one per three leaves, leave most blocks to
+// the short ranges or make tiles that cost more than their points: 600 k random
+// points on 2.7 M leaves take 365 us, ranges 304, tiles of points sorted by host
+// 329 (1 M: 307, 298, 352; markers 188, 243, 224).  The pass has three launches
+// more than the others.  Spreading, FP32, ranges against blocks: 200 k points on
+// 38 k leaves 91 against 117 us, 400 k 126 and 144, 600 k 162 and 159, 1 M 209 and
+// 168; on 0.6 M leaves 400 k 143 and 167, 1 M 217 and 208; markers on 38 k leaves
+// 331 k points 115 against 126, FP64 128 and 148, and with interpolation, whose
+// values ranges must buffer in LDS, 137 against 136 and 190 against 163.
+//
+// Ranges are a short chain where tiles of points sorted by host are a long one
+// (200 k points on 38 k leaves 91 us against 116), but each looks its nodes up
+// anew, and in FP64 with gathers one workgroup fills a CU's LDS: forward and
+// backward of 200 k points FP64 on 38 k leaves 150 us and 128 by tiles, 300 k on
+// 0.6 M leaves 215 and 163, 600 k on 2.7 M leaves 466 and 387 (spreading 326 and
+// 374).  Points much rarer than leaves share nothing in a tile (300 k on 17 M
+// leaves 413 and 574 us; 4 M 1585 and 1135).
 constexpr int64_t kBlkMinSpread = 400000, kBlkMinBoth = 300000;
 constexpr int64_t kBlkMinGather = 2000000;
+constexpr int64_t kNodeMaxSpread = 400000;
+// FP64 with gathers: blocks from 1 M points (0.6 M leaves 518 us by ranges, 311
+// blocks, 310 tiles) or where four to a leaf are there (400 k on 14 k leaves 236,
+// 204, 287), ranges below that (200 k on 2.7 M leaves 215 by ranges, 392 by tiles;
+// markers there 197 and 150).
+constexpr int64_t kBlkMinF64Both = 1000000, kBlkMinF64Crowded = 250000, kNodeMaxF64Both = 250000;
 // Plans that do not spread have only the sharing of lookups and field rows to
 // gain, so their line also asks for leaves that caches do not hold: 4 M random
 // points, interpolation, tiles of points sorted by host against block pass, on
@@ -167,24 +181,47 @@ constexpr int64_t kBlkMinGather = 2000000;
 // 449 -> 322 (10^7: 705 against 733, 736 -> 657, 902 -> 675, 978 -> 702); on 512
 // leaves, one block, 10^7 points took 643 against 1907.
 constexpr int64_t kBlkMinGatherLeaves = 131072;
-bool blk_rule(const ot_tree *t, int64_t n, int ops)
+// FP32 atomic sums in FP64 (blocks and ranges) cost 60 bytes a leaf and a launch
+// where FP32 ones cost 12: 10 us a million leaves, 0.18 ms of 17 M.  On larger
+// trees than this plans keep to tiles of points sorted by host and FP32 sums (100 k
+// points on 17 M leaves 317 us wide, 230 by tiles; 4 M 1574 and 1042), and plain
+// calls do not sort fewer points than a 64th of the leaves (100 k points in
+// host order 154 unsorted, 320 wide; 300 k 737 and 406, random ones 1152 and 408).
+constexpr int64_t kWideMaxLeaves = 4000000;
+static bool wide_fits(const ot_tree *t, int64_t n, bool plan)
 {
-    if (!(ops & ~kOpLocate)) return false;
-    const bool gathers = (ops & (kOpInterp | kOpGrad)) != 0;
-    const int64_t least = !(ops & kOpSpread) ? kBlkMinGather : gathers ? kBlkMinBoth : kBlkMinSpread;
-    if (!(ops & kOpSpread) && t->n_leaves < kBlkMinGatherLeaves) return false;
-    return t->view.lev[0] >= kBlkBits && n >= 64 * (int64_t)t->view.nblk && n >= least && n < (int64_t(1) << 31);
+    return t->n_leaves <= kWideMaxLeaves || (plan ? 2 : 64) * n >= t->n_leaves;
 }
 
-// Sorted runs that spread fewer points than this take the node-parallel pass
-// (its launch is 40 us where the per-point pass, one long chain per point,
-// takes 63 to 111 at 200 k points on 38 k leaves; at 1 M the block pass is as
-// fast), or rarer points than a quarter of the leaves (400 k points on 2.7 M
-// leaves 299 us in the per-point pass).
-constexpr int64_t kNodeMaxSpread = 400000;
-bool node_rule(const ot_tree *t, int64_t n, int ops)
+SortedRoute sorted_route(const ot_tree *t, int64_t n, int ops, int dtype, int mode, bool plan)
 {
-    return (ops & kOpSpread) && (n < kNodeMaxSpread || 4 * n < t->n_leaves);
+    SortedRoute r{false, false, false};
+    const bool spread = (ops & kOpSpread) != 0, gathers = (ops & (kOpInterp | kOpGrad)) != 0;
+    const bool f32_sums = spread && dtype == OT_F32 && mode == OT_SPREAD_ATOMIC;
+    const bool blocks = t->view.lev[0] >= kBlkBits && n >= 64 * (int64_t)t->view.nblk && n < (int64_t(1) << 31);
+    if (!(ops & ~kOpLocate) || (f32_sums && !wide_fits(t, n, plan))) return r;
+    if (!spread) {
+        r.blocks = blocks && n >= kBlkMinGather && t->n_leaves >= kBlkMinGatherLeaves;
+        return r;
+    }
+    const bool dense = 3 * n >= t->n_leaves;
+    if (dtype == OT_F64 && gathers) {
+        r.blocks = blocks && ((dense && n >= kBlkMinF64Both) || (n >= kBlkMinF64Crowded && n >= 4 * t->n_leaves));
+        r.nodes = !r.blocks && (n < kNodeMaxF64Both || 32 * n < t->n_leaves);
+    } else {
+        r.blocks = blocks && dense && n >= (gathers ? kBlkMinBoth : kBlkMinSpread);
+        r.nodes = !r.blocks && (n < kNodeMaxSpread || 16 * n < t->n_leaves || (f32_sums && !plan));
+    }
+    r.wide = f32_sums && (r.blocks || r.nodes);
+    return r;
+}
+
+// Which plain calls that search the hosts themselves are sorted (track.hip).
+bool plain_sorts(const ot_tree *t, int64_t n, int ops, int dtype, int mode)
+{
+    const bool f32_sums = dtype == OT_F32 && mode == OT_SPREAD_ATOMIC;
+    return (ops & kOpSpread) && t->n_leaves > kFewLeaves && n <= INT32_MAX &&
+           n >= (f32_sums ? kSortMinF32Sums : kSortMinSpread) && (!f32_sums || wide_fits(t, n, false));
 }
 
 // Sorted plans of so few points that the plain passes are faster unsorted

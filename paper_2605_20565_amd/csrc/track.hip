@@ -324,7 +324,7 @@ int run_pass(const ot_tree *t, int ops, const void *field, const void *force, co
     // 1.6e-7 -> 2.1e-7).
     const bool f32_sums = spread && mode == OT_SPREAD_ATOMIC && dtype == OT_F32;
     const bool few = spread && t->n_leaves <= kFewLeaves;
-    if (may_sort && !hid && spread && !few && n <= INT32_MAX && n >= (f32_sums ? kSortMinF32Sums : kSortMinSpread)) {
+    if (may_sort && !hid && plain_sorts(t, n, ops, dtype, mode)) {
         bool handled;
         rc = sorted_pass(t, ops, field, force, pos, dtype, n, mode, accumulate, ids, vel, fout, grad, work, s, handled);
         if (handled) {
