@@ -43,11 +43,13 @@
  *   - A tree handle is read-only after ot_build_tree: every call that needs
  *     working memory takes it from the caller (a `work` argument), from its
  *     batch plan, or allocates it on the call's stream, so calls on one tree
- *     may run on several streams at once.  Larger calls on points without
- *     given host ids sort the points first; that memory the tree keeps for
- *     the next such call (at most four buffers and 1 GiB, for one call each
- *     at a time, freed with the tree).  Where there is none to be had, and in
- *     calls that are captured in a graph, the points are taken as they are.
+ *     may run on several streams at once.  Larger calls that spread, on
+ *     points without given host ids, sort the points first; that memory the
+ *     library keeps for the next such call on any tree of the device (at most
+ *     four buffers and 1 GiB a device, for one call each at a time; 256 MiB
+ *     once the device's last tree is destroyed).  Where there is none to be
+ *     had, and in calls that are captured in a graph, the points are taken as
+ *     they are.
  *   - Memory of destroyed trees and of builds is kept for the trees built
  *     next on its device: at most six blocks and 256 MiB in the process,
  *     given back when an allocation for a build fails.

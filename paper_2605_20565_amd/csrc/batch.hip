@@ -13,6 +13,7 @@
 #include <vector>
 
 #include "batch_plan.h"
+#include "memory.h"
 #include "ot_common.h"
 #include "point_sort.h"
 #include "track_device.h"
@@ -132,7 +133,7 @@ int sorted_pass(const ot_tree *t, int ops, const void *field, const void *force,
     auto up = [](int64_t b) { return (b + 255) & ~int64_t(255); };
     const int64_t total = 2 * up(8 * n) + 2 * up(rec) + up(point_sort_ws_bytes(n)) +
                           (p.use_blocks ? up(blk_bytes(t, n)) : 0) + (p.wide ? up(spread_ws_bytes(t->n_leaves)) : 0) + 256;
-    const Scratch m = scratch_take(t, (size_t)total, s);
+    const Scratch m = scratch_take(t->device, (size_t)total, s);
     if (!m.p) return OT_OK;
     char *q = (char *)m.p;
     auto take = [&](int64_t b) {
@@ -150,7 +151,7 @@ int sorted_pass(const ot_tree *t, int ops, const void *field, const void *force,
     if (p.wide) p.fxws = take(spread_ws_bytes(t->n_leaves));
     handled = true;
     const int rc = enqueue_any(&p, field, force, pos, ids, vel, fout, grad, s);
-    scratch_give(t, m, s);
+    scratch_give(t->device, m, s);
     return rc;
 }
 

@@ -4,7 +4,6 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
-#include <mutex>
 #include <string>
 
 #include "../../include/octrack.h"
@@ -322,29 +321,6 @@ void radix_sort_pairs(const K *kin, K *ka, int32_t *va, K *kb, int32_t *vb, int6
                       int32_t **v_res, hipStream_t s);
 int fail(int code, const std::string &msg);
 
-// Working memory of plain calls that sort their points, kept with the tree
-// between calls (the runtime's stream-ordered allocator took ~50 us of host time
-// a call).  A call takes a buffer nobody is using, waits on its stream for the
-// event of the buffer's last call, and records the event anew when its kernels
-// are enqueued: calls may come from several threads and streams.  At most
-// kScratchSlots buffers and kScratchKeep bytes are kept (more is allocated for
-// the call and freed with it); they are given back with the tree.
-constexpr int kScratchSlots = 4;
-constexpr size_t kScratchKeep = size_t(1) << 30;
-struct ScratchSlot {
-    void *p;
-    size_t bytes;
-    hipEvent_t done;     // the last call's kernels
-    hipStream_t stream;  // and its stream
-    bool busy;           // a call is enqueueing
-};
-struct Scratch {
-    void *p;   // null: none to be had
-    int slot;  // -1: allocated for this call
-};
-Scratch scratch_take(const ot_tree *t, size_t bytes, hipStream_t s);
-void scratch_give(const ot_tree *t, const Scratch &m, hipStream_t s);
-
 // Fixed-point spreading workspace: a 256-byte header (FxState) followed by
 // the n_leaves x 3 int64 accumulators.
 constexpr int64_t kFxHeader = 256;
@@ -370,9 +346,6 @@ struct ot_tree {
     int64_t table_entries;
     size_t block_bytes[2];   // of the blocks that keys (with levels) and table start
     ot::TreeView view;
-    // working memory kept for plain calls (scratch_take), under its lock
-    mutable std::mutex scratch_lock;
-    mutable ot::ScratchSlot scratch[ot::kScratchSlots];
     // Read-only after the build: the workspace of fixed-point spreading
     // belongs to each call (or batch plan), so calls on one tree may run on
     // several streams at once.

@@ -10,11 +10,10 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <cstddef>
 #include <cstring>
-#include <mutex>
 #include <vector>
 
+#include "memory.h"
 #include "ot_common.h"
 
 namespace ot {
@@ -438,73 +437,6 @@ __global__ void k_count_value(const uint32_t *__restrict__ p, int64_t n, uint32_
 
 inline unsigned nblk(int64_t n, int b = 256) { return (unsigned)((n + b - 1) / b); }
 
-// Memory of trees that are gone, for the trees built next: freeing a used
-// buffer of some 20 MB costs the host 250 us or more (of the 2.4 ms in which a
-// tree of 2.7 M leaves was built and destroyed, 1.4 ms went to hipFree).  At
-// most kKeptBlocks blocks and kKeptBytes are kept, the oldest are freed first,
-// and all of a device's are given back when an allocation on it fails.  Blocks
-// come here only when no work on them is left, so any stream may have them next.
-constexpr size_t kKeptBlocks = 6, kKeptBytes = size_t(256) << 20;
-struct Block {
-    void *p = nullptr;
-    size_t bytes = 0;
-    int device = 0;
-};
-// (a plain array: nothing here throws, and trees may be destroyed after the
-// destructors of static objects)
-std::mutex g_kept_lock;
-Block g_kept[kKeptBlocks];   // oldest first
-size_t g_n_kept = 0;
-
-Block kept_remove(size_t i)
-{
-    const Block b = g_kept[i];
-    for (--g_n_kept; i < g_n_kept; ++i) g_kept[i] = g_kept[i + 1];
-    return b;
-}
-
-// A block of at least `bytes` on the current device; p = null: none.
-Block block_take(size_t bytes)
-{
-    Block b;
-    b.bytes = (bytes + 0xFFFF) & ~size_t(0xFFFF);
-    (void)hipGetDevice(&b.device);
-    std::lock_guard<std::mutex> lock(g_kept_lock);
-    size_t best = kKeptBlocks;
-    for (size_t i = 0; i < g_n_kept; ++i) {
-        const Block &c = g_kept[i];
-        // not more than twice what is asked for
-        if (c.device == b.device && c.bytes >= b.bytes && c.bytes / 2 <= b.bytes &&
-            (best == kKeptBlocks || c.bytes < g_kept[best].bytes))
-            best = i;
-    }
-    if (best < kKeptBlocks) return kept_remove(best);
-    if (hipMalloc(&b.p, b.bytes) == hipSuccess) return b;
-    (void)hipGetLastError();
-    for (size_t i = g_n_kept; i-- > 0;)
-        if (g_kept[i].device == b.device) (void)hipFree(kept_remove(i).p);
-    if (hipMalloc(&b.p, b.bytes) != hipSuccess) {
-        (void)hipGetLastError();
-        b.p = nullptr;
-    }
-    return b;
-}
-
-void block_give(const Block &b)
-{
-    if (!b.p) return;
-    std::lock_guard<std::mutex> lock(g_kept_lock);
-    size_t kept = b.bytes;
-    for (size_t i = 0; i < g_n_kept; ++i) kept += g_kept[i].bytes;
-    while (g_n_kept && (kept > kKeptBytes || g_n_kept == kKeptBlocks)) {
-        const Block old = kept_remove(0);
-        kept -= old.bytes;
-        (void)hipFree(old.p);
-    }
-    if (kept > kKeptBytes) (void)hipFree(b.p);
-    else g_kept[g_n_kept++] = b;
-}
-
 // A build's block: given back at the end, when the build's work on it is done.
 struct BuildBlock {
     Block b;
@@ -584,101 +516,6 @@ template void radix_sort_pairs<uint32_t>(const uint32_t *, uint32_t *, int32_t *
                                          void *, uint32_t **, int32_t **, hipStream_t);
 template void radix_sort_pairs<uint64_t>(const uint64_t *, uint64_t *, int32_t *, uint64_t *, int32_t *, int64_t, int,
                                          void *, uint64_t **, int32_t **, hipStream_t);
-
-}  // namespace ot
-
-namespace ot {
-
-namespace {
-// A graph capture that another stream or thread has under way (in its default,
-// global mode) forbids allocating and asking events; scratch memory never takes
-// part in one, so the calls here are made in relaxed mode.
-struct RelaxedCapture {
-    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-    bool set;
-    RelaxedCapture() : set(hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess) {}
-    ~RelaxedCapture()
-    {
-        if (set) (void)hipThreadExchangeStreamCaptureMode(&mode);
-    }
-    RelaxedCapture(const RelaxedCapture &) = delete;
-    RelaxedCapture &operator=(const RelaxedCapture &) = delete;
-};
-}  // namespace
-
-Scratch scratch_take(const ot_tree *t, size_t bytes, hipStream_t s)
-{
-    std::lock_guard<std::mutex> lock(t->scratch_lock);
-    const RelaxedCapture relaxed;
-    ScratchSlot *best = nullptr, *empty = nullptr;
-    size_t kept = 0;
-    for (ScratchSlot &c : t->scratch) {
-        kept += c.bytes;
-        if (c.busy) continue;
-        if (!c.p) empty = &c;
-        else if (c.bytes >= bytes && (c.stream == s || hipEventQuery(c.done) == hipSuccess) &&
-                 (!best || c.bytes < best->bytes))
-            best = &c;
-    }
-    (void)hipGetLastError();   // an event not reached yet is no error
-    if (!best) {
-        // a new buffer, or one that is too small made larger
-        if (!empty) {
-            for (ScratchSlot &c : t->scratch)
-                if (!c.busy && c.bytes < bytes && (!empty || c.bytes < empty->bytes)) empty = &c;
-            if (empty) {
-                kept -= empty->bytes;
-                (void)hipFree(empty->p);   // waits for its last call
-                empty->p = nullptr;
-                empty->bytes = 0;
-            }
-        }
-        const size_t want = (bytes + bytes / 4 + 0xFFFFF) & ~size_t(0xFFFFF);
-        if (empty && kept + want <= kScratchKeep) {
-            if (!empty->done && hipEventCreateWithFlags(&empty->done, hipEventDisableTiming) != hipSuccess) empty->done = nullptr;
-            if (empty->done && hipMalloc(&empty->p, want) == hipSuccess) {
-                empty->bytes = want;
-                empty->stream = s;
-                empty->busy = true;
-                return {empty->p, (int)(empty - t->scratch)};
-            }
-            empty->p = nullptr;
-            (void)hipGetLastError();
-        }
-        void *p = nullptr;
-        if (hipMallocAsync(&p, bytes, s) != hipSuccess) {
-            (void)hipGetLastError();
-            p = nullptr;
-        }
-        return {p, -1};
-    }
-    if (hipStreamWaitEvent(s, best->done, 0) != hipSuccess) {
-        (void)hipGetLastError();
-        return {nullptr, -1};
-    }
-    best->busy = true;
-    return {best->p, (int)(best - t->scratch)};
-}
-
-void scratch_give(const ot_tree *t, const Scratch &m, hipStream_t s)
-{
-    const RelaxedCapture relaxed;
-    if (m.slot < 0) {
-        if (m.p) (void)hipFreeAsync(m.p, s);
-        return;
-    }
-    std::lock_guard<std::mutex> lock(t->scratch_lock);
-    ScratchSlot &c = t->scratch[m.slot];
-    c.stream = s;
-    if (hipEventRecord(c.done, s) != hipSuccess) {
-        // without the event the buffer cannot be handed on in order
-        (void)hipGetLastError();
-        (void)hipFree(c.p);
-        c.p = nullptr;
-        c.bytes = 0;
-    }
-    c.busy = false;
-}
 
 }  // namespace ot
 
@@ -838,6 +675,7 @@ extern "C" int ot_build_tree(const uint64_t *keys, const uint8_t *levels, int64_
     tv.levels = tr->levels;
     tv.nleaf = (int32_t)n;
     tr->view = tv;
+    scratch_trees(tr->device, 1);
     *out = tr;
     return OT_OK;
 }
@@ -849,10 +687,7 @@ extern "C" int ot_destroy_tree(ot_tree *t)
     (void)hipGetDevice(&cur);
     (void)hipSetDevice(t->device);
     const bool idle = hipDeviceSynchronize() == hipSuccess;
-    for (ScratchSlot &c : t->scratch) {
-        if (c.p) (void)hipFree(c.p);
-        if (c.done) (void)hipEventDestroy(c.done);
-    }
+    scratch_trees(t->device, -1);
     if (idle) {
         block_give(Block{t->keys, t->block_bytes[0], t->device});
         block_give(Block{t->table, t->block_bytes[1], t->device});
