@@ -51,8 +51,9 @@
  *     had, and in calls that are captured in a graph, the points are taken as
  *     they are.
  *   - Memory of destroyed trees and of builds is kept for the trees built
- *     next on its device: at most six blocks and 256 MiB in the process,
- *     given back when an allocation for a build fails.
+ *     next on its device: at most six blocks and 256 MiB in the process.  Where
+ *     a call, a build or a plan finds no room on the device, this memory and
+ *     the buffers above that no call is using are given back first.
  *   - Host ids (`ids` arguments marked "input"): the host leaf of every point
  *     as ot_locate returns it (Algorithm 1's host_cell_id, which Sec. 3.2
  *     makes the prerequisite of interpolation and spreading).  When given,

@@ -225,28 +225,13 @@ extern "C" int ot_batch_plan_create(const ot_tree *tree, const int64_t *offsets,
                    !(mode == OT_SPREAD_ATOMIC && (ops_all & kOpSpread)) && small_rule(tree, p->n_points, ops_all);
     if (sort_points && p->n_points > 0 && !p->use_small) {
         const int64_t n = p->n_points;
-        SortedRoute route{false, false, false};
-        if (!(tuning->flags & OT_TUNE_HOST_MAJOR)) route = sorted_route(tree, n, ops_all, dtype, mode, true);
-        p->use_blocks = route.blocks;
-        p->use_nodes = route.nodes;
-        if (route.wide) {
-            p->wide = hipMalloc(&p->fxws, (size_t)spread_ws_bytes(tree->n_leaves)) == hipSuccess;
-            if (!p->wide) {   // no room for the sums: tiles of points sorted by host
-                (void)hipGetLastError();
-                p->fxws = nullptr;
-                p->use_blocks = p->use_nodes = false;
-            }
-        }
-        p->sort_key = p->use_blocks ? point_sort_by_block(tree->view.nblk) : point_sort_by_host(tree->n_leaves);
         const size_t rec = ((ops_all & (kOpSpread | kOpGrad)) ? 6 : 3) * (size_t)n * (dtype == OT_F32 ? 4 : 8);
         hipError_t e = hipSuccess;
         for (int i = 0; i < 2 && e == hipSuccess; ++i) {
-            e = hipMalloc((void **)&p->skv[i], 8 * (size_t)n);
-            if (e == hipSuccess) e = hipMalloc(&p->srec[i], rec);
+            e = device_malloc((void **)&p->skv[i], 8 * (size_t)n);
+            if (e == hipSuccess) e = device_malloc(&p->srec[i], rec);
         }
-        if (e == hipSuccess) e = hipMalloc(&p->sws, (size_t)point_sort_ws_bytes(n));
-        if (e == hipSuccess && p->use_blocks) e = hipMalloc(&p->blk_mem, (size_t)blk_bytes(tree, n));
-
+        if (e == hipSuccess) e = device_malloc(&p->sws, (size_t)point_sort_ws_bytes(n));
         if (e != hipSuccess) {
             (void)hipGetLastError();
             ot_batch_plan_destroy(p);
@@ -258,7 +243,7 @@ extern "C" int ot_batch_plan_create(const ot_tree *tree, const int64_t *offsets,
                 tuning && (tuning->flags & OT_TUNE_HOST_MAJOR) && p->n_points > 0;
     if (p->use_hm) {
         p->n_win = (p->n_points + kHmWindow - 1) / kHmWindow;
-        if (hipMalloc((void **)&p->fb_list, (size_t)p->n_win * 4) != hipSuccess) {
+        if (device_malloc((void **)&p->fb_list, (size_t)p->n_win * 4) != hipSuccess) {
             (void)hipGetLastError();
             p->fb_list = nullptr;
             ot_batch_plan_destroy(p);
@@ -266,7 +251,7 @@ extern "C" int ot_batch_plan_create(const ot_tree *tree, const int64_t *offsets,
         }
     }
     if (mode == OT_SPREAD_FIXED && (ops_union & kOpSpread)) {
-        if (hipMalloc(&p->fxws, (size_t)spread_ws_bytes(tree->n_leaves)) != hipSuccess) {
+        if (device_malloc(&p->fxws, (size_t)spread_ws_bytes(tree->n_leaves)) != hipSuccess) {
             (void)hipGetLastError();
             p->fxws = nullptr;
             ot_batch_plan_destroy(p);
@@ -286,7 +271,7 @@ extern "C" int ot_batch_plan_create(const ot_tree *tree, const int64_t *offsets,
     (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kfn, block, 0);
     if (per_cu <= 0) per_cu = 1;
     int grid = tuning && tuning->grid ? tuning->grid : std::max(1, cus) * per_cu;
-    if (p->n_tiles > 0 && grid > p->n_tiles && !p->use_blocks) grid = (int)p->n_tiles;
+    if (p->n_tiles > 0 && grid > p->n_tiles) grid = (int)p->n_tiles;
     p->grid = std::max(1, grid);
     if (p->use_hm) {
         const int hops = ops_all & (kOpInterp | kOpSpread);
@@ -300,16 +285,31 @@ extern "C" int ot_batch_plan_create(const ot_tree *tree, const int64_t *offsets,
         int hg = tuning && tuning->grid ? tuning->grid : std::max(1, cus) * hper;
         p->hm_grid = (int)std::max<int64_t>(1, std::min<int64_t>(hg, p->n_win));
     }
-    hipError_t e1 = hipMalloc((void **)&p->tile_start, std::max<size_t>(8, starts.size() * 8));
-    hipError_t e2 = hipMalloc((void **)&p->tile_info, std::max<size_t>(4, infos.size() * 4));
-    hipError_t e3 = hipMalloc((void **)&p->counter, 64);
+    hipError_t e1 = device_malloc((void **)&p->tile_start, std::max<size_t>(8, starts.size() * 8));
+    hipError_t e2 = device_malloc((void **)&p->tile_info, std::max<size_t>(4, infos.size() * 4));
+    hipError_t e3 = device_malloc((void **)&p->counter, 64);
     if (e1 != hipSuccess || e2 != hipSuccess || e3 != hipSuccess) {
         (void)hipGetLastError();
         ot_batch_plan_destroy(p);
         return fail(OT_ERR_OOM, "ot_batch_plan_create: device allocation failed");
     }
-    if (p->use_blocks) {
-        blk_layout(tree, p->n_points, p->blk_mem, p->counter, &p->blk);
+    if (sort_points && p->n_points > 0 && !p->use_small) {
+        // the faster passes' own memory comes last: a plan without room for it
+        // takes tiles of points sorted by host
+        SortedRoute route{false, false, false};
+        if (!(tuning->flags & OT_TUNE_HOST_MAJOR))
+            route = sorted_route(tree, p->n_points, ops_all, dtype, mode, true);
+        if ((route.blocks && device_malloc(&p->blk_mem, (size_t)blk_bytes(tree, p->n_points)) != hipSuccess) ||
+            (route.wide && device_malloc(&p->fxws, (size_t)spread_ws_bytes(tree->n_leaves)) != hipSuccess)) {
+            if (p->blk_mem) (void)hipFree(p->blk_mem);
+            p->blk_mem = nullptr;
+            route = SortedRoute{false, false, false};
+        }
+        p->use_blocks = route.blocks;
+        p->use_nodes = route.nodes;
+        p->wide = route.wide;
+        p->sort_key = p->use_blocks ? point_sort_by_block(tree->view.nblk) : point_sort_by_host(tree->n_leaves);
+        if (p->use_blocks) blk_layout(tree, p->n_points, p->blk_mem, p->counter, &p->blk);
     }
     if (!starts.empty()) {
         hipError_t e = hipMemcpy(p->tile_start, starts.data(), starts.size() * 8, hipMemcpyHostToDevice);

@@ -10,6 +10,7 @@
 
 #include <algorithm>
 
+#include "memory.h"
 #include "ot_common.h"
 
 namespace ot {
@@ -143,7 +144,7 @@ extern "C" int ot_force_mean(const ot_tree *t, void *field, int32_t dtype, int32
     hipStream_t s = (hipStream_t)stream;
     void *owned = nullptr;
     if (!work) {
-        if (hipMallocAsync(&owned, (size_t)ot_force_mean_workspace_bytes(), s) != hipSuccess) {
+        if (device_malloc_async(t->device, &owned, (size_t)ot_force_mean_workspace_bytes(), s) != hipSuccess) {
             (void)hipGetLastError();
             return fail(OT_ERR_OOM, "ot_force_mean: workspace");
         }

@@ -25,4 +25,9 @@ Scratch scratch_take(int device, size_t bytes, hipStream_t s);
 void scratch_give(int device, const Scratch &m, hipStream_t s);   // the call's kernels are enqueued
 void scratch_trees(int device, int change);                       // a tree was built (1) or destroyed (-1)
 
+// hipMalloc on the current device and hipMallocAsync on a stream of `device`;
+// where there is no room, once more after what is kept on it is given back.
+hipError_t device_malloc(void **p, size_t bytes);
+hipError_t device_malloc_async(int device, void **p, size_t bytes, hipStream_t s);
+
 }  // namespace ot

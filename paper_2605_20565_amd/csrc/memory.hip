@@ -12,7 +12,8 @@ namespace {
 // buffer of some 20 MB costs the host 250 us or more (of the 2.4 ms in which a
 // tree of 2.7 M leaves was built and destroyed, 1.4 ms went to hipFree).  At
 // most kKeptBlocks blocks and kKeptBytes are kept, the oldest are freed first,
-// and all of a device's are given back when an allocation on it fails.  Blocks
+// and all of a device's are given back where an allocation of the library finds
+// no room (give_back).  Blocks
 // come here only when no work on them is left, so any stream may have them next.
 constexpr size_t kKeptBlocks = 6, kKeptBytes = size_t(256) << 20;
 // (a plain array: nothing here throws, and trees may be destroyed after the
@@ -35,24 +36,19 @@ Block block_take(size_t bytes)
     Block b;
     b.bytes = (bytes + 0xFFFF) & ~size_t(0xFFFF);
     (void)hipGetDevice(&b.device);
-    std::lock_guard<std::mutex> lock(g_kept_lock);
-    size_t best = kKeptBlocks;
-    for (size_t i = 0; i < g_n_kept; ++i) {
-        const Block &c = g_kept[i];
-        // not more than twice what is asked for
-        if (c.device == b.device && c.bytes >= b.bytes && c.bytes / 2 <= b.bytes &&
-            (best == kKeptBlocks || c.bytes < g_kept[best].bytes))
-            best = i;
+    {
+        std::lock_guard<std::mutex> lock(g_kept_lock);
+        size_t best = kKeptBlocks;
+        for (size_t i = 0; i < g_n_kept; ++i) {
+            const Block &c = g_kept[i];
+            // not more than twice what is asked for
+            if (c.device == b.device && c.bytes >= b.bytes && c.bytes / 2 <= b.bytes &&
+                (best == kKeptBlocks || c.bytes < g_kept[best].bytes))
+                best = i;
+        }
+        if (best < kKeptBlocks) return kept_remove(best);
     }
-    if (best < kKeptBlocks) return kept_remove(best);
-    if (hipMalloc(&b.p, b.bytes) == hipSuccess) return b;
-    (void)hipGetLastError();
-    for (size_t i = g_n_kept; i-- > 0;)
-        if (g_kept[i].device == b.device) (void)hipFree(kept_remove(i).p);
-    if (hipMalloc(&b.p, b.bytes) != hipSuccess) {
-        (void)hipGetLastError();
-        b.p = nullptr;
-    }
+    if (device_malloc(&b.p, b.bytes) != hipSuccess) b.p = nullptr;
     return b;
 }
 
@@ -148,9 +144,34 @@ size_t kept_bytes(const DeviceScratch &d)
     return b;
 }
 
+// What nobody is using of a device's memory: its blocks of gone trees, and (its
+// lock held) its slots.
+void give_back_blocks(int device)
+{
+    std::lock_guard<std::mutex> lock(g_kept_lock);
+    for (size_t i = g_n_kept; i-- > 0;)
+        if (g_kept[i].device == device) (void)hipFree(kept_remove(i).p);
+}
+void give_back_slots(DeviceScratch &d)
+{
+    for (ScratchSlot &c : d.slot)
+        if (!c.busy) slot_free(c);
+}
+void give_back(int device)
+{
+    const OnDevice on(device);
+    const RelaxedCapture relaxed;
+    give_back_blocks(device);
+    if (DeviceScratch *d = scratch_of(device)) {
+        std::lock_guard<std::mutex> lock(d->lock);
+        give_back_slots(*d);
+    }
+    (void)hipGetLastError();
+}
+
 // A slot with new memory of at least `bytes`, or null.  Buffers that nobody is
 // using and that are too small for this call make room, the smallest first.
-ScratchSlot *slot_grow(DeviceScratch &d, size_t bytes)
+ScratchSlot *slot_grow(DeviceScratch &d, int device, size_t bytes)
 {
     size_t want = (bytes + bytes / 4 + 0xFFFFF) & ~size_t(0xFFFFF);   // room for calls a little larger
     if (want > kScratchKeep) want = (bytes + 0xFFFFF) & ~size_t(0xFFFFF);
@@ -167,7 +188,15 @@ ScratchSlot *slot_grow(DeviceScratch &d, size_t bytes)
                 empty->done = nullptr;
                 return nullptr;
             }
-            if (hipMalloc(&empty->p, want) != hipSuccess) {
+            hipError_t e = hipMalloc(&empty->p, want);
+            if (e == hipErrorOutOfMemory) {
+                (void)hipGetLastError();
+                give_back_blocks(device);
+                give_back_slots(d);
+                want = bytes;
+                e = hipMalloc(&empty->p, want);
+            }
+            if (e != hipSuccess) {
                 empty->p = nullptr;
                 return nullptr;
             }
@@ -180,6 +209,38 @@ ScratchSlot *slot_grow(DeviceScratch &d, size_t bytes)
 }
 
 }  // namespace
+
+hipError_t device_malloc(void **p, size_t bytes)
+{
+    hipError_t e = hipMalloc(p, bytes);
+    if (e == hipErrorOutOfMemory) {
+        (void)hipGetLastError();
+        int device = 0;
+        (void)hipGetDevice(&device);
+        give_back(device);
+        e = hipMalloc(p, bytes);
+    }
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        *p = nullptr;
+    }
+    return e;
+}
+
+hipError_t device_malloc_async(int device, void **p, size_t bytes, hipStream_t s)
+{
+    hipError_t e = hipMallocAsync(p, bytes, s);
+    if (e == hipErrorOutOfMemory) {
+        (void)hipGetLastError();
+        give_back(device);
+        e = hipMallocAsync(p, bytes, s);
+    }
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        *p = nullptr;
+    }
+    return e;
+}
 
 Scratch scratch_take(int device, size_t bytes, hipStream_t s)
 {
@@ -197,7 +258,7 @@ Scratch scratch_take(int device, size_t bytes, hipStream_t s)
             (void)hipGetLastError();
             return {nullptr, -1};
         }
-        if (!best) best = slot_grow(*d, bytes);
+        if (!best) best = slot_grow(*d, device, bytes);
         (void)hipGetLastError();
         if (best) {
             best->stream = s;
@@ -206,10 +267,7 @@ Scratch scratch_take(int device, size_t bytes, hipStream_t s)
         }
     }
     void *p = nullptr;
-    if (hipMallocAsync(&p, bytes, s) != hipSuccess) {
-        (void)hipGetLastError();
-        p = nullptr;
-    }
+    (void)device_malloc_async(device, &p, bytes, s);
     return {p, -1};
 }
 

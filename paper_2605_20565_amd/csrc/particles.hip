@@ -8,6 +8,7 @@
 // change itself, so the previous acceleration carries over unchanged.
 #include <hip/hip_runtime.h>
 
+#include "memory.h"
 #include "ot_common.h"
 #include "track_device.h"
 
@@ -271,7 +272,7 @@ extern "C" int ot_particle_sort(const ot_tree *t, int32_t dtype, int64_t n, cons
     hipStream_t s = (hipStream_t)stream;
     void *owned = nullptr;
     if (!work) {
-        if (hipMallocAsync(&owned, (size_t)ot_particle_sort_workspace_bytes(n), s) != hipSuccess) {
+        if (device_malloc_async(t->device, &owned, (size_t)ot_particle_sort_workspace_bytes(n), s) != hipSuccess) {
             (void)hipGetLastError();
             return fail(OT_ERR_OOM, "ot_particle_sort: workspace");
         }

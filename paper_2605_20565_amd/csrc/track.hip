@@ -10,6 +10,7 @@
 #include <hip/hip_runtime.h>
 
 #include "batch_plan.h"
+#include "memory.h"
 #include "ot_common.h"
 #include "track_device.h"
 
@@ -311,7 +312,7 @@ int run_pass(const ot_tree *t, int ops, const void *field, const void *force, co
     if (work && ((uintptr_t)work & 255u)) return fail(OT_ERR_INVALID, "work must be 256-byte aligned");
     void *owned = nullptr;
     if (spread && mode == OT_SPREAD_FIXED && !work) {
-        hipError_t e = hipMallocAsync(&owned, (size_t)spread_ws_bytes(t->n_leaves), s);
+        hipError_t e = device_malloc_async(t->device, &owned, (size_t)spread_ws_bytes(t->n_leaves), s);
         if (e != hipSuccess) {
             (void)hipGetLastError();
             return fail(OT_ERR_OOM, "fixed-point spreading workspace");
