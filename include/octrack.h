@@ -484,11 +484,13 @@ int ot_batch_run(ot_batch_plan *plan, const void *field, const void *force, cons
 int ot_batch_run_grad(ot_batch_plan *plan, const void *field, const void *force, const void *pos,
                       int32_t *ids, void *vel, void *field_out, void *grad, void *stream);
 
-/* Timing of the persistent kernel: with enable = 1, ot_batch_run enqueues
+/* Timing of the pass over the points: with enable = 1, ot_batch_run enqueues
  * the plan's sequence directly on the caller's stream (not through the
  * graph, whose captured events cannot be timed) with a pair of HIP events
- * recorded just before and after the persistent kernel;
- * ot_batch_last_kernel_ms returns the kernel's duration in the last
+ * recorded just before and after the pass: the kernels that interpolate and
+ * spread, without the sort, the clears and the conversion of the sums around
+ * them (runs that are not sorted for their few points: all of the run);
+ * ot_batch_last_kernel_ms returns its duration in the last
  * completed run (OT_ERR_HIP while it is still in flight).  enable = 0 returns
  * to the plan's usual launches (graph replays for OT_TUNE_GRAPH plans). */
 int ot_batch_plan_timing(ot_batch_plan *plan, int32_t enable);

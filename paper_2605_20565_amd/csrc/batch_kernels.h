@@ -149,7 +149,9 @@ int enqueue(ot_batch_plan *p, const void *field, const void *force, const void *
         kpos = r.rec;
         kforce = carry_force ? r.rec + 3 : nullptr;
         kids = nullptr;
-        if (!(p->ops_all & ~kOpLocate)) {
+        if (!(p->ops_all & ~kOpLocate)) {   // ids alone: no pass left, which a timed run times as nothing
+            if (p->timing) OT_HIP(hipEventRecord(p->ev[0], s));
+            if (p->timing) OT_HIP(hipEventRecord(p->ev[1], s));
             OT_HIP(hipGetLastError());
             return OT_OK;
         }
