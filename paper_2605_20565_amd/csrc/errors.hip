@@ -17,8 +17,11 @@ int fail(int code, const std::string &msg)
     return code;
 }
 
+// (The runtime keeps a call's error for the thread's next hipGetLastError,
+// which the next call here would take for its own.)
 int hip_fail(hipError_t e, const char *what)
 {
+    (void)hipGetLastError();
     g_last_error = std::string(what) + ": " + hipGetErrorString(e);
     return OT_ERR_HIP;
 }

@@ -27,3 +27,15 @@ def test_timed_run_has_a_duration(ops, n, sort):
     assert 0.0 <= plan.last_kernel_ms() < 1000.0
     assert torch.equal(ids, t.locate(X))
     plan.close()
+
+
+def test_a_failed_call_does_not_fail_the_next():
+    import paper_2605_20565_amd as ot
+    t = gpu_tree(synth.uniform_tree(2, seed=1))
+    X = torch.rand((100, 3), device="cuda") * 0.999
+    plan = ot.BatchPlan(t, [0, 100], [1])
+    plan.set_timing(True)
+    with pytest.raises(ot.OtError):   # nothing has run yet
+        plan.last_kernel_ms()
+    assert int(t.locate(X).min()) >= 0
+    plan.close()
