@@ -155,8 +155,9 @@ typedef struct {
  * writes each result at its point's input row.  Runs of at least 64 points
  * per block (a cube of 8^3 cells at the root table's level, or the leaves
  * below one split root cell) are sorted by block, and each block with enough
- * points is worked on as a dense grid of its stencil nodes in LDS; block,
- * tile and grid then shape the pass over the other blocks' points only.
+ * points is worked on as a dense grid of its stencil nodes in LDS, the other
+ * blocks' points in short ranges; smaller runs that spread take such ranges
+ * of points sorted by host.
  * Otherwise the points are sorted by host leaf, down to groups of at most 64
  * consecutive ids (two passes up to 4 M leaves, three above), so that
  * neighbouring threads share stencil nodes in cache and in the workgroup's
@@ -165,8 +166,10 @@ typedef struct {
  * sorted at all unless OT_TUNE_HOST_MAJOR asks for it or they spread with
  * OT_SPREAD_ATOMIC.  FP32 plans that do, on trees that their points are not
  * too few for, keep their sums in FP64 (a plan-owned buffer of
- * ot_spread_workspace_bytes) and round them once at the end of a run.  Results are the same bit for bit (FIXED).  Needs the
- * same ops for every instance. */
+ * ot_spread_workspace_bytes) and round them once at the end of a run.  block,
+ * tile and grid shape the tiles of points sorted by host leaf only: blocks,
+ * ranges and runs that are not sorted have shapes of their own.  Results are
+ * the same bit for bit (FIXED).  Needs the same ops for every instance. */
 #define OT_TUNE_SORT_POINTS 1
 
 /* Host-major pass for sorted plans whose instances interpolate or spread
@@ -496,7 +499,9 @@ int ot_batch_run_grad(ot_batch_plan *plan, const void *field, const void *force,
 int ot_batch_plan_timing(ot_batch_plan *plan, int32_t enable);
 int ot_batch_last_kernel_ms(const ot_batch_plan *plan, float *ms);
 
-/* Tiles and workgroups a plan uses (host ints, either may be NULL). */
+/* Tiles and workgroups of a plan's pass (host ints, either may be NULL).
+ * Blocks are cut on the device in every run: n_tiles is then the number of
+ * tiles that full ones would make, and grid the workgroups of each launch. */
 int ot_batch_plan_shape(const ot_batch_plan *plan, int64_t *n_tiles, int32_t *grid);
 
 /* Host-major plans (OT_TUNE_HOST_MAJOR): the number of 256-point windows

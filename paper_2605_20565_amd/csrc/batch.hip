@@ -4,9 +4,9 @@
 // (bubble-driven load imbalance, Sec. 5.2); launching one kernel per set
 // leaves the chip idle on the small ones.  Here the sets are cut into tiles
 // that never straddle a set, a fixed grid of workgroups pulls tiles from a
-// device counter until none are left, and the whole sequence (clears,
-// fixed-point scale, persistent kernel, finalize) is captured once in a HIP
-// graph and replayed.
+// device counter until none are left.  A run enqueues its kernels (sort,
+// clears, passes, finalize) on the caller's stream, or with OT_TUNE_GRAPH
+// replays them as one captured graph.
 #include <hip/hip_runtime.h>
 
 #include <cstring>
@@ -14,6 +14,7 @@
 
 #include "batch_plan.h"
 #include "memory.h"
+#include "node_pass.h"
 #include "ot_common.h"
 #include "point_sort.h"
 #include "track_device.h"
@@ -31,12 +32,9 @@ template <typename T, int MODE>
 const void *hm_fn(int ops);
 constexpr int kHmWindow = 256;   // points per window of the host-major pass (kHmThreads)
 
-namespace {
-
-}  // namespace
-
 int plain_pass(const ot_tree *t, int ops, const void *field, const void *force, const void *pos, int dtype, int64_t n,
                int mode, int32_t *ids, void *vel, void *fout, void *grad, void *work, hipStream_t s);   // track.hip
+int64_t plain_tiles(const ot_tree *t, int ops, int dtype, int64_t n, int mode);                          // track.hip
 
 namespace {
 
@@ -397,8 +395,19 @@ extern "C" int ot_batch_run_grad(ot_batch_plan *p, const void *field, const void
 extern "C" int ot_batch_plan_shape(const ot_batch_plan *p, int64_t *n_tiles, int32_t *grid)
 {
     if (!p) return fail(OT_ERR_INVALID, "plan is NULL");
-    if (n_tiles) *n_tiles = p->n_tiles;
-    if (grid) *grid = p->grid;
+    int64_t tiles = p->n_tiles, groups = p->grid;
+    auto cut = [&](int64_t pts) { return (p->n_points + pts - 1) / pts; };
+    if (p->use_small) {
+        groups = tiles = plain_tiles(p->tree, p->ops_all, p->dtype, p->n_points, p->mode);
+    } else if (p->use_blocks) {
+        tiles = cut(blk_tile_pts(p->tree, p->n_points));
+        groups = p->blk.grid;
+    } else if (p->use_nodes) {
+        tiles = cut(node_range_pts(p->tree, p->n_points, p->dtype == OT_F64 && p->mode == OT_SPREAD_ATOMIC));
+        groups = std::min<int64_t>(tiles, 2 * p->tree->cus);
+    }
+    if (n_tiles) *n_tiles = tiles;
+    if (grid) *grid = (int32_t)groups;
     return OT_OK;
 }
 

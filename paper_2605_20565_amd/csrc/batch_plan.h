@@ -22,6 +22,7 @@ struct BlkWork {
     int grid;                // persistent workgroups of each pass
 };
 int64_t blk_bytes(const ot_tree *t, int64_t n);       // device bytes besides the words
+int64_t blk_tile_pts(const ot_tree *t, int64_t n);    // most points of a tile
 void blk_layout(const ot_tree *t, int64_t n, void *mem, unsigned *words, BlkWork *w);
 // The pass over sorted points: tiles of blocks, short ranges, or neither (tiles
 // of points sorted by host); wide: FP32 sums kept in FP64 (ot_batch_plan::wide).

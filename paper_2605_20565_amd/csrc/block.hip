@@ -7,18 +7,18 @@
 
 namespace ot {
 
-namespace {
-int64_t align256(int64_t b) { return (b + 255) & ~int64_t(255); }
-// a dense block of c points gets ceil(c / blk_tile_pts) tiles; a run of sparse
-// blocks ends at a dense block or at the end of a workgroup's keys
-int64_t max_tiles(int64_t n) { return n / kBlkDense + n / kBlkTileMin + 1; }
-
 // Points per tile: whole blocks in large runs, and in smaller ones short tiles
 // for two workgroups per CU (a tile of 2,000 points takes ~50 us alone).
 int64_t blk_tile_pts(const ot_tree *t, int64_t n)
 {
     return std::min<int64_t>(kBlkTilePts, std::max<int64_t>(kBlkTileMin, n / (2 * t->cus)));
 }
+
+namespace {
+int64_t align256(int64_t b) { return (b + 255) & ~int64_t(255); }
+// a dense block of c points gets ceil(c / blk_tile_pts) tiles; a run of sparse
+// blocks ends at a dense block or at the end of a workgroup's keys
+int64_t max_tiles(int64_t n) { return n / kBlkDense + n / kBlkTileMin + 1; }
 
 int64_t max_ranges(const ot_tree *t, int64_t n)
 {

@@ -11,6 +11,7 @@
 
 #include "batch_plan.h"
 #include "memory.h"
+#include "node_pass.h"
 #include "ot_common.h"
 #include "track_device.h"
 
@@ -252,6 +253,30 @@ int nodes_pass(const ot_tree *t, int ops, const void *field, const void *force, 
     return rc;
 }
 
+// Enough workgroups to give every CU two, when there are points for them:
+// small sets get narrower workgroups and one point per thread (their time is
+// latency, not throughput); large ones up to kMaxPointsPerThread points per
+// thread.
+void track_shape(const ot_tree *t, int64_t n, int &threads, int64_t &tile)
+{
+    const int64_t want = 2 * (int64_t)t->cus;
+    threads = 256;
+    while (threads > 64 && (n + threads - 1) / threads < want) threads >>= 1;
+    tile = threads * std::max<int64_t>(1, std::min<int64_t>(kMaxPointsPerThread, n / ((int64_t)threads * want)));
+}
+
+// Most points for which an unsorted call takes the node-parallel pass.  Sums in
+// FP32 take the pass with the fewest adds to a leaf: workgroups of 28 points
+// had made them up to 1.3 times less exact (16 k markers in order: 1.6e-7 ->
+// 2.1e-7).
+int64_t nodes_max(const ot_tree *t, int ops, int dtype, int mode)
+{
+    if (!(ops & ~kOpLocate)) return 0;
+    if (!(ops & kOpSpread)) return kNodesMaxGather;
+    if (t->n_leaves <= kFewLeaves) return mode == OT_SPREAD_FIXED ? kNodesMaxFewLeaves : 0;
+    return mode == OT_SPREAD_ATOMIC && dtype == OT_F32 ? 0 : kNodesMaxSpread;
+}
+
 // The pass's kernel alone, no clearing, scale or conversion around it.
 int launch_ops(const ot_tree *t, int ops, const void *field, const void *force, const void *pos, int dtype, int64_t n,
                int mode, int32_t *ids, void *vel, void *fout, void *grad, const FxWs &ws, const int32_t *hid,
@@ -259,15 +284,9 @@ int launch_ops(const ot_tree *t, int ops, const void *field, const void *force, 
 {
     int rc = OT_OK;
     if (n > 0) {
-        // Enough workgroups to give every CU two, when there are points for
-        // them: small sets get narrower workgroups and one point per thread
-        // (their time is latency, not throughput); large ones up to
-        // kMaxPointsPerThread points per thread.
-        const int64_t want = 2 * (int64_t)t->cus;
-        int threads = 256;
-        while (threads > 64 && (n + threads - 1) / threads < want) threads >>= 1;
-        const int64_t ppt = std::max<int64_t>(1, std::min<int64_t>(kMaxPointsPerThread, n / ((int64_t)threads * want)));
-        const int64_t tile = (int64_t)threads * ppt;
+        int threads;
+        int64_t tile;
+        track_shape(t, n, threads, tile);
         dim3 b(threads), g((unsigned)((n + tile - 1) / tile));
         if (dtype == OT_F32)
             rc = mode == OT_SPREAD_FIXED
@@ -320,11 +339,6 @@ int run_pass(const ot_tree *t, int ops, const void *field, const void *force, co
         work = owned;
     }
     const FxWs ws = fx_ws(spread && mode == OT_SPREAD_FIXED ? work : nullptr);
-    // Sums in FP32 take the pass with the fewest adds to a leaf: workgroups of
-    // 28 points had made them up to 1.3 times less exact (16 k markers in order:
-    // 1.6e-7 -> 2.1e-7).
-    const bool f32_sums = spread && mode == OT_SPREAD_ATOMIC && dtype == OT_F32;
-    const bool few = spread && t->n_leaves <= kFewLeaves;
     if (may_sort && !hid && plain_sorts(t, n, ops, dtype, mode)) {
         bool handled;
         rc = sorted_pass(t, ops, field, force, pos, dtype, n, mode, accumulate, ids, vel, fout, grad, work, s, handled);
@@ -333,10 +347,7 @@ int run_pass(const ot_tree *t, int ops, const void *field, const void *force, co
             return rc;
         }
     }
-    const int64_t nodes_max = !spread ? kNodesMaxGather
-                              : !few  ? (f32_sums ? 0 : kNodesMaxSpread)
-                                      : (mode == OT_SPREAD_FIXED ? kNodesMaxFewLeaves : 0);
-    if (n > 0 && (ops & ~kOpLocate) && n <= nodes_max) {
+    if (n > 0 && n <= nodes_max(t, ops, dtype, mode)) {
         rc = dtype == OT_F32 ? nodes_pass<float>(t, ops, field, force, pos, dtype, n, mode, accumulate, ids, vel, fout,
                                                  grad, ws, hid, s)
                              : nodes_pass<double>(t, ops, field, force, pos, dtype, n, mode, accumulate, ids, vel, fout,
@@ -359,6 +370,16 @@ int plain_pass(const ot_tree *t, int ops, const void *field, const void *force, 
                int mode, int32_t *ids, void *vel, void *fout, void *grad, void *work, hipStream_t s)
 {
     return run_pass(t, ops, field, force, pos, dtype, n, mode, 0, ids, vel, fout, grad, nullptr, work, s, false);
+}
+
+// Workgroups of plain_pass, one a tile.
+int64_t plain_tiles(const ot_tree *t, int ops, int dtype, int64_t n, int mode)
+{
+    if (n <= nodes_max(t, ops, dtype, mode)) return (n + kNodePts - 1) / kNodePts;
+    int threads;
+    int64_t tile;
+    track_shape(t, n, threads, tile);
+    return (n + tile - 1) / tile;
 }
 
 // ot_spread without any allocation (work given, or ATOMIC).

@@ -2,8 +2,8 @@
 
 Tries workgroup size, tile size, grid size and in-run point sorting for one
 (tree, instances, precision, spreading mode) signature, times each candidate
-plan with events on the current stream (graph replays, after a warm-up
-replay), and keeps the fastest.  Results are cached in a JSON file keyed by
+plan with events on the current stream (after a warm-up run), and keeps the
+fastest.  Sorted plans whose passes have a shape of their own are timed once.  Results are cached in a JSON file keyed by
 the device name and the workload signature, so a later run with the same
 shapes skips the search.
 """
@@ -78,7 +78,7 @@ def store_cache(path: str, key: str, entry: dict) -> None:
 
 
 def time_plan(plan, pos, field, force, ids, vel, fout, reps: int = 5) -> float:
-    """Average milliseconds per replay of a plan."""
+    """Average milliseconds per run of a plan."""
     plan.run(pos, field=field, force=force, ids=ids, vel=vel, field_out=fout)
     torch.cuda.synchronize()
     a = torch.cuda.Event(enable_timing=True)
@@ -113,12 +113,19 @@ def tune(tree, offsets: Sequence[int], ops: Sequence[int], pos, field=None, forc
     fout = torch.empty((tree.n_leaves, 3), dtype=dtype, device=dev)
     timings: Dict[str, float] = {}
     best, best_ms = None, float("inf")
+    fixed_shape = False   # a sorted plan has been timed whose pass has a shape of its own
     for c in cands:
         if c.sort_points and not uniform:
             continue
         t0 = time.perf_counter()
         plan = ot.BatchPlan(tree, offsets, ops, dtype=dtype, mode=mode, block=c.block, tile=c.tile, grid=c.grid,
                             sort_points=c.sort_points)
+        if c.sort_points and plan.shape()[0] != -(-n // c.tile):
+            # blocks, ranges and unsorted small runs ignore block, tile and grid: the candidates are one plan
+            if fixed_shape:
+                plan.close()
+                continue
+            fixed_shape = True
         ms = time_plan(plan, pos, field, force, ids, vel, fout, reps)
         plan.close()
         timings[c.label()] = round(ms, 4)
