@@ -40,31 +40,51 @@ BYTES_PER_LEAF = {"f32": 9 + 12 + 12, "f64": 9 + 24 + 24}
 
 
 COPY_BYTES = 1 << 30
-PASSES = ("k_block<", "k_node_ranges<", "k_batch<")
+# The passes over the points, and where a kernel's template arguments hold its ops (-1: any).
+PASSES = {"k_block": 2, "k_node_ranges": 1, "k_hm": 3, "k_batch": -1}
+STEP_OPS = 6   # interpolate + spread: the bench's own count of touched leaves only spreads
+
+
+def pass_of(kernel):
+    """Name of the pass that a dispatch of the step's ops belongs to, or None."""
+    import re
+    m = re.search(r"\b(k_\w+)<([^>]*)>", kernel)
+    if not m or m.group(1) not in PASSES:
+        return None
+    at, targs = PASSES[m.group(1)], [a.strip() for a in m.group(2).split(",")]
+    return m.group(1) if at < 0 or targs[at] == str(STEP_OPS) else None
 
 
 def write_traffic(args, fetch_csv, write_csv):
-    """HBM bytes per run of the persistent passes (the block pass and the short
-    ranges, or k_batch) from FETCH_SIZE / WRITE_SIZE (KiB per dispatch; a run
-    is a k_fx_finalize dispatch, or without those a dispatch), each scaled by what the same counter reads for the 1 GiB
-    calibration copy (which reads and writes exactly COPY_BYTES)."""
+    """HBM bytes per run of the plan's passes from FETCH_SIZE / WRITE_SIZE (KiB
+    per dispatch), each scaled by what the same counter reads for the 1 GiB
+    calibration copy (which reads and writes exactly COPY_BYTES).  A run
+    launches each of its kernels once, so every kernel's dispatches count the
+    runs; where they differ the runs cannot be counted and nothing is written."""
     import csv
 
     def per_kernel(path, counter):
         rows = [r for r in csv.DictReader(open(path)) if r["Counter_Name"] == counter]
-        batch = [float(r["Counter_Value"]) for r in rows if any(k in r["Kernel_Name"] for k in PASSES)]
-        runs = sum("k_fx_finalize" in r["Kernel_Name"] for r in rows) or len(batch)
+        by_kernel = {}
+        for r in rows:
+            if pass_of(r["Kernel_Name"]):
+                by_kernel.setdefault(r["Kernel_Name"], []).append(float(r["Counter_Value"]))
         copies = [float(r["Counter_Value"]) for r in rows if "copy" in r["Kernel_Name"].lower()]
-        if not batch or not copies:
+        if not by_kernel or not copies:
             raise SystemExit(f"{path}: no pass or copy dispatch with {counter}")
-        return sum(batch) / runs, max(copies)
+        runs = {len(v) for v in by_kernel.values()}
+        if len(runs) != 1:
+            raise SystemExit(f"{path}: the passes' kernels were dispatched {sorted(runs)} times: runs of several plans")
+        return sum(map(sum, by_kernel.values())) / runs.pop(), max(copies), {pass_of(k) for k in by_kernel}
 
-    fb, fc = per_kernel(fetch_csv, "FETCH_SIZE")
-    wb, wc = per_kernel(write_csv, "WRITE_SIZE")
+    fb, fc, names = per_kernel(fetch_csv, "FETCH_SIZE")
+    wb, wc, wnames = per_kernel(write_csv, "WRITE_SIZE")
+    if names != wnames:
+        raise SystemExit(f"the two collections hold different passes: {sorted(names)} and {sorted(wnames)}")
     ff = (COPY_BYTES / 1024.0) / fc
     fw = (COPY_BYTES / 1024.0) / wc
-    rec = {"kernel": "k_block + k_node_ranges", "config": args.config, "dtype": args.dtype, "mode": args.mode,
-           "kernel_hash": kernel_source_hash(),
+    rec = {"kernel": " + ".join(k for k in PASSES if k in names), "config": args.config, "dtype": args.dtype,
+           "mode": args.mode, "kernel_hash": kernel_source_hash(),
            "fetch_kib_per_launch": fb, "write_kib_per_launch": wb,
            "copy_fetch_kib": fc, "copy_write_kib": wc, "factor_fetch": ff, "factor_write": fw,
            "fetch_bytes": fb * 1024 * ff, "write_bytes": wb * 1024 * fw,
@@ -237,16 +257,20 @@ def main():
     alg_bytes = n * BYTES_PER_POINT[args.dtype] + touched * BYTES_PER_LEAF[args.dtype]
     achieved = alg_bytes / (kernel_ms * 1e-3) / 1e9
     traffic = None
+    passes = "k_hm + k_batch" if args.host_major else "passes over sorted points" if shape["sort_points"] else "k_batch"
     if os.path.exists(PROFILE_TRAFFIC):
         with open(PROFILE_TRAFFIC) as f:
             tr = json.load(f)
         if tr.get("kernel_hash") == kernel_source_hash() and tr.get("dtype") == args.dtype \
-                and tr.get("mode") == args.mode and tr.get("config") == args.config:
+                and tr.get("mode") == args.mode and tr.get("config") == args.config and args.scale == 1.0 \
+                and ("k_hm" in tr["kernel"]) == args.host_major \
+                and (tr["kernel"] == "k_batch") == (not shape["sort_points"]):
             traffic = tr.get("bytes_per_launch")
+            passes = tr["kernel"]
     step_gbps = alg_bytes / (ms_per_step * 1e-3) / 1e9
     roofline = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBPS, "unit": "GB/s",
                 "frac": round(achieved / HBM_PEAK_GBPS, 4), "traffic": traffic,
-                "kernel": "k_hm + k_batch" if args.host_major else "k_block + k_node_ranges", "kernel_ms": round(kernel_ms, 4),
+                "kernel": passes, "kernel_ms": round(kernel_ms, 4),
                 "algorithmic_bytes": int(alg_bytes), "touched_leaves": touched,
                 "step_achieved": round(step_gbps, 1), "step_frac": round(step_gbps / HBM_PEAK_GBPS, 4)}
     log(f"[bench] passes {kernel_ms:.3f} ms, {achieved:.0f} GB/s algorithmic ({achieved / HBM_PEAK_GBPS:.1%} of peak); "
@@ -264,8 +288,7 @@ def main():
         "vs_baseline": None, "dtype": args.dtype, "data": "synthetic",
         "config": {**workload_desc(w, args.config), "precision": args.dtype, "spread_mode": args.mode,
                    "point_order": "host-leaf order (pre-sorted)" if args.presorted else "random (as generated)",
-                   "path": "batched persistent kernel" + (", in-step sort of points by host leaf"
-                                                          if shape["sort_points"] else ""),
+                   "path": "batched plan" + (", points sorted in every step" if shape["sort_points"] else ""),
                    "block": shape["block"] or "library default", "tile": shape["tile"] or "library default",
                    "tiles": n_tiles, "workgroups": grid, "autotuned": not args.no_tune,
                    "host_major_windows": hm_windows, "windows_to_per_point_pass": hm_handed},
@@ -301,7 +324,7 @@ def side_measurements(args, w, tree, pos, force, field, plan, step, dev, dt, ot,
         torch.cuda.synchronize()
         return (time.perf_counter() - a) * 1e3 / reps
 
-    # plain FP64 GPU path (one fused launch, FP64 atomics), the speedup's denominator
+    # plain FP64 GPU path (one call a step, which sorts its points; FP64 atomics), the speedup's denominator
     p64 = torch.from_numpy(w.points).to(dev, torch.float64)
     f64 = torch.from_numpy(w.forces).to(dev, torch.float64)
     fl64 = tree.permute_rows(torch.from_numpy(w.field).to(dev, torch.float64))
@@ -311,7 +334,7 @@ def side_measurements(args, w, tree, pos, force, field, plan, step, dev, dt, ot,
     ms64 = timeit(lambda: tree.track(p64, field=fl64, force=f64, mode="atomic", ids=i64, vel=v64, field_out=o64),
                   max(3, args.steps // 2))
     res["fp64_plain"] = {"ms_per_step": round(ms64, 4), "value": n / (ms64 * 1e-3), "spread_mode": "atomic",
-                         "path": "one fused launch per step"}
+                         "path": "one plain fused call per step (sorts its points)"}
     ms_main = timeit(step, max(3, args.steps // 2))
     res["speedup_vs_fp64_plain"] = round(ms64 / ms_main, 3)
     # the batched path in FP64 (FIXED, sorted), same launch shape as the measured step
@@ -457,7 +480,7 @@ def workload3_measure(args, dev, ot, torch, timeit):
            "per_instance_launches_ms_per_step": round(ms_i, 4), "batched_speedup": round(ms_i / ms_b, 2),
            "batched_shape": best.label(),
            "touched_leaves": touched, "batched_roofline": _roof(n, touched, ms_b, "f32"),
-           "path": "batched persistent kernel, in-step sort; FP32, FIXED"}
+           "path": "batched plan, points sorted in every step; FP32, FIXED"}
     tree.close()
     return out
 
