@@ -220,8 +220,10 @@ SortedRoute sorted_route(const ot_tree *t, int64_t n, int ops, int dtype, int mo
 bool plain_sorts(const ot_tree *t, int64_t n, int ops, int dtype, int mode)
 {
     const bool f32_sums = dtype == OT_F32 && mode == OT_SPREAD_ATOMIC;
-    return (ops & kOpSpread) && t->n_leaves > kFewLeaves && n <= INT32_MAX &&
-           n >= (f32_sums ? kSortMinF32Sums : kSortMinSpread) && (!f32_sums || wide_fits(t, n, false));
+    const bool f64_gathers = dtype == OT_F64 && (ops & (kOpInterp | kOpGrad));
+    const int64_t least = f32_sums ? kSortMinF32Sums : f64_gathers ? kSortMinF64Both : kSortMinSpread;
+    return (ops & kOpSpread) && t->n_leaves > kFewLeaves && n >= least && n <= INT32_MAX &&
+           (!f32_sums || wide_fits(t, n, false));
 }
 
 // Sorted plans of so few points that the plain passes are faster unsorted

@@ -59,14 +59,23 @@ constexpr int64_t kNodesMaxGather = 16384;
 // 5.6e-16, 50 k 9.5e-16 -> 1.28e-15).
 static_assert(kFewLeaves == kSmallSlots, "every leaf has a slot of its own");
 constexpr int64_t kNodesMaxFewLeaves = 8192;
-// Larger sets are sorted first, as a sorted plan does, when the call searches
-// the hosts itself and may allocate: calls that spread from kSortMinSpread
-// points (random points on 38 k leaves, fixed point: 60 k 88 -> 58 us, 100 k
-// 238 -> 63, 1 M 3406 -> 160; markers in order 100 k 66 -> 63, 1 M 236 -> 179;
-// FP64 forward and backward of 50 k random points 118 unsorted, 132 sorted), sums
-// in FP32, which do not take the node pass, from kSortMinF32Sums (38 k leaves, 28 k
-// random points 107 us unsorted, 28 k markers in order 53; 40 k 148 -> 52 and
-// 88 -> 45).  Calls that only gather take their points as they are: sorting
+// Larger sets are sorted first, as a sorted plan does, when the call spreads,
+// searches the hosts itself and may allocate.  What that gains depends on the
+// order of the points, which nothing tells before the call: random ones fill
+// an unsorted workgroup's spreading table many times over, those in order do
+// not.  Unsorted against sorted, us a call on 38 k leaves, spreading in fixed
+// point FP32: random points 65 k 95 (node pass) and 58, 100 k 238 and 64, 200 k
+// 600 and 91, 1 M 3400 and 168; markers in order 65 k 86 and 56, 100 k 65 and 64,
+// 200 k 86 and 93, 400 k 128 and 129, 1 M 243 and 187; points in host order 65 k
+// 26 and 58, 100 k 46 and 63, 200 k 72 and 91, 400 k 174 and 127.  The lines lie
+// where random points gain by half (kSortMinSpread); points in order lose up to
+// some 400 k, and programs that keep them so have their hosts' ids to give,
+// which keeps a call unsorted.  FP64 with gathers, whose ranges are slower,
+// sort where the node pass ends (forward and backward of random points 65 k 102
+// and 85, 100 k 247 and 95; markers in order 100 k 70 and 96, host order 48 and
+// 95); sums in FP32, which do not take the node pass, from kSortMinF32Sums
+// (random points 40 k 157 and 54, markers in order 88 and 48, host order 40 and
+// 54).  Calls that only gather take their points as they are: sorting
 // would gain with random points on large trees what it would lose with points
 // in host order, as particles are kept (interpolation of 10^7 points, FP32, on
 // 2.7 M leaves 2743 -> 702 us and 302 -> 535, on 38 k leaves 1175 -> 657 and 179 ->
