@@ -86,6 +86,7 @@ struct ScratchSlot {
     hipEvent_t done;     // the last call's kernels
     hipStream_t stream;  // and its stream
     bool busy;           // a call is enqueueing
+    bool used;           // done has been recorded for this memory
 };
 struct DeviceScratch {
     std::mutex lock;
@@ -132,7 +133,11 @@ struct OnDevice {
 
 void slot_free(ScratchSlot &c)
 {
-    if (c.p) (void)hipFree(c.p);   // waits for its last call
+    if (c.p) {
+        if (c.used) (void)hipEventSynchronize(c.done);   // its last call
+        (void)hipFree(c.p);
+    }
+    c.used = false;
     c.p = nullptr;
     c.bytes = 0;
 }
@@ -250,11 +255,11 @@ Scratch scratch_take(int device, size_t bytes, hipStream_t s)
         std::lock_guard<std::mutex> lock(d->lock);
         ScratchSlot *best = nullptr;
         for (ScratchSlot &c : d->slot)
-            if (!c.busy && c.bytes >= bytes && (c.stream == s || hipEventQuery(c.done) == hipSuccess) &&
+            if (!c.busy && c.bytes >= bytes && (c.stream == s || !c.used || hipEventQuery(c.done) == hipSuccess) &&
                 (!best || c.bytes < best->bytes))
                 best = &c;
         (void)hipGetLastError();   // an event not reached yet is no error
-        if (best && hipStreamWaitEvent(s, best->done, 0) != hipSuccess) {
+        if (best && best->used && hipStreamWaitEvent(s, best->done, 0) != hipSuccess) {
             (void)hipGetLastError();
             return {nullptr, -1};
         }
@@ -285,7 +290,11 @@ void scratch_give(int device, const Scratch &m, hipStream_t s)
     if (hipEventRecord(c.done, s) != hipSuccess) {
         // without the event the buffer cannot be handed on in order
         (void)hipGetLastError();
+        (void)hipStreamSynchronize(s);
+        c.used = false;
         slot_free(c);
+    } else {
+        c.used = true;
     }
     c.busy = false;
 }
