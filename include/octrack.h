@@ -60,7 +60,10 @@
  *     the call takes each point's host from it instead of searching the
  *     tree; -1 or an id outside [0, n_leaves) means "no host".  NULL: the
  *     call searches.  Ids that are not the points' hosts give meaningless
- *     (but in-bounds) results.
+ *     (but in-bounds) results.  Calls with ids never sort their points: that
+ *     suits points in host order (ot_particle_sort) and markers in order,
+ *     which sorting would slow down up to some 400,000 points; a million
+ *     points in random order spread 15 to 20 times slower than without ids.
  *   - Return value: OT_OK (0) or a negative OT_ERR_* code; ot_last_error()
  *     returns a message for the calling thread's last failure.
  */

@@ -294,7 +294,9 @@ class Tree:
                accumulate: bool = False, ids: Optional[torch.Tensor] = None,
                work: Optional[torch.Tensor] = None) -> torch.Tensor:
         """Leaf field of the spread forces; ids: known host ids; work: FIXED mode's workspace
-        (``workspace()``; a fresh one per call when None)."""
+        (``workspace()``; a fresh one per call when None).  A large call without ids sorts its points; one
+        with ids takes them in their order, which suits points kept in host order or markers in order (for a
+        million points in random order it is 15 to 20 times slower)."""
         pos = _rows3(pos, "pos")
         force = _rows3(force, "force")
         if force.dtype != pos.dtype or force.shape[0] != pos.shape[0]:
@@ -368,7 +370,7 @@ class Tree:
                         grad_field: Optional[torch.Tensor] = None, grad_pos: Optional[torch.Tensor] = None,
                         ids: Optional[torch.Tensor] = None, work: Optional[torch.Tensor] = None):
         """Backward of `interpolate` in one pass: (spread(grad_vel), grad_pos(field, grad_vel)); an output
-        not asked for is None."""
+        not asked for is None.  ids: as in `spread`."""
         pos = _rows3(pos, "pos")
         field = _rows3(field, "field")
         grad_vel = _rows3(grad_vel, "grad_vel")

@@ -12,7 +12,7 @@
 namespace ot {
 struct BlkTile;
 // Device memory of a run's block pass (block_pass.h): work words (counts and
-// queues), tiles of root cubes and of sub-tables, and the per-point pass's
+// queues), tiles of root cubes and of sub-tables, and the sparse blocks'
 // ranges (first sorted point, count).
 struct BlkWork {
     int64_t n;               // points

@@ -27,7 +27,7 @@ int64_t max_ranges(const ot_tree *t, int64_t n)
 
 // The blocks among the sorted words, and the passes' work: tiles of the blocks
 // with enough points (root cubes and sub-tables apart), and ranges of at most
-// kBlkWindow points for the per-point pass (sparser blocks next to each other
+// kBlkWindow points for the node-parallel pass (sparser blocks next to each other
 // in the order, and points without a host).  A workgroup takes kBlkKeys - 1
 // consecutive keys; eight lanes find a key's first point, probing eight places
 // of the remaining range at once, so a search is ~log_9 n dependent loads.

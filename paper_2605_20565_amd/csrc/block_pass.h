@@ -24,13 +24,13 @@
 //
 // Measured (FP32, fixed point, interpolation and spreading): 10^7 points on a
 // tree of 2.66 M leaves 0.60 ms against 1.05 of the per-point pass, 10^8 points
-// in shells on 20 M leaves 8.3 against 10.7 ms; the sort passes need the block
+// in shells on 20 M leaves 5.8 against 10.7 ms; the sort passes need the block
 // bits only (two passes instead of three above 4 M leaves).
 //
 // Values are those of the per-point pass: the same weights, the same order of
 // the interpolation sums and the same rounded fixed-point contributions.
-// Blocks with few points are left to the per-point pass (a
-// tile's grid costs more than their points do).
+// Blocks with few points are left to short ranges of points (node_pass.h): a
+// tile's grid costs more than their points do.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -54,11 +54,11 @@ struct BlkTile {
 // Device words of a plan's block pass, zeroed before each run: counts of
 // tiles and ranges, and the tile queues.
 enum : int { kBlkRootTiles = 3, kBlkSubTiles = 4, kBlkRanges = 5, kBlkRootQueue = 6, kBlkSubQueue = 7 };
-constexpr int kBlkWindow = 256;     // most points per range of the per-point pass
+constexpr int kBlkWindow = 256;     // most points per range of points in sparse blocks
 // Fewest points of a block that gets tiles: a tile's grid (lookups, field
-// loads, clears, flush) costs about as much as the per-point pass of a few
+// loads, clears, flush) costs about as much as the other passes over a few
 // hundred points.  Measured on 16.9 M points in 17.1 M leaves (60 k sub-tables
-// of ~37 points): from 192 points 1.04 ms (per-point) + 0.01 (tiles), from 64
+// of ~37 points): from 192 points 1.04 ms (sparse blocks) + 0.01 (tiles), from 64
 // points 0.95 + 0.81, from 24 points 0.80 + 1.37.
 constexpr int kBlkDense = 192;
 constexpr int kBlkTilePts = 3072;   // most points per tile
@@ -140,7 +140,7 @@ constexpr int64_t kBlkStreamBytes = int64_t(256) << 20;
 // l0 + g) when the leaf is coarser than the grid: the leaf's cell in the grid
 // of its own level, or of its cells in the coarsest grid the first one there.
 // All of a leaf's nodes then reach device memory with one add, as one table
-// slot of the per-point pass would (FP32 atomic sums are rounded there).
+// slot of the per-point pass would (atomic sums are rounded there).
 __device__ __forceinline__ int blk_canonical(int level, int l0, const uint32_t a[3], int g, const int n[3])
 {
     const int gg = max(level - l0, 1), k = max(l0 + 1 - level, 0);

@@ -1,15 +1,15 @@
-// Sorting the points of a batched run by host leaf, carrying their
-// positions and forces with them.
+// Sorting the points of a run by host leaf or block, carrying their positions
+// and forces with them.
 //
 // Neighbouring threads of the tracking pass then work on neighbouring host
 // cells: their stencil nodes share cache lines and the workgroup's spreading
 // table, and positions and forces are read with coalesced loads.  Each point
-// is one 64-bit word (host's leaf entry) << 32 | input index plus one record of R values
+// is one 64-bit word (host's leaf entry or block key) << 32 | input index plus one record of R values
 // (position, then force when spreading).  The passes order by key bits
-// [shift, shift + bits) only (groups of 2^shift consecutive leaves; 8-bit
-// LSD passes, see point_sort_key_bits).
+// [shift, shift + bits) only (groups of 2^shift consecutive leaves, or whole
+// block keys; LSD passes of 8 bits at most, point_sort_by_host and _by_block).
 //
-// A pass takes tiles of 2048 points: the keys are staged in LDS with
+// A pass takes tiles of 2048 points (512 or 1024 in small runs): the keys are staged in LDS with
 // coalesced loads, ranked by the digit (stably, with one 1-bit split per digit bit,
 // except in the first pass, whose order no later pass relies on: there each
 // key takes the next slot of its digit from an LDS counter), and every
