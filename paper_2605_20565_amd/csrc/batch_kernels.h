@@ -98,8 +98,8 @@ __global__ __launch_bounds__(512) void k_batch(TreeView tv, const int64_t *__res
 
 // Instantiated in block_inst.hip: the block pass over sorted points.
 template <typename T, int MODE>
-int enqueue_blocks(const ot_tree *t, BlkWork &w, int ops, const uint64_t *kv, const T *rec, const T *field, T *vel,
-                   T *fout, const FxWs &ws, T *grad, hipStream_t s);
+int enqueue_blocks(const ot_tree *t, BlkWork &w, int ops, const uint64_t *kv, const T *rec, const T *pos, const T *vec,
+                   const T *field, T *vel, T *fout, const FxWs &ws, T *grad, hipStream_t s);
 
 // Instantiated in node_inst.hip: the node-parallel pass over sorted ranges.
 template <typename T, int MODE>
@@ -201,8 +201,9 @@ int enqueue(ot_batch_plan *p, const void *field, const void *force, const void *
     if (p->sort_points) fb = FbTiles{nullptr, nullptr, (int64_t)p->tile, n, (uint32_t)bops};
     if (p->sort_points && n > 0 && (p->use_blocks || p->use_nodes)) {
         // dense blocks first, then the ranges of points in sparse ones (or all points)
-        if (p->use_blocks && (rc = enqueue_blocks<T, MODE>(t, p->blk, bops, kv, kpos, (const T *)field, (T *)vel,
-                                                           (T *)fout, ws, (T *)grad, s)))
+        if (p->use_blocks && (rc = enqueue_blocks<T, MODE>(t, p->blk, bops, kv, kpos, (const T *)pos,
+                                                           (const T *)force, (const T *)field, (T *)vel, (T *)fout, ws,
+                                                           (T *)grad, s)))
             return rc;
         constexpr bool atomic_f64 = sizeof(T) == 8 && MODE == kModeAtomic;
         const NodeRanges nr = p->use_blocks ? NodeRanges{p->blk.ranges, p->counter + kBlkRanges, n, kBlkWindow, false}

@@ -421,23 +421,6 @@ __global__ __launch_bounds__((BlkThreads<T, ROOT>::value), (BlkThreads<T, ROOT>:
                             }
                         }
                     }
-                    if constexpr ((OPS & kOpGrad) != 0) {
-                        // a node that is not there has field 0, which an infinite
-                        // vector would turn into NaN: once more without such nodes
-                        if (!(isfinite(F[0]) && isfinite(F[1]) && isfinite(F[2]))) {
-                            G[0] = G[1] = G[2] = T(0);
-#pragma unroll
-                            for (int i27 = 0; i27 < 27; ++i27) {
-                                const int ox = i27 % 3, oy = (i27 / 3) % 3, oz = i27 / 9;
-                                const int q = h - 1 + ox + E * ((oy - 1) + E * (oz - 1));
-                                if (sh.ent[q] == kBlkNoNode) continue;
-                                const T dot = fma(F[0], sh.u[0][q], fma(F[1], sh.u[1][q], F[2] * sh.u[2][q]));
-                                G[0] = fma(dot * dw[0][ox], w[1][oy] * w[2][oz], G[0]);
-                                G[1] = fma(dot * w[0][ox], dw[1][oy] * w[2][oz], G[1]);
-                                G[2] = fma(dot * w[0][ox], w[1][oy] * dw[2][oz], G[2]);
-                            }
-                        }
-                    }
                     if (OPS & kOpInterp) blk_store(vel + 3 * kd, U, stream);
                     if (OPS & kOpGrad) blk_store(grad + 3 * kd, G, stream);
                 }
