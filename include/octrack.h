@@ -167,7 +167,7 @@ typedef struct {
  * spreading table.  Runs of few points (under 55,000 that spread, under
  * 100,000 that do not) and runs that spread on at most 512 leaves are not
  * sorted at all unless OT_TUNE_HOST_MAJOR asks for it or they spread with
- * OT_SPREAD_ATOMIC.  FP32 plans that do, on trees that their points are not
+ * OT_SPREAD_ATOMIC (FP64: more than 1,024 points).  FP32 plans that do, on trees that their points are not
  * too few for, keep their sums in FP64 (a plan-owned buffer of
  * ot_spread_workspace_bytes) and round them once at the end of a run.  block,
  * tile and grid shape the tiles of points sorted by host leaf only: blocks,

@@ -218,9 +218,8 @@ extern "C" int ot_batch_plan_create(const ot_tree *tree, const int64_t *offsets,
     p->sort_points = sort_points;
     p->ops_all = ops_all;
     p->grad_plan = (ops_union & kOpGrad) != 0;
-    // atomic sums keep their tiles of sorted points, which split a leaf's sum least
     p->use_small = sort_points && !(tuning->flags & OT_TUNE_HOST_MAJOR) &&
-                   !(mode == OT_SPREAD_ATOMIC && (ops_all & kOpSpread)) && small_rule(tree, p->n_points, ops_all);
+                   small_rule(tree, p->n_points, ops_all, dtype, mode);
     if (sort_points && p->n_points > 0 && !p->use_small) {
         const int64_t n = p->n_points;
         const size_t rec = ((ops_all & (kOpSpread | kOpGrad)) ? 6 : 3) * (size_t)n * (dtype == OT_F32 ? 4 : 8);

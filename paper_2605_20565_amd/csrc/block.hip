@@ -169,18 +169,21 @@ void blk_layout(const ot_tree *t, int64_t n, void *mem, unsigned *words, BlkWork
 constexpr int64_t kBlkMinSpread = 400000, kBlkMinBoth = 300000;
 constexpr int64_t kBlkMinGather = 2000000;
 constexpr int64_t kNodeMaxSpread = 400000;
-// FP64 with gathers: blocks from 1 M points (0.6 M leaves 518 us by ranges, 311
-// blocks, 310 tiles) or where four to a leaf are there (400 k on 14 k leaves 236,
-// 204, 287), ranges below that (200 k on 2.7 M leaves 215 by ranges, 392 by tiles;
-// markers there 197 and 150).
-constexpr int64_t kBlkMinF64Both = 1000000, kBlkMinF64Crowded = 250000, kNodeMaxF64Both = 250000;
+// FP64 with gathers: blocks from 400 k points (with interpolation on 0.6 M leaves
+// 205 us, 238 by ranges, 208 by tiles; 1 M 294, 478, 354) or where four to a leaf
+// are there (400 k on 14 k leaves 204, 236, 287), ranges below that (200 k on 2.7 M
+// leaves 215 by ranges, 392 by tiles; markers there 197 and 150).
+constexpr int64_t kBlkMinF64Both = 400000, kBlkMinF64Crowded = 250000, kNodeMaxF64Both = 250000;
 // Plans that do not spread have only the sharing of lookups and field rows to
-// gain, so their line also asks for leaves that caches do not hold: 4 M random
-// points, interpolation, tiles of points sorted by host against block pass, on
-// 14 k leaves 261 against 321 us, 38 k 273 against 283, 0.6 M 366 -> 293, 2.7 M
-// 449 -> 322 (10^7: 705 against 733, 736 -> 657, 902 -> 675, 978 -> 702); on 512
-// leaves, one block, 10^7 points took 643 against 1907.
-constexpr int64_t kBlkMinGatherLeaves = 131072;
+// gain, so their line also asks for leaves that caches do not hold, or for more
+// points; and a root of more than one cube, since a sort by one block has one
+// digit.  Interpolation, FP32, tiles of points sorted by host against block
+// pass: 4 M random points on 14 k leaves 261 and 321 us, 38 k 273 and 283, 0.6 M 366
+// and 293, 2.7 M 449 and 322; 10^7 on 14 k 705 and 733 (markers 853 and 581), 38 k
+// 736 and 657, on 512 leaves, one cube, 643 and 1907; 2 M on 4,096 leaves without
+// sub-tables 146 and 143.  With both outputs blocks gain less (14 k leaves, 10^7
+// points, 1020 and 1146).
+constexpr int64_t kBlkMinGatherLeaves = 131072, kBlkMinGatherFew = 8000000;
 // FP32 atomic sums in FP64 (blocks and ranges) cost 60 bytes a leaf and a launch
 // where FP32 ones cost 12: 10 us a million leaves, 0.18 ms of 17 M.  On larger
 // trees than this plans keep to tiles of points sorted by host and FP32 sums (100 k
@@ -201,7 +204,11 @@ SortedRoute sorted_route(const ot_tree *t, int64_t n, int ops, int dtype, int mo
     const bool blocks = t->view.lev[0] >= kBlkBits && n >= 64 * (int64_t)t->view.nblk && n < (int64_t(1) << 31);
     if (!(ops & ~kOpLocate) || (f32_sums && !wide_fits(t, n, plan))) return r;
     if (!spread) {
-        r.blocks = blocks && n >= kBlkMinGather && t->n_leaves >= kBlkMinGatherLeaves;
+        const bool one_output = !(ops & kOpInterp) || !(ops & kOpGrad);
+        r.blocks = blocks && n >= kBlkMinGather &&
+                   (t->n_leaves >= kBlkMinGatherLeaves ||
+                    (one_output && t->view.lev[0] > kBlkBits &&
+                     (t->view.nblk == t->view.blk1 || n >= kBlkMinGatherFew)));
         return r;
     }
     const bool dense = 3 * n >= t->n_leaves;
@@ -228,14 +235,20 @@ bool plain_sorts(const ot_tree *t, int64_t n, int ops, int dtype, int mode)
 
 // Sorted plans of so few points that the plain passes are faster unsorted
 // (30 k points on 38 k leaves: spreading 51 against 61 us, interpolation 10
-// against 47; 100 k: spreading 66 sorted against 134, interpolation 16).  Not
-// for atomic spreading: an unsorted pass adds to a leaf more often, and the
-// sums were up to 3 times less exact (FP64, 50 k random points on 4,096 leaves
-// 3.5e-16 -> 6.4e-16, on 512 leaves 4.3e-16 -> 1.3e-15).
-bool small_rule(const ot_tree *t, int64_t n, int ops)
+// against 47; 100 k: spreading 66 sorted against 134, interpolation 16; on 512
+// leaves at any size, 390 k points 71 against 219).  Not for atomic spreading:
+// an unsorted pass adds to a leaf more often, and the sums were up to 3 times
+// less exact (FP64, 50 k random points on 4,096 leaves 3.5e-16 -> 6.4e-16, on 512
+// leaves 4.3e-16 -> 1.3e-15).  FP64 sums of up to 1,024 points, in 37 workgroups
+// of 28, are as exact as those of 16 tiles of 64 (13 us against 30).
+constexpr int64_t kSmallAtomic = 1024;
+bool small_rule(const ot_tree *t, int64_t n, int ops, int dtype, int mode)
 {
-    if (n > 0 && (ops & kOpSpread) && t->n_leaves <= kFewLeaves) return true;   // (390 k points 219 sorted, 71 us)
-    return n > 0 && (ops & ~kOpLocate) && n < ((ops & kOpSpread) ? kSortMinSpread : int64_t(100000));
+    if (n <= 0 || !(ops & ~kOpLocate)) return false;
+    if (!(ops & kOpSpread)) return n < 100000;
+    const bool atomic = mode == OT_SPREAD_ATOMIC;
+    if (t->n_leaves <= kFewLeaves) return !atomic;
+    return atomic ? dtype == OT_F64 && n <= kSmallAtomic : n < kSortMinSpread;
 }
 
 }  // namespace ot

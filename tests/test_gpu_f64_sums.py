@@ -37,7 +37,7 @@ def _inputs(level, n, order):
 
 
 @pytest.mark.parametrize("order", ["random", "host"])
-@pytest.mark.parametrize("n", [3000, 50_000, 65_000, 100_000])
+@pytest.mark.parametrize("n", [1024, 1025, 3000, 50_000, 65_000, 100_000])
 def test_sorted_plan(n, order):
     import paper_2605_20565_amd as ot
     spec, t, X, V, err = _inputs(4, n, order)
