@@ -160,19 +160,19 @@ typedef struct {
  * below one split root cell) are sorted by block, and each block with enough
  * points is worked on as a dense grid of its stencil nodes in LDS, the other
  * blocks' points in short ranges; smaller runs that spread take such ranges
- * of points sorted by host.
- * Otherwise the points are sorted by host leaf, down to groups of at most 64
- * consecutive ids (two passes up to 4 M leaves, three above), so that
- * neighbouring threads share stencil nodes in cache and in the workgroup's
- * spreading table.  Runs of few points (under 55,000 that spread, under
- * 100,000 that do not) and runs that spread on at most 512 leaves are not
+ * of points sorted by host.  Otherwise the points are sorted by host leaf,
+ * down to groups of at most 64 consecutive ids (two passes up to 4 M leaves,
+ * three above), so that neighbouring threads share stencil nodes in cache and
+ * in the workgroup's spreading table.  Runs of few points (under 55,000 that
+ * spread, under 100,000 that do not) and runs that spread on at most 512 leaves are not
  * sorted at all unless OT_TUNE_HOST_MAJOR asks for it or they spread with
- * OT_SPREAD_ATOMIC (FP64: more than 1,024 points).  FP32 plans that do, on trees that their points are not
- * too few for, keep their sums in FP64 (a plan-owned buffer of
- * ot_spread_workspace_bytes) and round them once at the end of a run.  block,
- * tile and grid shape the tiles of points sorted by host leaf only: blocks,
- * ranges and runs that are not sorted have shapes of their own.  Results are
- * the same bit for bit (FIXED).  Needs the same ops for every instance. */
+ * OT_SPREAD_ATOMIC (FP64: more than 1,024 points).  FP32 plans that do, on
+ * trees that their points are not too few for, keep their sums in FP64 (a
+ * plan-owned buffer of ot_spread_workspace_bytes) and round them once at the
+ * end of a run.  block, tile and grid shape the tiles of points sorted by host
+ * leaf only: blocks, ranges and runs that are not sorted have shapes of their
+ * own.  Results are the same bit for bit (FIXED).  Needs the same ops for
+ * every instance. */
 #define OT_TUNE_SORT_POINTS 1
 
 /* Host-major pass for sorted plans whose instances interpolate or spread

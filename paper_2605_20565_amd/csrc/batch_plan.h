@@ -31,7 +31,8 @@ struct SortedRoute {
 };
 SortedRoute sorted_route(const ot_tree *t, int64_t n, int ops, int dtype, int mode, bool plan);
 bool plain_sorts(const ot_tree *t, int64_t n, int ops, int dtype, int mode);   // a plain call's points
-bool small_rule(const ot_tree *t, int64_t n, int ops, int dtype, int mode);   // a sorted plan takes the unsorted passes of plain calls
+// whether a sorted plan takes the unsorted passes of plain calls
+bool small_rule(const ot_tree *t, int64_t n, int ops, int dtype, int mode);
 // plain calls that spread sort from here on (track.hip)
 constexpr int64_t kSortMinSpread = 55000, kSortMinF32Sums = 30000, kSortMinF64Both = 65536;
 constexpr int64_t kFewLeaves = 512;   // a tree that the smallest spreading table holds (track.hip)

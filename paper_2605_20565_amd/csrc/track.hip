@@ -47,7 +47,7 @@ constexpr int kMaxPointsPerThread = 4;
 // markers in order on few leaves are faster there: 100 k 66 against 134 us a
 // call).  A whole fused FP32 fixed-point call on 11 k points: 53.5 -> 25.9 us
 // (three launches instead of five).
-constexpr int64_t kNodesMaxSpread = 65535;   // sums in FP32 apart (run_pass)
+constexpr int64_t kNodesMaxSpread = 65535;   // sums in FP32 apart (nodes_max)
 constexpr int64_t kNodesMaxGather = 16384;
 // Trees of so few leaves that the smallest spreading table holds them all: the
 // per-point pass then adds a leaf's sum to device memory once a workgroup in
